@@ -1277,26 +1277,6 @@ hipError_t nn_apply_folded(const qiral_nn *nn, void *out0, void *out1, const voi
   return hipGetLastError();
 }
 
-// D on a packed full field (out = A in - kappa H in, A = 1 + 2 i kappa mu gamma_5), precision prec
-hipError_t apply_D_full(const qiral_lattice *lat, int prec, void *out, const void *in, hipStream_t s) {
-  const size_t hb = half_bytes(lat->geo, prec);
-  const char *ie = (const char *)in, *io = ie + hb;
-  char *oe = (char *)out, *oo = oe + hb;
-  hipError_t e = launch_hop(lat, prec, 0, 0, 1, -lat->kappa, io, oe, ie, 1, s, CHI_ONE, CHI_A);
-  if (e != hipSuccess) return e;
-  return launch_hop(lat, prec, 0, 1, 1, -lat->kappa, ie, oo, io, 1, s, CHI_ONE, CHI_A);
-}
-
-// D^dagger on a packed full field (out = A^dagger in - kappa H^dagger in)
-hipError_t apply_Ddag_full(const qiral_lattice *lat, int prec, void *out, const void *in, hipStream_t s) {
-  const size_t hb = half_bytes(lat->geo, prec);
-  const char *ie = (const char *)in, *io = ie + hb;
-  char *oe = (char *)out, *oo = oe + hb;
-  hipError_t e = launch_hop(lat, prec, 1, 0, 1, -lat->kappa, io, oe, ie, 1, s, CHI_ONE, CHI_ADAG);
-  if (e != hipSuccess) return e;
-  return launch_hop(lat, prec, 1, 1, 1, -lat->kappa, ie, oo, io, 1, s, CHI_ONE, CHI_ADAG);
-}
-
 void neumann2(int hidden, double kappa, std::vector<float2> &w) {
   // layer 1: ch0 = psi (identity path), ch1 = H psi; layer 2: psi + kappa ch1 + kappa^2 H ch1.
   // Spin matrices 1 -+ gamma_mu of the chiral basis gamma_mu = [[0, B],[B^+, 0]],
@@ -1552,7 +1532,7 @@ extern "C" qiral_status qiral_nn_train(qiral_nn *nn, int32_t steps, double lr, u
     const unsigned long long ctr = (unsigned long long)nn->adam_step;
     hipLaunchKernelGGL(k_gauss, dim3(nb), dim3(256), 0, s, g, nn->fv, make_uint2((unsigned)seed, (unsigned)(seed >> 32)),
                        ctr, nn->part);
-    QIRAL_HIP(apply_D_full(nn->lat, QIRAL_F32, nn->fb, nn->fv, s));
+    QIRAL_HIP(launch_D(nn->lat, QIRAL_F32, 0, nn->fb, nn->fv, 1, s));
     QIRAL_HIP(train_step(nn, nn->fb, nn->fv, nn->loss_dev + k % LOSS_CAP, s));
     nn->adam_step += 1;
     const float c1 = 1.f - powf(b1, (float)nn->adam_step), c2 = 1.f - powf(b2, (float)nn->adam_step);
@@ -1697,18 +1677,10 @@ qiral_status flex_setup(qiral_lattice *lat, const qiral_solve_params *prm, void 
 }
 
 // y = A x or A^dagger x in FP64 (A = D, or S = A_oo - kappa^2 H_oe A_ee^-1 H_eo)
-// for nsys consecutive vectors (the Schur operator's hops take them together)
+// for nsys consecutive vectors, taken together
 hipError_t flex_A(const Flex &f, void *y, const void *x, bool dag, hipStream_t s, int nsys = 1) {
   const qiral_lattice *lat = f.lat;
-  if (!f.schur) {
-    for (int k = 0; k < nsys; ++k) {
-      void *yk = (char *)y + (size_t)k * f.vb;
-      const void *xk = (const char *)x + (size_t)k * f.vb;
-      hipError_t e = dag ? apply_Ddag_full(lat, QIRAL_F64, yk, xk, s) : apply_D_full(lat, QIRAL_F64, yk, xk, s);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
+  if (!f.schur) return launch_D(lat, QIRAL_F64, dag, y, x, nsys, s);
   const double k = lat->kappa;
   hipError_t e = launch_hop(lat, QIRAL_F64, dag, 0, 0, 1.0, x, f.tmpE, nullptr, nsys, s,
                             dag ? CHI_AINVDAG : CHI_AINV, CHI_ONE);
@@ -1824,7 +1796,7 @@ qiral_status flex_end(const Flex &f, const double2 *X, double *x_canon, double &
     // x_e = A^-1 (b_e + kappa H_eo x_o)
     QIRAL_HIP(launch_hop(lat, QIRAL_F64, 0, 0, 1, lat->kappa, xo, xe, f.BF, 1, s, CHI_AINV, CHI_ONE));
   }
-  QIRAL_HIP(apply_D_full(lat, QIRAL_F64, f.RF, f.XF, s));
+  QIRAL_HIP(launch_D(lat, QIRAL_F64, 0, f.RF, f.XF, 1, s));
   const size_t nf = 2 * f.hb64 / 16;
   hipLaunchKernelGGL(k_bminus, dim3(nblk(nf)), dim3(256), 0, s, f.BF, f.RF, nf);
   hipLaunchKernelGGL(k_norm, dim3(nblk(nf)), dim3(256), 0, s, f.RF, nf, f.npart);

@@ -73,9 +73,19 @@ int hop_zb(const Geo &g);
 int hop_tile(const Geo &g, int ngroups, int tuned = 0);
 int tuned_nr(const qiral_lattice *lat, int prec, int nrhs);
 HopCfg hop_config(const qiral_lattice *lat, int prec, long nrhs);
-hipError_t launch_hop_cfg(const HopCfg &c, const qiral_lattice *lat, int prec, int dagger, int out_parity, int epi,
-                          double a, const void *in, void *out, const void *x, int nrhs, hipStream_t s,
-                          int chio = 0, int chix = 0);
+// What a hop computes: see launch_hop.  p = -1: in, out and x are full fields
+// and both output parities are computed.
+struct HopCall {
+  int dagger, p, epi;
+  double a;
+  const void *in;
+  void *out;
+  const void *x;
+  int nrhs;
+  hipStream_t st;
+  int chio = 0, chix = 0;
+};
+hipError_t launch_hop_cfg(const HopCfg &c, const qiral_lattice *lat, int prec, const HopCall &h);
 
 // Grid of ceil(nwaves / 4) work-groups (4 waves of 64 lanes each).
 inline int wg_count(long nwaves) { return (int)((nwaves + 3) / 4); }
@@ -86,6 +96,8 @@ inline int wg_count(long nwaves) { return (int)((nwaves + 3) / 4); }
 // the identity for CHI_ONE or mu = 0).
 hipError_t launch_hop(const qiral_lattice *lat, int prec, int dagger, int out_parity, int epi, double a,
                       const void *in, void *out, const void *x, int nrhs, hipStream_t s, int chio = 0, int chix = 0);
+// out = D in (or D^dagger in) on nrhs consecutive full fields.
+hipError_t launch_D(const qiral_lattice *lat, int prec, int dagger, void *out, const void *in, int nrhs, hipStream_t s);
 
 // The checks of qiral_solve's arguments that do not read the handle, the
 // handle's links of the inner precision, and the solve itself in a workspace

@@ -121,9 +121,9 @@ extern "C" qiral_status qiral_tune(qiral_lattice *lat, qiral_prec prec, int32_t 
           c.nr = n;
           c.tile = groups ? tl : 0;
           const int reps = 10;
-          for (int w = 0; w < 2; ++w) (void)launch_hop_cfg(c, lat, prec, 0, 0, 0, 1.0, in, out, nullptr, nrhs, s);
+          for (int w = 0; w < 2; ++w) (void)launch_hop_cfg(c, lat, prec, HopCall{0, 0, 0, 1.0, in, out, nullptr, nrhs, s});
           (void)hipEventRecord(e0, s);
-          for (int r = 0; r < reps; ++r) (void)launch_hop_cfg(c, lat, prec, 0, 0, 0, 1.0, in, out, nullptr, nrhs, s);
+          for (int r = 0; r < reps; ++r) (void)launch_hop_cfg(c, lat, prec, HopCall{0, 0, 0, 1.0, in, out, nullptr, nrhs, s});
           (void)hipEventRecord(e1, s);
           e = hipEventSynchronize(e1);
           if (e != hipSuccess) break;

@@ -1,0 +1,51 @@
+"""Launch paths chosen by a rule on sizes, at the sizes where they can go wrong,
+against the complex128 oracle.  Tolerances: FP64 1e-12 and FP32 2e-6 relative
+(5e-6 of the largest element), F16S half an FP16 ulp of each site's scale plus
+FP32 rounding, as for the operators in general."""
+import numpy as np
+import pytest
+import torch
+
+import latgen
+from oracle import ptc, storage, wilson as W
+import paper_1401_2039_amd as q
+from gpu_util import say, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+def _rounded(cfg, prec):
+    U, b = cfg["U"], cfg["b"]
+    if prec == q.F64:
+        return U, b
+    if prec == q.F32:
+        return storage.round_links_r12(U, np.complex64), storage.round_f32(b)
+    return storage.round_links_r12(U, "f16"), storage.round_f16s(b)
+
+
+def _check(got, want, prec):
+    d = np.abs(got - want)
+    if prec == q.F64:
+        assert d.max() < 1e-12 * np.abs(want).max()
+    elif prec == q.F32:
+        assert np.sqrt(W.norm2(got - want) / W.norm2(want)) < 2e-6 and d.max() < 5e-6 * np.abs(want).max()
+    else:
+        scale = np.abs(np.stack([want.real, want.imag])).reshape(2, -1, 12).max(axis=(0, 2))
+        assert np.all(d.reshape(-1, 12).max(axis=1) <= 2.0 ** -11 * 1.01 * scale + 1e-6 * scale.max())
+
+
+# one launch of D takes both output parities of every right-hand side: an odd
+# number of fields (a short last group), a ragged last block, one block, two
+@pytest.mark.parametrize("prec", [q.F64, q.F32, q.F16S], ids=["f64", "f32", "f16s"])
+@pytest.mark.parametrize("dims,nrhs", [((6, 4, 2, 4), 5), ((2, 2, 2, 2), 3), ((4, 4, 4, 4), 2), ((6, 10, 2, 8), 1)])
+def test_full_operator_of_several_fields(dims, nrhs, prec):
+    say("D of several fields", dims, nrhs, prec)
+    cfg = latgen.small_config(dims, seed=81, kind="expih", eps=0.4, nrhs=nrhs)
+    lat = q.Lattice(dims, 0.12, cfg["U"], mu=0.35)
+    Ur, br = _rounded(cfg, prec)
+    inp, out = lat.import_field(dev(cfg["b"]), q.FULL, prec), lat.field(q.FULL, prec, nrhs)
+    for op, ref in ((q.OP_D, W.apply_D), (q.OP_DDAG, W.apply_Ddag)):
+        lat.apply_M(out, inp, None, op, prec, nrhs)
+        got = host(lat.export_field(out, q.FULL, prec, nrhs=nrhs))
+        for r in range(nrhs):
+            _check(got[r], ref(Ur, 0.12, 0.35, br[r]), prec)
