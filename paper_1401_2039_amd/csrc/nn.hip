@@ -29,16 +29,16 @@ struct qiral_nn {
   int hidden = 0;
   int nw1 = 0, nw2 = 0;     // complex weights per layer
   float2 *w = nullptr;      // [nw1 + nw2]
-  float2 *wadj = nullptr;   // adjoint-layer weights (scratch)
   float2 *kmat = nullptr;   // folded path-pair weights K, then K' (scratch)
-  void *kfrag = nullptr;    // MFMA A fragments of K, then of K' (scratch)
+  void *kfrag = nullptr;    // bf16 MFMA A fragments of K's hop pairs, then of K' (scratch)
+  float *kfrag32 = nullptr; // FP32 MFMA A fragments of K, then of K' (scratch)
   float *am = nullptr, *av = nullptr;   // Adam moments, [2 (nw1 + nw2)]
   double *grad = nullptr;   // dL/dRe, dL/dIm interleaved, [2 (nw1 + nw2)]
-  double *part = nullptr;   // weight-gradient partials
+  double *part = nullptr;   // partial sums of the gradient, the loss and the norms
+  double *dk = nullptr;     // their sum over the work-groups: the gradient of K (DK_VALUES)
   double *scal = nullptr;   // small reductions: [0] ||v||^2, [1] loss sum, ... ; plus partial area
-  void *act = nullptr;      // hidden activations (H full F32 fields)
-  void *gact = nullptr;     // gradient w.r.t. the activations (H fields)
-  void *fv = nullptr, *fb = nullptr, *fy = nullptr, *fg = nullptr;   // one full F32 field each
+  void *paths = nullptr;    // the nine path fields m_p (full F32 fields)
+  void *fv = nullptr, *fb = nullptr, *fg = nullptr;   // one full F32 field each
   double *loss_dev = nullptr;   // losses of up to LOSS_CAP training steps
   long adam_step = 0;
 };
@@ -46,7 +46,11 @@ struct qiral_nn {
 namespace {
 
 constexpr int NPATH = 9;
-constexpr int WG_CHUNKS = 64;   // site chunks of the weight-gradient reduction
+constexpr int MT32 = 5;          // 16-row tiles of the real form of K (9 paths x 4 spins x re/im = 72 rows)
+constexpr int KS32 = 18;         // its 4-column steps
+constexpr int FRAG32 = MT32 * KS32 * 64;   // floats of its FP32 MFMA fragments
+constexpr int DK_VALUES = MT32 * MT32 * 256;   // doubles of the gradient of K as MFMA tiles
+constexpr int DK_WGS = 512;      // most work-groups of the gradient kernel: two per compute unit
 constexpr int LOSS_CAP = 256;    // training losses kept on the device between copies to the host
 
 qiral_status fail(qiral_status s, const char *m) {
@@ -103,148 +107,72 @@ __device__ __forceinline__ void path_apply(const Geo &g, const void *links, cons
 // ---------------------------------------------------------------------------
 // kernels
 
-// One layer (training), CI output channels per pass of each thread over the
-// paths.
-template <int CIN, int COUT, int CI>
-__global__ __launch_bounds__(256) void k_ptc_layer(Geo g, const void *__restrict__ links,
-                                                   const float2 *__restrict__ w, const void *__restrict__ in,
-                                                   void *__restrict__ out, size_t fstride) {
-  __shared__ float2 sw[NPATH * COUT * CIN * 16];
-  for (int i = threadIdx.x; i < NPATH * COUT * CIN * 16; i += blockDim.x) sw[i] = w[i];
-  __syncthreads();
-  const size_t npad = (size_t)g.nb * WAVE, hb = npad * SpinorIO<S_F32>::SITE_BYTES;
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= 2 * npad) return;
-  const int par = (int)(gid / npad), s = (int)(gid % npad);
-  if (s >= g.vh) return;
-  const SiteC c = site_c(g, s, par);
-  if constexpr (COUT == 1 && CIN > 1) {
-    // Spin weights commute with the colour transport: per path, mix the CIN
-    // input channels at the neighbour, then transport once.
-    cpx<float> acc[12];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) acc[k] = cmake(0.f, 0.f);
-#pragma unroll 1
-    for (int p = 0; p < NPATH; ++p) {
-      int mu = 0, n = s, lp = par;
-      bool fwd = true;
-      if (p > 0) {
-        path_of(p, mu, fwd);
-        n = nbr(g, c, mu, fwd);
-        lp = 1 - par;
-      }
-      cpx<float> m[12];
-#pragma unroll
-      for (int k = 0; k < 12; ++k) m[k] = cmake(0.f, 0.f);
-#pragma unroll 1
-      for (int j = 0; j < CIN; ++j) {
-        cpx<float> psi[12];
-        SpinorIO<S_F32>::load((const char *)in + j * fstride + lp * hb, n, npad, psi);
-        const float2 *W = sw + (p * CIN + j) * 16;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const cpx<float> wr = cmake(W[4 * r + q].x, W[4 * r + q].y);
-#pragma unroll
-            for (int a = 0; a < 3; ++a) m[4 * a + r] = cmac(wr, psi[4 * a + q], m[4 * a + r]);
-          }
-      }
-      if (p == 0) {
-#pragma unroll
-        for (int k = 0; k < 12; ++k) acc[k] = cadd(acc[k], m[k]);
-      } else {
-        cpx<float> u[9], t[12];
-        if (fwd) LinkIO<L_F32R12>::load(links, par, mu, c.s, g.nb, u);
-        else LinkIO<L_F32R12>::load(links, 1 - par, mu, n, g.nb, u);
-        transport(u, m, t, !fwd);
-#pragma unroll
-        for (int k = 0; k < 12; ++k) acc[k] = cadd(acc[k], t[k]);
-      }
-    }
-    SpinorIO<S_F32>::store((char *)out + par * hb, s, npad, acc);
-    return;
-  }
-#pragma unroll 1
-  for (int i0 = 0; i0 < COUT; i0 += CI) {
-    cpx<float> acc[CI][12];
-#pragma unroll
-    for (int ii = 0; ii < CI; ++ii)
-#pragma unroll
-      for (int k = 0; k < 12; ++k) acc[ii][k] = cmake(0.f, 0.f);
-#pragma unroll 1
-    for (int p = 0; p < NPATH; ++p) {
-#pragma unroll 1
-      for (int j = 0; j < CIN; ++j) {
-        cpx<float> t[12];
-        path_apply(g, links, (const char *)in + j * fstride, hb, npad, c, par, p, t);
-#pragma unroll
-        for (int ii = 0; ii < CI; ++ii) {
-          const float2 *W = sw + ((p * COUT + i0 + ii) * CIN + j) * 16;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const cpx<float> wr = cmake(W[4 * r + q].x, W[4 * r + q].y);
-#pragma unroll
-              for (int a = 0; a < 3; ++a) acc[ii][4 * a + r] = cmac(wr, t[4 * a + q], acc[ii][4 * a + r]);
-            }
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int ii = 0; ii < CI; ++ii)
-      SpinorIO<S_F32>::store((char *)out + (i0 + ii) * fstride + par * hb, s, npad, acc[ii]);
-  }
-}
-
-// Adjoint-layer weights: W'[mirror(p)][j][i] = (W[p][i][j])^dagger, so that the
-// forward layer with W' (CIN and COUT swapped) applies the adjoint.
-__global__ void k_adj_weights(const float2 *__restrict__ w, float2 *__restrict__ wa, int cout, int cin) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = NPATH * cout * cin * 16;
-  if (idx >= n) return;
-  const int e = idx & 15, blk = idx >> 4;
-  const int j = blk % cin, i = (blk / cin) % cout, p = blk / (cin * cout);
-  const int pm = p == 0 ? 0 : (p <= 4 ? p + 4 : p - 4);
-  const int r = e >> 2, q = e & 3;
-  const float2 v = w[((p * cout + i) * cin + j) * 16 + 4 * q + r];
-  wa[((pm * cin + j) * cout + i) * 16 + 4 * r + q] = make_float2(v.x, -v.y);
-}
-
 // ---------------------------------------------------------------------------
-// Inference with the two layers folded.  The layers are linear and a spin
-// matrix commutes with a colour transport, so
+// The two layers folded.  The layers are linear and a spin matrix commutes with
+// a colour transport, so
 //     N = sum_{p,p'} T_p K_{pp'} T_{p'},   K_{pp'} = sum_c W2_p^c W1_{p'}^c,
 // and N^dagger has the same form with K'_{pp'} = (K_{m(p') m(p)})^dagger, m the
 // mirror path (T_p^dagger = T_{m(p)}).  Pass A forms m_p(y) = sum_{p'} K_{pp'}
 // (T_{p'} v)(y) at every site, pass B sums out(x) = sum_p (T_p m_p)(x): one
 // transport per path and a spin product per path pair, where the layers take a
 // transport and H spin products per path in each layer and pass the H hidden
-// fields through memory nine times.
+// fields through memory nine times.  Training folds too: the loss depends on
+// the weights through K alone, so its gradient is that of K (k_nn_dk) carried
+// on to the weights by the two 4x4 products of K's definition (k_nn_dw), and no
+// kernel over the sites sees the hidden channels.
 
 __device__ __forceinline__ int mirror_path(int p) { return p == 0 ? 0 : (p <= 4 ? p + 4 : p - 4); }
 
-// K (adj = 0) or K' (adj = 1) into k[p][p'][4][4], summed over the H channels
-// in FP64; one thread per entry.
-__global__ void k_nn_fold(const float2 *__restrict__ w1, const float2 *__restrict__ w2, int hidden, int adj,
-                          float2 *__restrict__ k) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= NPATH * NPATH * 16) return;
-  const int e = idx & 15, pq = idx >> 4, p = pq / NPATH, q = pq % NPATH;
+// Entry (r, c) of K_pq (adj = 0) or K'_pq (adj = 1), summed over the H channels
+// in FP64.
+__device__ __forceinline__ float2 fold_entry(const float2 *__restrict__ w1, const float2 *__restrict__ w2, int hidden,
+                                             int adj, int p, int q, int r, int c) {
   const int P = adj ? mirror_path(q) : p, Q = adj ? mirror_path(p) : q;
-  const int r = adj ? e & 3 : e >> 2, c = adj ? e >> 2 : e & 3;
+  const int rr = adj ? c : r, cc = adj ? r : c;
   double re = 0.0, im = 0.0;
   for (int h = 0; h < hidden; ++h) {
     const float2 *a = w2 + (P * hidden + h) * 16, *b = w1 + (Q * hidden + h) * 16;
+#pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const float2 x = a[4 * r + j], y = b[4 * j + c];
+      const float2 x = a[4 * rr + j], y = b[4 * j + cc];
       re += (double)x.x * y.x - (double)x.y * y.y;
       im += (double)x.x * y.y + (double)x.y * y.x;
     }
   }
-  k[idx] = make_float2((float)re, (float)(adj ? -im : im));
+  return make_float2((float)re, (float)(adj ? -im : im));
+}
+
+// K (blockIdx.y = 0) and K' (1) into k[adj][p][p'][4][4]; one thread per entry.
+__global__ void k_nn_fold(const float2 *__restrict__ w1, const float2 *__restrict__ w2, int hidden,
+                          float2 *__restrict__ k) {
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x, adj = blockIdx.y;
+  if (idx >= NPATH * NPATH * 16) return;
+  const int e = idx & 15, pq = idx >> 4;
+  k[adj * NPATH * NPATH * 16 + idx] = fold_entry(w1, w2, hidden, adj, pq / NPATH, pq % NPATH, e >> 2, e & 3);
+}
+
+// Row and column of the real form of a complex matrix entry: the (re, im) of
+// the product k x are k.re x.re - k.im x.im and k.im x.re + k.re x.im.
+__device__ __forceinline__ float real_form(float2 k, int row, int col) {
+  return row == 0 ? (col == 0 ? k.x : -k.y) : (col == 0 ? k.y : k.x);
+}
+
+// FP32 MFMA (16x16x4) A fragments of the real form of K (adj0) or K':
+// f[(mt * KS32 + ks) * 64 + lane].  Row lane % 16 of M-tile mt is the real
+// 16 mt + lane % 16 of the output in the order (path, spin, re/im), zero past
+// the 72nd.  The four columns of step ks, one per lane group lane / 16: for
+// ks < 16 the real ks % 8 (spin, re/im) of the input paths 1 + 4 (ks / 8) +
+// group, for ks = 16, 17 the reals 4 (ks - 16) + group of path 0.
+__global__ void k_nn_frag32(const float2 *__restrict__ w1, const float2 *__restrict__ w2, int hidden, int adj0,
+                            float *__restrict__ f) {
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x, adj = adj0 + blockIdx.y;
+  if (idx >= FRAG32) return;
+  const int lane = idx & 63, ks = (idx >> 6) % KS32, mt = (idx >> 6) / KS32, g = lane >> 4;
+  const int row = 16 * mt + (lane & 15), p = row >> 3;
+  const int q = ks < 16 ? 1 + 4 * (ks >> 3) + g : 0, e = ks < 16 ? ks & 7 : 4 * (ks - 16) + g;
+  float v = 0.f;
+  if (p < NPATH) v = real_form(fold_entry(w1, w2, hidden, adj, p, q, (row & 7) >> 1, e >> 1), row & 1, e & 1);
+  f[adj * FRAG32 + idx] = v;
 }
 
 // A spinor of a field in storage class S (F32, or F64 rounded to F32).
@@ -259,67 +187,95 @@ __device__ __forceinline__ void load_as_f32(const void *half, int s, size_t npad
   }
 }
 
-// Pass A over both parities and all nine paths (vector ALU, FP32): the input's
-// half-fields are in0 (even) and in1 (odd), storage SIN; m_p is written to the
-// F32 half-field m + p * mstride + parity * (npad * 96 bytes).  Two waves share
-// a 64-site block, each sweeping the input paths for its own PC output paths,
-// so the second wave's neighbour loads hit the cache lines the first has just
-// brought in.  Site blocks in the hop's XCD-mapped order (zb as block_order).
-// Grid: (ceil(nb / 2), 2 parities), 256 threads: two site blocks.
-template <int SIN, int PC>
-__global__ __launch_bounds__(256) void k_nn_pass_a(Geo g, const void *__restrict__ links,
-                                                   const float2 *__restrict__ K, const void *__restrict__ in0,
-                                                   const void *__restrict__ in1, void *__restrict__ m,
-                                                   size_t mstride, int zb) {
-  const int ya = blockIdx.y;
+// Pass A over both parities and all nine paths on the FP32 matrix cores: the
+// input's half-fields are in0 (even) and in1 (odd), storage SIN; m_p is written
+// to the F32 half-field m + p * mstride + parity * (npad * 96 bytes).
+//
+// Per site and colour m is a 72x72 real matrix times the 72 reals of the nine
+// transported spinors (rows and columns (path, spin, re/im)), in FP32 throughout:
+// the same products as on the vector ALU, summed in another order, at twice its
+// rate.  A wave takes 16 sites at a time, its four lane groups one direction
+// each: lane (g, n) makes the transports of paths 1 + g and 5 + g at site n,
+// which is the B operand of the 16x16x4 MFMA as it stands (column n, row g of
+// the four), so nothing passes through LDS but K's fragments, read there by
+// every wave.  The accumulator rows of lane (g, n) are two complex spin
+// components of one path, colour and site, a float4 unit of the spinor layout,
+// and are stored as they are.  At 24^3x48 with the F32 input: 300 us (the
+// vector-ALU form, two waves per block sweeping the input paths for five and four
+// output paths, took 441).
+//
+// Work-groups of four waves walk the 64-site blocks of both parities in the
+// hop's XCD-mapped order, `nblk` of them, and keep the fragments.
+template <int SIN>
+__global__ __launch_bounds__(256, 3) void k_nn_pass_a(Geo g, const void *__restrict__ links,
+                                                      const float *__restrict__ frag, const void *__restrict__ in0,
+                                                      const void *__restrict__ in1, void *__restrict__ m,
+                                                      size_t mstride, int zb) {
+  __shared__ float lds_frag[FRAG32];
+  for (int i = threadIdx.x; i < FRAG32; i += 256) lds_frag[i] = frag[i];
+  __syncthreads();
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int L = xcd_remap(blockIdx.x, gridDim.x) * 2 + (w >> 1);
-  if (L >= g.nb) return;
-  const int s = block_order(g, L, zb) * WAVE + (threadIdx.x & (WAVE - 1));
-  if (s >= g.vh) return;
+  const int lane = threadIdx.x & (WAVE - 1), g4 = lane >> 4, n = lane & 15;
   const size_t npad = (size_t)g.nb * WAVE, hb = npad * SpinorIO<S_F32>::SITE_BYTES;
-  const int p0 = (w & 1) * PC, p1 = min(NPATH, p0 + PC);
-  const void *here = ya ? in1 : in0, *there = ya ? in0 : in1;
-  const SiteC c = site_c(g, s, ya);
-  cpx<float> acc[PC][12];
+  const float *A = lds_frag + lane;
+  for (int v = blockIdx.x; v < 2 * g.nb; v += gridDim.x) {
+    const int item = xcd_remap(v, 2 * g.nb), ya = item & 1;
+    const int sb = block_order(g, item >> 1, zb), s0 = sb * WAVE + 16 * w;
+    if (s0 >= g.vh) continue;
+    // lanes past the last site take part with the tile's first site and store nothing
+    const bool live = s0 + n < g.vh;
+    const int sl = live ? 16 * w + n : 16 * w, s = sb * WAVE + sl;
+    const void *here = ya ? in1 : in0, *there = ya ? in0 : in1;
+    const SiteC c = site_c(g, s, ya);
+    f32x4 D[MT32][3];
 #pragma unroll
-  for (int j = 0; j < PC; ++j)
+    for (int mt = 0; mt < MT32; ++mt)
 #pragma unroll
-    for (int k = 0; k < 12; ++k) acc[j][k] = cmake(0.f, 0.f);
-#pragma unroll 1
-  for (int q = 0; q < NPATH; ++q) {
-    cpx<float> t[12];
-    if (q == 0) {
-      load_as_f32<SIN>(here, s, npad, t);
-    } else {
-      int mu;
-      bool fwd;
-      path_of(q, mu, fwd);
-      const int n = nbr(g, c, mu, fwd);
-      cpx<float> u[9], psi[12];
-      if (fwd) LinkIO<L_F32R12>::load(links, ya, mu, s, g.nb, u);
-      else LinkIO<L_F32R12>::load(links, 1 - ya, mu, n, g.nb, u);
-      load_as_f32<SIN>(there, n, npad, psi);
-      transport(u, psi, t, !fwd);
-    }
+      for (int a = 0; a < 3; ++a) D[mt][a] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < PC; ++j) {
-      if (p0 + j >= p1) break;
-      const float2 *Kp = K + ((p0 + j) * NPATH + q) * 16;
+    for (int h = 0; h < 2; ++h) {
+      const int nb_ = nbr(g, c, g4, h == 0);
+      cpx<float> u[9], psi[12], t[12];
+      if (h == 0) LinkIO<L_F32R12>::load(links, ya, g4, s, g.nb, u);
+      else LinkIO<L_F32R12>::load(links, 1 - ya, g4, nb_, g.nb, u);
+      load_as_f32<SIN>(there, nb_, npad, psi);
+      transport(u, psi, t, h == 1);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+      for (int e = 0; e < 8; ++e) {
+        float af[MT32];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const cpx<float> kr = cmake(Kp[4 * r + e].x, Kp[4 * r + e].y);
+        for (int mt = 0; mt < MT32; ++mt) af[mt] = A[(mt * KS32 + 8 * h + e) * WAVE];
 #pragma unroll
-          for (int a = 0; a < 3; ++a) acc[j][4 * a + r] = cmac(kr, t[4 * a + e], acc[j][4 * a + r]);
+        for (int a = 0; a < 3; ++a) {
+          const float b = (e & 1) ? t[4 * a + (e >> 1)].im : t[4 * a + (e >> 1)].re;
+#pragma unroll
+          for (int mt = 0; mt < MT32; ++mt) D[mt][a] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[mt], b, D[mt][a], 0, 0, 0);
         }
+      }
     }
-  }
 #pragma unroll
-  for (int j = 0; j < PC; ++j) {
-    if (p0 + j >= p1) break;
-    SpinorIO<S_F32>::store((char *)m + (size_t)(p0 + j) * mstride + ya * hb, s, npad, acc[j]);
+    for (int e = 0; e < 2; ++e) {   // path 0: lane group g4 takes the real 4 e + g4 of each colour
+      float af[MT32];
+#pragma unroll
+      for (int mt = 0; mt < MT32; ++mt) af[mt] = A[(mt * KS32 + 16 + e) * WAVE];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        float b;
+        if constexpr (SIN == S_F32) b = ((const float *)here)[(((size_t)sb * 6 + 2 * a + e) * WAVE + sl) * 4 + g4];
+        else b = (float)((const double *)here)[(((size_t)sb * 12 + 4 * a + 2 * e + (g4 >> 1)) * WAVE + sl) * 2 + (g4 & 1)];
+#pragma unroll
+        for (int mt = 0; mt < MT32; ++mt) D[mt][a] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[mt], b, D[mt][a], 0, 0, 0);
+      }
+    }
+    if (!live) continue;
+#pragma unroll
+    for (int mt = 0; mt < MT32; ++mt) {
+      const int p = 2 * mt + (g4 >> 1);
+      if (p >= NPATH) continue;
+      float4 *dst = (float4 *)((char *)m + (size_t)p * mstride + ya * hb) + ((size_t)sb * 6 + (g4 & 1)) * WAVE + sl;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) dst[2 * a * WAVE] = make_float4(D[mt][a][0], D[mt][a][1], D[mt][a][2], D[mt][a][3]);
+    }
   }
 }
 
@@ -351,23 +307,20 @@ __global__ __launch_bounds__(256) void k_nn_pass_a(Geo g, const void *__restrict
 // Path field p of a system starts at p * mstride and its parity-x half at
 // x * hoff (hoff = 0: each path field holds only the parity it is used on).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // A fragments of the real form of K (or K') over the hop pairs, bf16 hi and lo:
 // f[(((mt * 2 + ks) * 2 + hl) * 64 + lane) * 8 + kk]; row lane % 16 of M-tile mt
 // is (p = 1 + 2 mt + row / 8, spin (row % 8) / 2, re/im row % 2); kk is (spin
 // kk / 2, re/im kk % 2) of input path q = 1 + 4 ks + lane / 16.
 __global__ void k_nn_frag(const float2 *__restrict__ K, __bf16 *__restrict__ f) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x, adj = blockIdx.y;   // K, then K'
   if (idx >= 4 * 2 * 2 * 64 * 8) return;
   const int kk = idx & 7, lane = (idx >> 3) & 63, hl = (idx >> 9) & 1, ks = (idx >> 10) & 1, mt = idx >> 11;
   const int row = lane & 15, r = (row & 7) >> 1, c = row & 1, e = kk >> 1, ci = kk & 1;
   const int p = 1 + 2 * mt + (row >> 3), q = 1 + 4 * ks + (lane >> 4);
-  const float2 k = K[(p * NPATH + q) * 16 + 4 * r + e];
-  // (re, im) of the product k x: re = k.re x.re - k.im x.im, im = k.im x.re + k.re x.im
-  const float v = c == 0 ? (ci == 0 ? k.x : -k.y) : (ci == 0 ? k.y : k.x);
+  const float v = real_form(K[adj * NPATH * NPATH * 16 + (p * NPATH + q) * 16 + 4 * r + e], c, ci);
   const __bf16 hi = (__bf16)v;
-  f[idx] = hl == 0 ? hi : (__bf16)(v - (float)hi);
+  f[adj * 4 * 2 * 2 * 64 * 8 + idx] = hl == 0 ? hi : (__bf16)(v - (float)hi);
 }
 
 template <int SIN>
@@ -493,6 +446,19 @@ __global__ __launch_bounds__(256, 3) void k_nn_pass_a_mfma(Geo g, const void *__
   }
 }
 
+// acc = sum_p (T_p m_p)(x) at site x = (px, c.s) of the path fields m.
+__device__ __forceinline__ void path_sum(const Geo &g, const void *links, const char *m, size_t mstride, size_t hoff,
+                                         size_t npad, const SiteC &c, int px, cpx<float> acc[12]) {
+  SpinorIO<S_F32>::load(m + px * hoff, c.s, npad, acc);
+#pragma unroll 1
+  for (int p = 1; p < NPATH; ++p) {
+    cpx<float> t[12];
+    path_apply(g, links, m + (size_t)p * mstride, hoff, npad, c, px, p, t);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) acc[k] = cadd(acc[k], t[k]);
+  }
+}
+
 // Pass B: out(x) = sum_p (T_p m_p)(x) at the sites of parity out_par (both if
 // negative; grid (ceil(nb / 4), 1 or 2), four site blocks in the hop's
 // XCD-mapped order), written in storage SOUT to out0 (even half) or out1 (odd
@@ -514,16 +480,8 @@ __global__ __launch_bounds__(256) void k_nn_pass_b(Geo g, const void *__restrict
   const int ns = MULTI ? nsys : 1;
 #pragma unroll 1
   for (int sy = 0; sy < ns; ++sy) {
-    const char *ms = (const char *)m + sy * msys;
     cpx<float> acc[12];
-    SpinorIO<S_F32>::load(ms + px * hoff, s, npad, acc);
-#pragma unroll 1
-    for (int p = 1; p < NPATH; ++p) {
-      cpx<float> t[12];
-      path_apply(g, links, ms + (size_t)p * mstride, hoff, npad, c, px, p, t);
-#pragma unroll
-      for (int k = 0; k < 12; ++k) acc[k] = cadd(acc[k], t[k]);
-    }
+    path_sum(g, links, (const char *)m + sy * msys, mstride, hoff, npad, c, px, acc);
     void *dst = (char *)(px ? out1 : out0) + sy * ostride;
     if constexpr (SOUT == S_F32) {
       SpinorIO<S_F32>::store(dst, s, npad, acc);
@@ -535,98 +493,205 @@ __global__ __launch_bounds__(256) void k_nn_pass_b(Geo g, const void *__restrict
   }
 }
 
-// dL/d conj(W_p^{ij}) = sum_{x,c} g^i(x)[c][r] conj((T_p psi^j)(x)[c][s]).  One
-// block row per path p and chunk of JC inputs j and IC outputs i (the link of
-// p is loaded once per site for the JC transports, each g^i once for the JC
-// inputs), WG_CHUNKS site chunks, partials in FP64 per (p, i, j), each over the
-// same sites in the same order as with one row per pair.
-template <int CIN, int COUT, int JC, int IC>
-__global__ __launch_bounds__(256) void k_ptc_wgrad(Geo g, const void *__restrict__ links, const void *__restrict__ in,
-                                                   const void *__restrict__ gout, size_t fstride,
-                                                   double *__restrict__ part) {
-  static_assert(CIN % JC == 0 && COUT % IC == 0, "k_ptc_wgrad: whole chunks");
-  constexpr int NJ = CIN / JC, NI = COUT / IC;
-  const int row = blockIdx.y;   // (p * NI + ib) * NJ + jb
-  const int jb = row % NJ, ib = (row / NJ) % NI, p = row / (NJ * NI);
+// Pass B of a training step: with y(x) = sum_p (T_p m_p)(x) the network's
+// output, g = (y - v) / ||v||^2 and partials of ||y - v||^2, one per work-group;
+// y itself is not stored.  Grid (ceil(nb / 4), 2 parities) as pass B.
+__global__ __launch_bounds__(256) void k_nn_pass_b_loss(Geo g, const void *__restrict__ links,
+                                                        const void *__restrict__ m, size_t mstride,
+                                                        const void *__restrict__ v, const double *__restrict__ vnorm,
+                                                        void *__restrict__ gout, int zb, double *__restrict__ part) {
+  const int px = (int)blockIdx.y;
+  const int L = xcd_remap(blockIdx.x, gridDim.x) * 4 + (int)(threadIdx.x >> 6);
   const size_t npad = (size_t)g.nb * WAVE, hb = npad * SpinorIO<S_F32>::SITE_BYTES;
-  const size_t nsite = 2 * npad;
-  cpx<float> acc[IC][JC][16];
+  const int s = L < g.nb ? block_order(g, L, zb) * WAVE + (int)(threadIdx.x & (WAVE - 1)) : g.vh;
+  double d2 = 0.0;
+  if (s < g.vh) {
+    const SiteC c = site_c(g, s, px);
+    cpx<float> a[12], b[12];
+    path_sum(g, links, (const char *)m, mstride, hb, npad, c, px, a);
+    SpinorIO<S_F32>::load((const char *)v + px * hb, s, npad, b);
+    const float inv = (float)(1.0 / vnorm[0]);
 #pragma unroll
-  for (int ii = 0; ii < IC; ++ii)
+    for (int k = 0; k < 12; ++k) a[k] = csub(a[k], b[k]);
+    d2 = norm12(a);
 #pragma unroll
-    for (int jj = 0; jj < JC; ++jj)
-#pragma unroll
-      for (int k = 0; k < 16; ++k) acc[ii][jj][k] = cmake(0.f, 0.f);
-  for (size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x; gid < nsite; gid += (size_t)gridDim.x * blockDim.x) {
-    const int par = (int)(gid / npad), s = (int)(gid % npad);
-    if (s >= g.vh) continue;
-    const SiteC c = site_c(g, s, par);
-    cpx<float> t[JC][12];
-    if (p == 0) {
-#pragma unroll
-      for (int jj = 0; jj < JC; ++jj)
-        SpinorIO<S_F32>::load((const char *)in + (size_t)(jb * JC + jj) * fstride + par * hb, s, npad, t[jj]);
-    } else {
-      int mu;
-      bool fwd;
-      path_of(p, mu, fwd);
-      const int n = nbr(g, c, mu, fwd);
-      cpx<float> u[9];
-      if (fwd) LinkIO<L_F32R12>::load(links, par, mu, c.s, g.nb, u);
-      else LinkIO<L_F32R12>::load(links, 1 - par, mu, n, g.nb, u);
-#pragma unroll
-      for (int jj = 0; jj < JC; ++jj) {
-        cpx<float> psi[12];
-        SpinorIO<S_F32>::load((const char *)in + (size_t)(jb * JC + jj) * fstride + (1 - par) * hb, n, npad, psi);
-        transport(u, psi, t[jj], !fwd);
-      }
-    }
-#pragma unroll
-    for (int ii = 0; ii < IC; ++ii) {
-      cpx<float> gg[12];
-      SpinorIO<S_F32>::load((const char *)gout + (size_t)(ib * IC + ii) * fstride + par * hb, s, npad, gg);
-#pragma unroll
-      for (int jj = 0; jj < JC; ++jj)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-              acc[ii][jj][4 * r + q] = cjmac(t[jj][4 * a + q], gg[4 * a + r], acc[ii][jj][4 * r + q]);
-    }
+    for (int k = 0; k < 12; ++k) a[k] = cscale(inv, a[k]);
+    SpinorIO<S_F32>::store((char *)gout + px * hb, s, npad, a);
   }
-  // fixed-order block reduction, one (i, j) pair after the other
-  __shared__ double red[32][4];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int ii = 0; ii < IC; ++ii)
-#pragma unroll
-    for (int jj = 0; jj < JC; ++jj) {
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        double re = wave_sum((double)acc[ii][jj][k].re), im = wave_sum((double)acc[ii][jj][k].im);
-        if (lane == 0) { red[2 * k][wv] = re; red[2 * k + 1][wv] = im; }
-      }
-      __syncthreads();
-      if (threadIdx.x < 32) {
-        const int combo = (p * COUT + ib * IC + ii) * CIN + jb * JC + jj;
-        const double v = (red[threadIdx.x][0] + red[threadIdx.x][1]) + (red[threadIdx.x][2] + red[threadIdx.x][3]);
-        part[((size_t)combo * gridDim.x + blockIdx.x) * 32 + threadIdx.x] = v;
-      }
-      __syncthreads();   // red is written again for the next pair
-    }
+  d2 = wave_sum(d2);
+  __shared__ double red[4];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = d2;
+  __syncthreads();
+  if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// grad[2 k] = dL/dRe W_k = 2 Re G_k, grad[2 k + 1] = dL/dIm W_k = 2 Im G_k.
-__global__ void k_wgrad_final(const double *__restrict__ part, double *__restrict__ grad, int ncombo, int nchunk) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= ncombo * 32) return;
-  const int combo = idx >> 5, k = idx & 31;
+// The gradient of the loss with respect to K: with g = dL / d conj(y),
+//   dL / d conj(K_pq)[r][s] = sum_{x,c} (T_p^+ g)(x)[c][r] conj((T_q psi)(x)[c][s])
+// and T_p^+ = T_m(p), m the mirror path: a contraction over sites and colours
+// of the nine transports of g with the nine of psi, 72 x 72 real, on the FP32
+// matrix cores.  Bound by them: 25 tiles of 16 x 16 (5 x 5, the last row and
+// column half used), 12 steps of four sites per 16 sites and tile, 162 us at
+// 24^3x48 at the full rate; each site's two spinors and its links come from
+// memory once (382 MB there).  The hidden channels do not appear, so the cost is
+// the same for every width.
+//
+// A work-group of four waves takes 32 sites at a time.  Wave w makes the
+// transports of g (w < 2) or psi (w >= 2) at 16 of them, lane (g4, n) those of
+// paths 1 + g4 and 5 + g4 at site n, and leaves them in LDS as
+// [field][path][real][colour][site], where the MFMA operands (row = real, k =
+// site) are read four sites at a time.  Wave w accumulates the tiles (0..4, w)
+// and (w, 4), and wave 0 also (4, 4).  The strides keep writes (16 sites of four
+// paths) and reads (eight reals, four sites each) off each other's banks.
+// FP32 sums run over 128 sites x 3 colours and go on in FP64.
+constexpr int DK_RS = 100, DK_PS = 8 * DK_RS + 16, DK_FS = NPATH * DK_PS;   // strides: real, path, field
+__global__ __launch_bounds__(256, 2) void k_nn_dk(Geo g, const void *__restrict__ links, const void *__restrict__ gf,
+                                                  const void *__restrict__ psif, int zb, double *__restrict__ part) {
+  __shared__ __attribute__((aligned(16))) float T[2 * DK_FS];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & (WAVE - 1), g4 = lane >> 4, n = lane & 15;
+  const size_t npad = (size_t)g.nb * WAVE, hb = npad * SpinorIO<S_F32>::SITE_BYTES;
+  const char *field = (const char *)(w < 2 ? gf : psif);
+  float *dst = T + (w >> 1) * DK_FS + 16 * (w & 1) + n;
+  constexpr int NT = MT32 + 2;
+  // operand rows of this lane in a tile: row n of tile t is the real 16 t + n
+  // (tile 4's second half repeats path 8: its products are not used)
+  const float *ra[MT32], *rb[2];
+#pragma unroll
+  for (int t = 0; t < MT32; ++t) ra[t] = T + min(2 * t + (n >> 3), NPATH - 1) * DK_PS + (n & 7) * DK_RS + 4 * g4;
+  rb[0] = T + DK_FS + (2 * w + (n >> 3)) * DK_PS + (n & 7) * DK_RS + 4 * g4;
+  rb[1] = T + DK_FS + (NPATH - 1) * DK_PS + (n & 7) * DK_RS + 4 * g4;
+  f32x4 acc[NT];
+  double sum[NT][4];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum[t][i] = 0.0;
+  }
+  int done = 0;
+  for (int v = blockIdx.x; v < 4 * g.nb; v += gridDim.x) {
+    const int item = xcd_remap(v, 4 * g.nb), ya = (item >> 1) & 1;
+    const int sb = block_order(g, item >> 2, zb), sl = 32 * (item & 1) + 16 * (w & 1) + n, s = sb * WAVE + sl;
+    const bool live = s < g.vh;   // sites past the last one add zeros
+    const SiteC c = site_c(g, live ? s : 0, ya);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      cpx<float> t[12];
+#pragma unroll
+      for (int k = 0; k < 12; ++k) t[k] = cmake(0.f, 0.f);
+      if (live) {
+        const int nb_ = nbr(g, c, g4, h == 0);
+        cpx<float> u[9], psi[12];
+        if (h == 0) LinkIO<L_F32R12>::load(links, ya, g4, s, g.nb, u);
+        else LinkIO<L_F32R12>::load(links, 1 - ya, g4, nb_, g.nb, u);
+        SpinorIO<S_F32>::load(field + (1 - ya) * hb, nb_, npad, psi);
+        transport(u, psi, t, h == 1);
+      }
+      float *d = dst + (1 + 4 * h + g4) * DK_PS;
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          d[(2 * r) * DK_RS + 32 * a] = t[4 * a + r].re;
+          d[(2 * r + 1) * DK_RS + 32 * a] = t[4 * a + r].im;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e)   // path 0: lane group g4 copies the real 4 e + g4
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        dst[(4 * e + g4) * DK_RS + 32 * a] =
+            live ? ((const float *)(field + ya * hb))[(((size_t)sb * 6 + 2 * a + e) * WAVE + sl) * 4 + g4] : 0.f;
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        f32x4 A[MT32], B[2];
+#pragma unroll
+        for (int t = 0; t < MT32; ++t) A[t] = *(const f32x4 *)(ra[t] + 32 * a + 16 * h);
+        B[0] = *(const f32x4 *)(rb[0] + 32 * a + 16 * h);
+        B[1] = *(const f32x4 *)(rb[1] + 32 * a + 16 * h);
+        f32x4 Aw = A[0];   // tile row w, for the last tile column
+        if (w == 1) Aw = A[1];
+        else if (w == 2) Aw = A[2];
+        else if (w == 3) Aw = A[3];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+#pragma unroll
+          for (int t = 0; t < MT32; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[t][k], B[0][k], acc[t], 0, 0, 0);
+          acc[MT32] = __builtin_amdgcn_mfma_f32_16x16x4f32(Aw[k], B[1][k], acc[MT32], 0, 0, 0);
+          if (w == 0) acc[MT32 + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[MT32 - 1][k], B[1][k], acc[MT32 + 1], 0, 0, 0);
+        }
+      }
+    if ((++done & 3) == 0)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[t][i] += (double)acc[t][i];
+        acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    __syncthreads();   // the next sites overwrite T
+  }
+  // tile (rt, ct) of this work-group: 256 doubles, register i of a lane at 64 i + lane
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    if (t == MT32 + 1 && w != 0) continue;
+    const int rt = t < MT32 ? t : t == MT32 ? w : MT32 - 1, ct = t < MT32 ? w : MT32 - 1;
+    double *o = part + (size_t)blockIdx.x * DK_VALUES + (rt * MT32 + ct) * 256 + lane;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i * WAVE] = sum[t][i] + (double)acc[t][i];
+  }
+}
+
+// dk[v] = sum over the n work-groups of part[i][v]: 64 values per work-group,
+// each wave every fourth partial, the four waves' sums added in wave order.
+__global__ __launch_bounds__(256) void k_nn_dk_sum(const double *__restrict__ part, int n, double *__restrict__ dk) {
+  __shared__ double red[4][WAVE];
+  const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x >> 6, v = blockIdx.x * WAVE + lane;
   double s = 0.0;
 #pragma unroll 8
-  for (int ch = 0; ch < nchunk; ++ch) s += part[((size_t)combo * nchunk + ch) * 32 + k];
-  grad[(size_t)combo * 32 + k] = 2.0 * s;
+  for (int i = w; i < n; i += 4) s += part[(size_t)i * DK_VALUES + v];
+  red[w][lane] = s;
+  __syncthreads();
+  if (w == 0) dk[v] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+}
+
+// The real product sum_x a b of real ar of the transports of g and real br of
+// those of psi (order (path, spin, re/im)) in k_nn_dk's tiles.
+__device__ __forceinline__ double dk_real(const double *dk, int ar, int br) {
+  const int row = ar & 15, col = br & 15;
+  return dk[((ar >> 4) * MT32 + (br >> 4)) * 256 + (row & 3) * WAVE + (row >> 2) * 16 + col];
+}
+
+// From the gradient of K to the weights': dL/dconj(W2_p^h) = sum_q dK_pq (W1_q^h)^+ and
+// dL/dconj(W1_q^h) = sum_p (W2_p^h)^+ dK_pq; grad[2 k] = dL/dRe W_k, grad[2 k + 1]
+// = dL/dIm W_k (twice the real and imaginary part).  One wave per matrix
+// (layer, path, channel): lane (j, entry) sums a quarter of the paths.
+__global__ __launch_bounds__(64) void k_nn_dw(const double *__restrict__ dk, const float2 *__restrict__ w1,
+                                              const float2 *__restrict__ w2, int hidden, double *__restrict__ grad) {
+  const int lane = threadIdx.x, e = lane & 15, j0 = lane >> 4, r = e >> 2, s = e & 3;
+  const int layer = blockIdx.x / (NPATH * hidden), path = (blockIdx.x / hidden) % NPATH, h = blockIdx.x % hidden;
+  double re = 0.0, im = 0.0;
+  for (int o = j0; o < NPATH; o += 4) {
+    const int p = layer ? path : o, q = layer ? o : path, mp = mirror_path(p);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      // dK_pq entry (r, k) for W2, (k, s) for W1
+      const int gr = (mp * 4 + (layer ? r : k)) * 2, gc = (q * 4 + (layer ? k : s)) * 2;
+      const double kr = dk_real(dk, gr, gc) + dk_real(dk, gr + 1, gc + 1);
+      const double ki = dk_real(dk, gr + 1, gc) - dk_real(dk, gr, gc + 1);
+      // times conj(W1_q[s][k]) from the right, or conj(W2_p[k][r]) from the left
+      const float2 c = layer ? w1[(q * hidden + h) * 16 + 4 * s + k] : w2[(p * hidden + h) * 16 + 4 * k + r];
+      re += kr * c.x + ki * c.y;
+      im += ki * c.x - kr * c.y;
+    }
+  }
+  re += __shfl_xor(re, 16, WAVE);
+  im += __shfl_xor(im, 16, WAVE);
+  re += __shfl_xor(re, 32, WAVE);
+  im += __shfl_xor(im, 32, WAVE);
+  if (j0 == 0) ((double2 *)grad)[(size_t)blockIdx.x * 16 + e] = make_double2(2.0 * re, 2.0 * im);
 }
 
 // Adam on the real and imaginary parts of every weight.
@@ -697,33 +762,6 @@ __global__ __launch_bounds__(256) void k_gauss(Geo g, void *__restrict__ out, ui
   nrm = wave_sum(nrm);
   __shared__ double red[4];
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = nrm;
-  __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
-}
-
-// g = (y - v) / ||v||^2 and partials of ||y - v||^2.
-__global__ __launch_bounds__(256) void k_loss_grad(Geo g, const void *__restrict__ y, const void *__restrict__ v,
-                                                   void *__restrict__ gout, const double *__restrict__ vnorm,
-                                                   double *__restrict__ part) {
-  const size_t npad = (size_t)g.nb * WAVE, hb = npad * SpinorIO<S_F32>::SITE_BYTES;
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  double d2 = 0.0;
-  if (gid < 2 * npad) {
-    const int par = (int)(gid / npad), s = (int)(gid % npad);
-    cpx<float> a[12], b[12];
-    SpinorIO<S_F32>::load((const char *)y + par * hb, s, npad, a);
-    SpinorIO<S_F32>::load((const char *)v + par * hb, s, npad, b);
-    const float inv = (float)(1.0 / vnorm[0]);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) a[k] = csub(a[k], b[k]);
-    d2 = s < g.vh ? norm12(a) : 0.0;
-#pragma unroll
-    for (int k = 0; k < 12; ++k) a[k] = cscale(inv, a[k]);
-    SpinorIO<S_F32>::store((char *)gout + par * hb, s, npad, a);
-  }
-  d2 = wave_sum(d2);
-  __shared__ double red[4];
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = d2;
   __syncthreads();
   if (threadIdx.x == 0) part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
@@ -1184,65 +1222,34 @@ inline int nblk(size_t n) { return (int)((n + 255) / 256); }
 size_t full_bytes32(const Geo &g) { return 2 * half_bytes(g, QIRAL_F32); }
 size_t full_bytes64(const Geo &g) { return 2 * half_bytes(g, QIRAL_F64); }
 
-hipError_t layer_launch(const qiral_nn *nn, const float2 *w, int cin, int cout, const void *in, void *out,
-                        hipStream_t s) {
-  const Geo &g = nn->lat->geo;
-  const size_t fs = full_bytes32(g);
-  const int nb = nblk(2 * npad_of(g));
-  const void *links = nn->lat->g32;
-  // 1 -> 8 in two passes of 4 channels (184 VGPRs): one pass of 8 (256 VGPRs, one
-  // wave per SIMD) recomputes no transport but measured 12% slower
-  if (cin == 1 && cout == 8)
-    hipLaunchKernelGGL((k_ptc_layer<1, 8, 4>), dim3(nb), dim3(256), 0, s, g, links, w, in, out, fs);
-  else if (cin == 8 && cout == 1)
-    hipLaunchKernelGGL((k_ptc_layer<8, 1, 1>), dim3(nb), dim3(256), 0, s, g, links, w, in, out, fs);
-  else if (cin == 1 && cout == 4)
-    hipLaunchKernelGGL((k_ptc_layer<1, 4, 4>), dim3(nb), dim3(256), 0, s, g, links, w, in, out, fs);
-  else if (cin == 4 && cout == 1)
-    hipLaunchKernelGGL((k_ptc_layer<4, 1, 1>), dim3(nb), dim3(256), 0, s, g, links, w, in, out, fs);
-  else if (cin == 1 && cout == 2)
-    hipLaunchKernelGGL((k_ptc_layer<1, 2, 2>), dim3(nb), dim3(256), 0, s, g, links, w, in, out, fs);
-  else if (cin == 2 && cout == 1)
-    hipLaunchKernelGGL((k_ptc_layer<2, 1, 1>), dim3(nb), dim3(256), 0, s, g, links, w, in, out, fs);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
-hipError_t wgrad_launch(const qiral_nn *nn, int cin, int cout, const void *in, const void *gout, double *grad,
-                        hipStream_t s) {
-  const Geo &g = nn->lat->geo;
-  const size_t fs = full_bytes32(g);
-  const int ncombo = NPATH * cin * cout;
-  // rows of 2 (p, i, j) pairs: one transport or one g^i serves both
-  dim3 grid(WG_CHUNKS, ncombo / 2);
-  const void *links = nn->lat->g32;
-  if (cin == 1 && cout == 8) hipLaunchKernelGGL((k_ptc_wgrad<1, 8, 1, 2>), grid, dim3(256), 0, s, g, links, in, gout, fs, nn->part);
-  else if (cin == 8 && cout == 1) hipLaunchKernelGGL((k_ptc_wgrad<8, 1, 2, 1>), grid, dim3(256), 0, s, g, links, in, gout, fs, nn->part);
-  else if (cin == 1 && cout == 4) hipLaunchKernelGGL((k_ptc_wgrad<1, 4, 1, 2>), grid, dim3(256), 0, s, g, links, in, gout, fs, nn->part);
-  else if (cin == 4 && cout == 1) hipLaunchKernelGGL((k_ptc_wgrad<4, 1, 2, 1>), grid, dim3(256), 0, s, g, links, in, gout, fs, nn->part);
-  else if (cin == 1 && cout == 2) hipLaunchKernelGGL((k_ptc_wgrad<1, 2, 1, 2>), grid, dim3(256), 0, s, g, links, in, gout, fs, nn->part);
-  else if (cin == 2 && cout == 1) hipLaunchKernelGGL((k_ptc_wgrad<2, 1, 2, 1>), grid, dim3(256), 0, s, g, links, in, gout, fs, nn->part);
-  else return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_wgrad_final, dim3((ncombo * 32 + 255) / 256), dim3(256), 0, s, nn->part, grad, ncombo, WG_CHUNKS);
+// The FP32 fragments of K (adj0 = 0) and / or K' of the current weights.
+hipError_t nn_frag32(const qiral_nn *nn, int adj0, int count, hipStream_t s) {
+  hipLaunchKernelGGL(k_nn_frag32, dim3(nblk(FRAG32), count), dim3(256), 0, s, nn->w, nn->w + nn->nw1, nn->hidden, adj0,
+                     nn->kfrag32);
   return hipGetLastError();
 }
 
 // K and K' of the current weights into nn->kmat, and their MFMA fragments into
-// nn->kfrag (before folded inference).
+// nn->kfrag and nn->kfrag32 (before a flexible solve).
 hipError_t nn_fold(const qiral_nn *nn, hipStream_t s) {
   const int n = NPATH * NPATH * 16, nf = 4 * 2 * 2 * 64 * 8;
-  for (int adj = 0; adj < 2; ++adj) {
-    hipLaunchKernelGGL(k_nn_fold, dim3((n + 255) / 256), dim3(256), 0, s, nn->w, nn->w + nn->nw1, nn->hidden, adj,
-                       nn->kmat + adj * n);
-    hipLaunchKernelGGL(k_nn_frag, dim3(nf / 256), dim3(256), 0, s, (const float2 *)(nn->kmat + adj * n),
-                       (__bf16 *)nn->kfrag + adj * nf);
-  }
-  return hipGetLastError();
+  hipLaunchKernelGGL(k_nn_fold, dim3(nblk(n), 2), dim3(256), 0, s, nn->w, nn->w + nn->nw1, nn->hidden, nn->kmat);
+  hipLaunchKernelGGL(k_nn_frag, dim3(nf / 256, 2), dim3(256), 0, s, (const float2 *)nn->kmat, (__bf16 *)nn->kfrag);
+  return nn_frag32(nn, 0, 2, s);
 }
 
-// out = N(in) (adj = false) or N^dagger(in), folded, with the K of the last
-// nn_fold.  SIO: storage of in and out (packed F32 or F64 fields), given as
+// Pass A on both parities: the path fields of the F32 or F64 full field (in0, in1).
+template <int SIO>
+void nn_pass_a(const qiral_nn *nn, const void *in0, const void *in1, bool adj, int zb, hipStream_t s) {
+  const Geo &g = nn->lat->geo;
+  // three work-groups per compute unit (its register use) walk the blocks
+  const int wgs = std::min(2 * g.nb, 3 * 256);
+  hipLaunchKernelGGL((k_nn_pass_a<SIO>), dim3(wgs), dim3(256), 0, s, g, nn->lat->g32,
+                     (const float *)(nn->kfrag32 + (adj ? FRAG32 : 0)), in0, in1, nn->paths, full_bytes32(g), zb);
+}
+
+// out = N(in) (adj = false) or N^dagger(in), folded, with the fragments of the
+// last nn_fold (nn_frag32 suffices for par < 0).  SIO: storage of in and out (packed F32 or F64 fields), given as
 // half-fields (in0, in1) and (out0, out1).  par >= 0: in is zero off parity par
 // (in0 or in1 is then not read) and only that parity of out is written, and
 // pass A runs on bf16 MFMA (about 1e-5 relative; the flexible solvers only).
@@ -1258,7 +1265,7 @@ hipError_t nn_apply_folded(const qiral_nn *nn, void *out0, void *out1, const voi
   const int zb = hop_zb(g);   // the hops' z-tiles: neighbours stay in one XCD's L2
   if (par >= 0) {
     // path field p is the one parity it is used on: m_0 on par, m_1..m_8 on 1 - par
-    void *m = mbuf ? mbuf : nn->act;
+    void *m = mbuf ? mbuf : nn->paths;
     hipLaunchKernelGGL((k_nn_pass_a_mfma<SIO>), dim3(g.nb, 2), dim3(256), 0, s, g, nn->lat->g32, K,
                        (const bf16x8 *)nn->kfrag + (adj ? 4 * 2 * 2 * WAVE : 0), par ? in1 : in0, iostride, m, hb,
                        (size_t)0, NPATH * hb, nsys, par, zb);
@@ -1268,11 +1275,10 @@ hipError_t nn_apply_folded(const qiral_nn *nn, void *out0, void *out1, const voi
     else
       hipLaunchKernelGGL((k_nn_pass_b<SIO, false>), dim3((g.nb + 3) / 4, 1), dim3(256), 0, s, g, nn->lat->g32,
                          (const void *)m, hb, (size_t)0, NPATH * hb, out0, out1, (size_t)0, 1, par, zb);
-  } else {   // all nine output paths in two waves per site block, five and four
-    hipLaunchKernelGGL((k_nn_pass_a<SIO, 5>), dim3((g.nb + 1) / 2, 2), dim3(256), 0, s, g, nn->lat->g32, K, in0, in1,
-                       nn->act, fs, zb);
+  } else {
+    nn_pass_a<SIO>(nn, in0, in1, adj, zb, s);
     hipLaunchKernelGGL((k_nn_pass_b<SIO, false>), dim3((g.nb + 3) / 4, 2), dim3(256), 0, s, g, nn->lat->g32,
-                       (const void *)nn->act, fs, hb, (size_t)0, out0, out1, (size_t)0, 1, par, zb);
+                       (const void *)nn->paths, fs, hb, (size_t)0, out0, out1, (size_t)0, 1, par, zb);
   }
   return hipGetLastError();
 }
@@ -1322,9 +1328,11 @@ void neumann2(int hidden, double kappa, std::vector<float2> &w) {
 namespace {
 // Offsets of the network's device memory (one caller-owned buffer).
 struct NnLayout {
-  size_t w, wadj, kmat, kfrag, am, av, grad, part, scal, act, gact, pairx, fv, fb, fy, fg, loss, total;
+  size_t w, kmat, kfrag, kfrag32, am, av, grad, part, dk, scal, paths, fv, fb, fg, loss, total;
 };
 inline size_t al256(size_t v) { return (v + 255) / 256 * 256; }
+// Work-groups of the gradient kernel: one per 32 sites while they are few.
+inline int dk_wgs(const Geo &g) { return std::min(4 * g.nb, DK_WGS); }
 NnLayout nn_layout(const Geo &g, int hidden) {
   NnLayout l;
   const size_t nw = (size_t)2 * NPATH * hidden * 16;
@@ -1333,22 +1341,18 @@ NnLayout nn_layout(const Geo &g, int hidden) {
   size_t o = 0;
   auto take = [&](size_t bytes) { const size_t at = o; o = al256(o + bytes); return at; };
   l.w = take(sizeof(float2) * nw);
-  l.wadj = take(sizeof(float2) * nw);
   l.kmat = take(sizeof(float2) * 2 * NPATH * NPATH * 16);
   l.kfrag = take(2 * 4 * 2 * 2 * 64 * 8 * sizeof(__bf16));
+  l.kfrag32 = take(2 * FRAG32 * sizeof(float));
   l.am = take(sizeof(float) * 2 * nw);
   l.av = take(sizeof(float) * 2 * nw);
   l.grad = take(sizeof(double) * 2 * nw);
-  l.part = take(sizeof(double) * std::max<size_t>((size_t)NPATH * hidden * WG_CHUNKS * 32, (size_t)nblocks + 64));
+  l.part = take(sizeof(double) * std::max<size_t>((size_t)dk_wgs(g) * DK_VALUES, (size_t)nblocks + 64));
+  l.dk = take(sizeof(double) * DK_VALUES);
   l.scal = take(sizeof(double) * ((size_t)nblocks + 64));
-  l.act = take(f32 * hidden);
-  l.gact = take(f32 * hidden);
-  // f32 is a whole number of 256-byte units, so act, gact and pairx are
-  // adjacent: together they hold the nine F32 fields m_p of folded inference
-  l.pairx = take(f32 * (size_t)std::max(0, NPATH - 2 * hidden));
+  l.paths = take(f32 * NPATH);   // the path fields m_p
   l.fv = take(f32);
   l.fb = take(f32);
-  l.fy = take(f32);
   l.fg = take(f32);
   l.loss = take(sizeof(double) * LOSS_CAP);
   l.total = o;
@@ -1380,30 +1384,28 @@ extern "C" qiral_status qiral_nn_create(qiral_nn **out, qiral_lattice *lat, int3
   const int nw = nn->nw1 + nn->nw2;
   char *m = (char *)mem;
   nn->w = (float2 *)(m + l.w);
-  nn->wadj = (float2 *)(m + l.wadj);
   nn->kmat = (float2 *)(m + l.kmat);
   nn->kfrag = m + l.kfrag;
+  nn->kfrag32 = (float *)(m + l.kfrag32);
   nn->am = (float *)(m + l.am);
   nn->av = (float *)(m + l.av);
   nn->grad = (double *)(m + l.grad);
   nn->part = (double *)(m + l.part);
+  nn->dk = (double *)(m + l.dk);
   nn->scal = (double *)(m + l.scal);
-  nn->act = m + l.act;
-  nn->gact = m + l.gact;
+  nn->paths = m + l.paths;
   nn->fv = m + l.fv;
   nn->fb = m + l.fb;
-  nn->fy = m + l.fy;
   nn->fg = m + l.fg;
   nn->loss_dev = (double *)(m + l.loss);
   hipStream_t s = (hipStream_t)stream;
   std::vector<float2> w0;
   neumann2(hidden, lat->kappa, w0);
   hipError_t e = hipMemcpyAsync(nn->w, w0.data(), sizeof(float2) * nw, hipMemcpyHostToDevice, s);
-  // Adam moments start at zero; activations too, so that padding sites stay zero
+  // Adam moments start at zero; the path fields too, so that padding sites stay zero
   if (e == hipSuccess) e = hipMemsetAsync(nn->am, 0, sizeof(float) * 2 * nw, s);
   if (e == hipSuccess) e = hipMemsetAsync(nn->av, 0, sizeof(float) * 2 * nw, s);
-  if (e == hipSuccess) e = hipMemsetAsync(nn->act, 0, full_bytes32(lat->geo) * hidden, s);
-  if (e == hipSuccess) e = hipMemsetAsync(nn->gact, 0, full_bytes32(lat->geo) * hidden, s);
+  if (e == hipSuccess) e = hipMemsetAsync(nn->paths, 0, full_bytes32(lat->geo) * NPATH, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);   // w0 is a host temporary
   if (e != hipSuccess) {
     delete nn;
@@ -1445,7 +1447,7 @@ static qiral_status nn_apply_api(const qiral_nn *nn, void *out, const void *in, 
   if (out == in) return fail(QIRAL_ERR_INVALID_ARG, "in and out must not alias");
   hipStream_t s = (hipStream_t)stream;
   const size_t hb = half_bytes(nn->lat->geo, QIRAL_F32);
-  QIRAL_HIP(nn_fold(nn, s));
+  QIRAL_HIP(nn_frag32(nn, adj, 1, s));
   QIRAL_HIP(nn_apply_folded<S_F32>(nn, out, (char *)out + hb, in, (const char *)in + hb, adj, s));
   return QIRAL_OK;
 }
@@ -1479,27 +1481,25 @@ namespace {
 
 // Loss L = ||N(src) - target||^2 / ||target||^2 into *loss_dev and its gradient
 // with respect to the real and imaginary parts of every weight into nn->grad.
-hipError_t train_step(qiral_nn *nn, const void *src, const void *target, double *loss_dev, hipStream_t s) {
+// have_norm: nn->part holds the nb partials of ||target||^2 already.
+hipError_t train_step(qiral_nn *nn, const void *src, const void *target, double *loss_dev, bool have_norm,
+                      hipStream_t s) {
   const Geo &g = nn->lat->geo;
-  const int H = nn->hidden;
-  const int nb = nblk(2 * npad_of(g));
-  hipLaunchKernelGGL(k_norm32, dim3(nb), dim3(256), 0, s, g, target, nn->part);
-  hipLaunchKernelGGL(k_sum, dim3(1), dim3(256), 0, s, nn->part, nb, nn->scal, (const double *)nullptr);
-  hipError_t e = layer_launch(nn, nn->w, 1, H, src, nn->act, s);
+  const int nb = nblk(2 * npad_of(g)), zb = hop_zb(g), nwg = dk_wgs(g);
+  const size_t fs = full_bytes32(g), hb = fs / 2;
+  const dim3 gb((g.nb + 3) / 4, 2), bd(256);
+  if (!have_norm) hipLaunchKernelGGL(k_norm32, dim3(nb), bd, 0, s, g, target, nn->part);
+  hipLaunchKernelGGL(k_sum, dim3(1), bd, 0, s, nn->part, nb, nn->scal, (const double *)nullptr);
+  hipError_t e = nn_frag32(nn, 0, 1, s);
   if (e != hipSuccess) return e;
-  e = layer_launch(nn, nn->w + nn->nw1, H, 1, nn->act, nn->fy, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_loss_grad, dim3(nb), dim3(256), 0, s, g, nn->fy, target, nn->fg, nn->scal, nn->part);
-  hipLaunchKernelGGL(k_sum, dim3(1), dim3(256), 0, s, nn->part, nb, loss_dev, nn->scal);
-  // layer 2: weights and the gradient w.r.t. its input (the adjoint layer)
-  e = wgrad_launch(nn, H, 1, nn->act, nn->fg, nn->grad + 2 * nn->nw1, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_adj_weights, dim3((NPATH * H * 16 + 255) / 256), dim3(256), 0, s, nn->w + nn->nw1, nn->wadj, 1, H);
-  e = layer_launch(nn, nn->wadj, 1, H, nn->fg, nn->gact, s);
-  if (e != hipSuccess) return e;
-  // layer 1 weights
-  e = wgrad_launch(nn, 1, H, src, nn->gact, nn->grad, s);
-  if (e != hipSuccess) return e;
+  nn_pass_a<S_F32>(nn, src, (const char *)src + hb, false, zb, s);
+  hipLaunchKernelGGL(k_nn_pass_b_loss, gb, bd, 0, s, g, nn->lat->g32, nn->paths, fs, target, nn->scal, nn->fg, zb,
+                     nn->part);
+  hipLaunchKernelGGL(k_sum, dim3(1), bd, 0, s, nn->part, (int)(2 * gb.x), loss_dev, nn->scal);
+  hipLaunchKernelGGL(k_nn_dk, dim3(nwg), bd, 0, s, g, nn->lat->g32, nn->fg, src, zb, nn->part);
+  hipLaunchKernelGGL(k_nn_dk_sum, dim3(DK_VALUES / WAVE), bd, 0, s, nn->part, nwg, nn->dk);
+  hipLaunchKernelGGL(k_nn_dw, dim3(2 * NPATH * nn->hidden), dim3(WAVE), 0, s, nn->dk, nn->w, nn->w + nn->nw1,
+                     nn->hidden, nn->grad);
   return hipGetLastError();
 }
 
@@ -1509,7 +1509,7 @@ extern "C" qiral_status qiral_nn_grad(qiral_nn *nn, const void *src, const void 
                                       qiral_stream_t stream) {
   if (!nn || !src || !target) return fail(QIRAL_ERR_INVALID_ARG, "NULL argument");
   hipStream_t s = (hipStream_t)stream;
-  QIRAL_HIP(train_step(nn, src, target, nn->scal + 1, s));
+  QIRAL_HIP(train_step(nn, src, target, nn->scal + 1, false, s));
   if (loss) QIRAL_HIP(hipMemcpyAsync(loss, nn->scal + 1, sizeof(double), hipMemcpyDeviceToHost, s));
   if (grad) QIRAL_HIP(hipMemcpyAsync(grad, nn->grad, sizeof(double) * 2 * (nn->nw1 + nn->nw2), hipMemcpyDeviceToHost, s));
   QIRAL_HIP(hipStreamSynchronize(s));
@@ -1533,7 +1533,7 @@ extern "C" qiral_status qiral_nn_train(qiral_nn *nn, int32_t steps, double lr, u
     hipLaunchKernelGGL(k_gauss, dim3(nb), dim3(256), 0, s, g, nn->fv, make_uint2((unsigned)seed, (unsigned)(seed >> 32)),
                        ctr, nn->part);
     QIRAL_HIP(launch_D(nn->lat, QIRAL_F32, 0, nn->fb, nn->fv, 1, s));
-    QIRAL_HIP(train_step(nn, nn->fb, nn->fv, nn->loss_dev + k % LOSS_CAP, s));
+    QIRAL_HIP(train_step(nn, nn->fb, nn->fv, nn->loss_dev + k % LOSS_CAP, true, s));   // k_gauss left ||v||^2's partials
     nn->adam_step += 1;
     const float c1 = 1.f - powf(b1, (float)nn->adam_step), c2 = 1.f - powf(b2, (float)nn->adam_step);
     hipLaunchKernelGGL(k_adam, dim3((nreal + 255) / 256), dim3(256), 0, s, (float *)nn->w, nn->grad, nn->am, nn->av,

@@ -49,3 +49,34 @@ def test_full_operator_of_several_fields(dims, nrhs, prec):
         got = host(lat.export_field(out, q.FULL, prec, nrhs=nrhs))
         for r in range(nrhs):
             _check(got[r], ref(Ur, 0.12, 0.35, br[r]), prec)
+
+
+# The network's pass over all paths and the gradient of its folded weights work
+# on tiles of 16 and 32 sites in a bounded number of work-groups: one partly
+# filled block, a ragged last tile, whole tiles, and 12x12x16x24 with more blocks
+# (864 of both parities) than work-groups.  FP32 sums of 72 products in each of
+# two passes: 2e-6 relative.  A gradient entry sums a product per site and colour
+# in FP32 pieces: 1e-5 of the largest.
+@pytest.mark.parametrize("dims,H", [((2, 2, 2, 2), 8), ((6, 4, 2, 4), 2), ((4, 4, 4, 4), 4), ((6, 10, 2, 8), 8),
+                                    ((12, 12, 16, 24), 2)])
+def test_network_and_gradient_tiles(dims, H):
+    say("network tiles", dims, H)
+    cfg = latgen.small_config(dims, seed=83, kind="expih", eps=0.4, nrhs=2)
+    lat = q.Lattice(dims, 0.125, cfg["U"])
+    net = q.Network(lat, H)
+    rng = np.random.default_rng(H)
+    w1, w2 = (0.3 * (rng.standard_normal(n) + 1j * rng.standard_normal(n)) for n in ((9, H, 1, 4, 4), (9, 1, H, 4, 4)))
+    net.set_weights(w1, w2)
+    ws = [w.astype(np.complex64).astype(np.complex128) for w in (w1, w2)]
+    Ur, br = _rounded(cfg, q.F32)
+    src, tgt = (lat.import_field(dev(cfg["b"][i:i + 1]), q.FULL, q.F32) for i in (0, 1))
+    out = lat.field(q.FULL, q.F32)
+    for adj, ref in ((False, ptc.network), (True, ptc.network_adjoint)):
+        net.apply(out, src, adjoint=adj)
+        got, want = host(lat.export_field(out, q.FULL, q.F32))[0], ref(Ur, ws, br[0])
+        assert np.sqrt(W.norm2(got - want) / W.norm2(want)) < 2e-6
+    loss, g = net.grad(src, tgt)
+    L, G = ptc.loss_and_grad(Ur, ws, br[0], br[1])
+    want = np.concatenate([(2 * G[0]).ravel(), (2 * G[1]).ravel()])
+    assert abs(loss - L) < 1e-6 * L
+    assert np.abs(g[0::2] + 1j * g[1::2] - want).max() < 1e-5 * np.abs(want).max()
