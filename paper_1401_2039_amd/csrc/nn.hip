@@ -86,24 +86,6 @@ __device__ __forceinline__ void transport(const cpx<float> u[9], const cpx<float
   }
 }
 
-// (T_p psi)(x) for a full field: x = (par, s), psi read at the neighbour.
-__device__ __forceinline__ void path_apply(const Geo &g, const void *links, const void *field, size_t hb, size_t npad,
-                                           const SiteC &c, int par, int p, cpx<float> t[12]) {
-  if (p == 0) {
-    SpinorIO<S_F32>::load((const char *)field + par * hb, c.s, npad, t);
-    return;
-  }
-  int mu;
-  bool fwd;
-  path_of(p, mu, fwd);
-  const int n = nbr(g, c, mu, fwd);
-  cpx<float> u[9], psi[12];
-  if (fwd) LinkIO<L_F32R12>::load(links, par, mu, c.s, g.nb, u);
-  else LinkIO<L_F32R12>::load(links, 1 - par, mu, n, g.nb, u);
-  SpinorIO<S_F32>::load((const char *)field + (1 - par) * hb, n, npad, psi);
-  transport(u, psi, t, !fwd);
-}
-
 // ---------------------------------------------------------------------------
 // kernels
 
@@ -187,6 +169,52 @@ __device__ __forceinline__ void load_as_f32(const void *half, int s, size_t npad
   }
 }
 
+// What a lane reads for the nine transports at its site s of block sb: links and
+// neighbour spinors of the paths 1 + g4 (from x + mu) and 5 + g4 (from x - mu) of
+// its lane group g4, as stored, and the reals 4 e + g4 of path 0 per colour.
+template <int SIN> struct PathIn {
+  LinkIO<L_F32R12>::Raw lr[2];
+  typename SpinorIO<SIN>::Raw pr[2];
+  float own[2][3];
+};
+
+template <int SIN>
+__device__ __forceinline__ void path_fetch(const Geo &g, const void *links, const void *here, const void *there, int ya,
+                                           int s, int g4, PathIn<SIN> &in) {
+  const size_t npad = (size_t)g.nb * WAVE;
+  const SiteC c = site_c(g, s, ya);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int n = nbr(g, c, g4, h == 0);
+    LinkIO<L_F32R12>::fetch(links, h == 0 ? ya : 1 - ya, g4, h == 0 ? s : n, g.nb, in.lr[h]);
+    SpinorIO<SIN>::fetch(there, n, npad, in.pr[h]);
+  }
+  const size_t sb = s >> 6;
+  const int sl = s & (WAVE - 1);
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      if constexpr (SIN == S_F32) in.own[e][a] = ((const float *)here)[((sb * 6 + 2 * a + e) * WAVE + sl) * 4 + g4];
+      else in.own[e][a] = (float)((const double *)here)[((sb * 12 + 4 * a + 2 * e + (g4 >> 1)) * WAVE + sl) * 2 + (g4 & 1)];
+    }
+}
+
+// The transport of path 1 + g4 (h = 0) or 5 + g4 (h = 1).
+template <int SIN>
+__device__ __forceinline__ void path_use(const PathIn<SIN> &in, int h, cpx<float> t[12]) {
+  cpx<float> u[9], psi[12];
+  LinkIO<L_F32R12>::decode(in.lr[h], u);
+  if constexpr (SIN == S_F32) {
+    SpinorIO<S_F32>::decode(in.pr[h], psi);
+  } else {
+    cpx<double> d[12];
+    SpinorIO<S_F64>::decode(in.pr[h], d);
+    cvt12(d, psi);
+  }
+  transport(u, psi, t, h == 1);
+}
+
 // Pass A over both parities and all nine paths on the FP32 matrix cores: the
 // input's half-fields are in0 (even) and in1 (odd), storage SIN; m_p is written
 // to the F32 half-field m + p * mstride + parity * (npad * 96 bytes).
@@ -200,14 +228,16 @@ __device__ __forceinline__ void load_as_f32(const void *half, int s, size_t npad
 // the four), so nothing passes through LDS but K's fragments, read there by
 // every wave.  The accumulator rows of lane (g, n) are two complex spin
 // components of one path, colour and site, a float4 unit of the spinor layout,
-// and are stored as they are.  At 24^3x48 with the F32 input: 300 us (the
-// vector-ALU form, two waves per block sweeping the input paths for five and four
-// output paths, took 441).
+// and are stored as they are, as streaming stores (the nine fields are far
+// larger than a cache keeps until pass B reads them once; the same holds for
+// k_nn_pass_a_mfma).  At 24^3x48 with the F32 input: 275 us, 150 of them the
+// products at the full FP32 MFMA rate (the vector-ALU form, two waves per block
+// sweeping the input paths for five and four output paths, took 441).
 //
 // Work-groups of four waves walk the 64-site blocks of both parities in the
 // hop's XCD-mapped order, `nblk` of them, and keep the fragments.
 template <int SIN>
-__global__ __launch_bounds__(256, 3) void k_nn_pass_a(Geo g, const void *__restrict__ links,
+__global__ __launch_bounds__(256, 2) void k_nn_pass_a(Geo g, const void *__restrict__ links,
                                                       const float *__restrict__ frag, const void *__restrict__ in0,
                                                       const void *__restrict__ in1, void *__restrict__ m,
                                                       size_t mstride, int zb) {
@@ -218,15 +248,41 @@ __global__ __launch_bounds__(256, 3) void k_nn_pass_a(Geo g, const void *__restr
   const int lane = threadIdx.x & (WAVE - 1), g4 = lane >> 4, n = lane & 15;
   const size_t npad = (size_t)g.nb * WAVE, hb = npad * SpinorIO<S_F32>::SITE_BYTES;
   const float *A = lds_frag + lane;
+  // the next tile's loads run under this one's matrix products (F32 input; the
+  // registers do not hold two F64 spinors more)
+  constexpr bool AHEAD = SIN == S_F32;
+  PathIn<SIN> in;
+  struct Tile { int ya, sb, sl; bool any, live; };
+  // lanes past the last site take part with their tile's first site and store
+  // nothing; a tile wholly past it is skipped
+  auto fetch = [&](int v) {
+    Tile t;
+    const int item = xcd_remap(v, 2 * g.nb);
+    t.ya = item & 1;
+    t.sb = block_order(g, item >> 1, zb);
+    const int s0 = t.sb * WAVE + 16 * w;
+    t.any = s0 < g.vh;
+    t.live = s0 + n < g.vh;
+    t.sl = 16 * w + (t.live ? n : 0);
+    if (t.any) path_fetch<SIN>(g, links, t.ya ? in1 : in0, t.ya ? in0 : in1, t.ya, t.sb * WAVE + t.sl, g4, in);
+    return t;
+  };
+  Tile tile = fetch(blockIdx.x);
   for (int v = blockIdx.x; v < 2 * g.nb; v += gridDim.x) {
-    const int item = xcd_remap(v, 2 * g.nb), ya = item & 1;
-    const int sb = block_order(g, item >> 1, zb), s0 = sb * WAVE + 16 * w;
-    if (s0 >= g.vh) continue;
-    // lanes past the last site take part with the tile's first site and store nothing
-    const bool live = s0 + n < g.vh;
-    const int sl = live ? 16 * w + n : 16 * w, s = sb * WAVE + sl;
-    const void *here = ya ? in1 : in0, *there = ya ? in0 : in1;
-    const SiteC c = site_c(g, s, ya);
+    if (!AHEAD && v != (int)blockIdx.x) tile = fetch(v);
+    const Tile cur = tile;
+    const int ya = cur.ya, sb = cur.sb, sl = cur.sl;
+    cpx<float> t[2][12];
+    float own[2][3];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) path_use<SIN>(in, h, t[h]);
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) own[e][a] = in.own[e][a];
+    if (AHEAD && v + (int)gridDim.x < 2 * g.nb) tile = fetch(v + gridDim.x);
+    __builtin_amdgcn_sched_barrier(0);
+    if (!cur.any) continue;
     f32x4 D[MT32][3];
 #pragma unroll
     for (int mt = 0; mt < MT32; ++mt)
@@ -234,12 +290,6 @@ __global__ __launch_bounds__(256, 3) void k_nn_pass_a(Geo g, const void *__restr
       for (int a = 0; a < 3; ++a) D[mt][a] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int nb_ = nbr(g, c, g4, h == 0);
-      cpx<float> u[9], psi[12], t[12];
-      if (h == 0) LinkIO<L_F32R12>::load(links, ya, g4, s, g.nb, u);
-      else LinkIO<L_F32R12>::load(links, 1 - ya, g4, nb_, g.nb, u);
-      load_as_f32<SIN>(there, nb_, npad, psi);
-      transport(u, psi, t, h == 1);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         float af[MT32];
@@ -247,7 +297,7 @@ __global__ __launch_bounds__(256, 3) void k_nn_pass_a(Geo g, const void *__restr
         for (int mt = 0; mt < MT32; ++mt) af[mt] = A[(mt * KS32 + 8 * h + e) * WAVE];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-          const float b = (e & 1) ? t[4 * a + (e >> 1)].im : t[4 * a + (e >> 1)].re;
+          const float b = (e & 1) ? t[h][4 * a + (e >> 1)].im : t[h][4 * a + (e >> 1)].re;
 #pragma unroll
           for (int mt = 0; mt < MT32; ++mt) D[mt][a] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[mt], b, D[mt][a], 0, 0, 0);
         }
@@ -260,21 +310,19 @@ __global__ __launch_bounds__(256, 3) void k_nn_pass_a(Geo g, const void *__restr
       for (int mt = 0; mt < MT32; ++mt) af[mt] = A[(mt * KS32 + 16 + e) * WAVE];
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        float b;
-        if constexpr (SIN == S_F32) b = ((const float *)here)[(((size_t)sb * 6 + 2 * a + e) * WAVE + sl) * 4 + g4];
-        else b = (float)((const double *)here)[(((size_t)sb * 12 + 4 * a + 2 * e + (g4 >> 1)) * WAVE + sl) * 2 + (g4 & 1)];
+        const float b = own[e][a];
 #pragma unroll
         for (int mt = 0; mt < MT32; ++mt) D[mt][a] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[mt], b, D[mt][a], 0, 0, 0);
       }
     }
-    if (!live) continue;
+    if (!cur.live) continue;
 #pragma unroll
     for (int mt = 0; mt < MT32; ++mt) {
       const int p = 2 * mt + (g4 >> 1);
       if (p >= NPATH) continue;
       float4 *dst = (float4 *)((char *)m + (size_t)p * mstride + ya * hb) + ((size_t)sb * 6 + (g4 & 1)) * WAVE + sl;
 #pragma unroll
-      for (int a = 0; a < 3; ++a) dst[2 * a * WAVE] = make_float4(D[mt][a][0], D[mt][a][1], D[mt][a][2], D[mt][a][3]);
+      for (int a = 0; a < 3; ++a) st_nt(dst + 2 * a * WAVE, make_float4(D[mt][a][0], D[mt][a][1], D[mt][a][2], D[mt][a][3]));
     }
   }
 }
@@ -440,20 +488,33 @@ __global__ __launch_bounds__(256, 3) void k_nn_pass_a_mfma(Geo g, const void *__
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         const f32x4 d = D[j][a];
-        base[((size_t)sb * 6 + 2 * a + (g4 & 1)) * WAVE + 16 * j + n] = make_float4(d[0], d[1], d[2], d[3]);
+        st_nt(base + ((size_t)sb * 6 + 2 * a + (g4 & 1)) * WAVE + 16 * j + n, make_float4(d[0], d[1], d[2], d[3]));
       }
     }
   }
 }
 
-// acc = sum_p (T_p m_p)(x) at site x = (px, c.s) of the path fields m.
+// acc = sum_p (T_p m_p)(x) at site x = (px, c.s) of the path fields m.  Each
+// spinor of m is read once in the whole pass: streaming loads, which took pass B
+// over both parities at 24^3x48 from 190 to 131 us (6.8 TB/s) and the lockstep
+// solver's pass over 12 systems from 1100 to 923 us.
 __device__ __forceinline__ void path_sum(const Geo &g, const void *links, const char *m, size_t mstride, size_t hoff,
                                          size_t npad, const SiteC &c, int px, cpx<float> acc[12]) {
-  SpinorIO<S_F32>::load(m + px * hoff, c.s, npad, acc);
+  SpinorIO<S_F32>::Raw r;
+  SpinorIO<S_F32>::fetch<true>(m + px * hoff, c.s, npad, r);
+  SpinorIO<S_F32>::decode(r, acc);
 #pragma unroll 1
   for (int p = 1; p < NPATH; ++p) {
-    cpx<float> t[12];
-    path_apply(g, links, m + (size_t)p * mstride, hoff, npad, c, px, p, t);
+    int mu;
+    bool fwd;
+    path_of(p, mu, fwd);
+    const int n = nbr(g, c, mu, fwd);
+    cpx<float> u[9], psi[12], t[12];
+    if (fwd) LinkIO<L_F32R12>::load(links, px, mu, c.s, g.nb, u);
+    else LinkIO<L_F32R12>::load(links, 1 - px, mu, n, g.nb, u);
+    SpinorIO<S_F32>::fetch<true>(m + (size_t)p * mstride + (1 - px) * hoff, n, npad, r);
+    SpinorIO<S_F32>::decode(r, psi);
+    transport(u, psi, t, !fwd);
 #pragma unroll
     for (int k = 0; k < 12; ++k) acc[k] = cadd(acc[k], t[k]);
   }
@@ -536,30 +597,55 @@ __global__ __launch_bounds__(256) void k_nn_pass_b_loss(Geo g, const void *__res
 // the same for every width.
 //
 // A work-group of four waves takes 32 sites at a time.  Wave w makes the
-// transports of g (w < 2) or psi (w >= 2) at 16 of them, lane (g4, n) those of
-// paths 1 + g4 and 5 + g4 at site n, and leaves them in LDS as
-// [field][path][real][colour][site], where the MFMA operands (row = real, k =
-// site) are read four sites at a time.  Wave w accumulates the tiles (0..4, w)
-// and (w, 4), and wave 0 also (4, 4).  The strides keep writes (16 sites of four
-// paths) and reads (eight reals, four sites each) off each other's banks.
+// transports of both fields at 16 of them, lane (g4, n) those of path 1 + g4 (w <
+// 2) or 5 + g4 (w >= 2) at site n, with one load of the link, and leaves them in
+// LDS as [field][path][real][colour][site], where the MFMA operands (row = real,
+// k = site) are read four sites at a time.  The next sites' loads run under the
+// matrix products, of which wave w accumulates the tiles (0..4, w) and (w, 4),
+// and wave 0 also (4, 4).  The strides keep writes (16 sites of four paths) and
+// reads (eight reals, four sites each) off each other's banks.  Two work-groups
+// a compute unit, so that one's transports meet the other's products (a version
+// with four waves for each of the two, and two LDS buffers, was 15% slower).
 // FP32 sums run over 128 sites x 3 colours and go on in FP64.
 constexpr int DK_RS = 100, DK_PS = 8 * DK_RS + 16, DK_FS = NPATH * DK_PS;   // strides: real, path, field
 __global__ __launch_bounds__(256, 2) void k_nn_dk(Geo g, const void *__restrict__ links, const void *__restrict__ gf,
                                                   const void *__restrict__ psif, int zb, double *__restrict__ part) {
-  __shared__ __attribute__((aligned(16))) float T[2 * DK_FS];
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __shared__ __attribute__((aligned(16))) float Tb[2 * DK_FS];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = w & 1, h = w >> 1;
   const int lane = threadIdx.x & (WAVE - 1), g4 = lane >> 4, n = lane & 15;
   const size_t npad = (size_t)g.nb * WAVE, hb = npad * SpinorIO<S_F32>::SITE_BYTES;
-  const char *field = (const char *)(w < 2 ? gf : psif);
-  float *dst = T + (w >> 1) * DK_FS + 16 * (w & 1) + n;
+  const int nitem = 4 * g.nb, step = gridDim.x;
+  struct {
+    LinkIO<L_F32R12>::Raw lr;
+    SpinorIO<S_F32>::Raw pr[2];
+    float own[2][3];   // path 0 of field h: the reals 4 e + g4 per colour
+    bool live;
+  } in;
+  auto fetch = [&](int v) {   // sites past the last one add zeros
+    const int item = xcd_remap(v, nitem), ya = (item >> 1) & 1, sb = block_order(g, item >> 2, zb);
+    const int sl = 32 * (item & 1) + 16 * half + n;
+    in.live = sb * WAVE + sl < g.vh;
+    const SiteC c = site_c(g, in.live ? sb * WAVE + sl : 0, ya);
+    const int nb_ = nbr(g, c, g4, h == 0);
+    LinkIO<L_F32R12>::fetch(links, h == 0 ? ya : 1 - ya, g4, h == 0 ? c.s : nb_, g.nb, in.lr);
+    SpinorIO<S_F32>::fetch((const char *)gf + (1 - ya) * hb, nb_, npad, in.pr[0]);
+    SpinorIO<S_F32>::fetch((const char *)psif + (1 - ya) * hb, nb_, npad, in.pr[1]);
+    const float *own = (const float *)((const char *)(h ? psif : gf) + ya * hb);
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        in.own[e][a] = own[((size_t)(c.s >> 6) * 6 + 2 * a + e) * WAVE * 4 + (c.s & (WAVE - 1)) * 4 + g4];
+  };
+  float *dst = Tb + 16 * half + n;
   constexpr int NT = MT32 + 2;
   // operand rows of this lane in a tile: row n of tile t is the real 16 t + n
   // (tile 4's second half repeats path 8: its products are not used)
-  const float *ra[MT32], *rb[2];
+  int ra[MT32], rb[2];
 #pragma unroll
-  for (int t = 0; t < MT32; ++t) ra[t] = T + min(2 * t + (n >> 3), NPATH - 1) * DK_PS + (n & 7) * DK_RS + 4 * g4;
-  rb[0] = T + DK_FS + (2 * w + (n >> 3)) * DK_PS + (n & 7) * DK_RS + 4 * g4;
-  rb[1] = T + DK_FS + (NPATH - 1) * DK_PS + (n & 7) * DK_RS + 4 * g4;
+  for (int t = 0; t < MT32; ++t) ra[t] = min(2 * t + (n >> 3), NPATH - 1) * DK_PS + (n & 7) * DK_RS + 4 * g4;
+  rb[0] = DK_FS + (2 * w + (n >> 3)) * DK_PS + (n & 7) * DK_RS + 4 * g4;
+  rb[1] = DK_FS + (NPATH - 1) * DK_PS + (n & 7) * DK_RS + 4 * g4;
   f32x4 acc[NT];
   double sum[NT][4];
 #pragma unroll
@@ -569,49 +655,43 @@ __global__ __launch_bounds__(256, 2) void k_nn_dk(Geo g, const void *__restrict_
     for (int i = 0; i < 4; ++i) sum[t][i] = 0.0;
   }
   int done = 0;
-  for (int v = blockIdx.x; v < 4 * g.nb; v += gridDim.x) {
-    const int item = xcd_remap(v, 4 * g.nb), ya = (item >> 1) & 1;
-    const int sb = block_order(g, item >> 2, zb), sl = 32 * (item & 1) + 16 * (w & 1) + n, s = sb * WAVE + sl;
-    const bool live = s < g.vh;   // sites past the last one add zeros
-    const SiteC c = site_c(g, live ? s : 0, ya);
+  fetch(blockIdx.x);
+  for (int v = blockIdx.x; v < nitem; v += step) {
+    {
+      cpx<float> u[9];
+      LinkIO<L_F32R12>::decode(in.lr, u);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      cpx<float> t[12];
+      for (int f = 0; f < 2; ++f) {
+        cpx<float> psi[12], t[12];
+        SpinorIO<S_F32>::decode(in.pr[f], psi);
+        if (h) transport(u, psi, t, true);
+        else transport(u, psi, t, false);
+        float *d = dst + f * DK_FS + (1 + 4 * h + g4) * DK_PS;
 #pragma unroll
-      for (int k = 0; k < 12; ++k) t[k] = cmake(0.f, 0.f);
-      if (live) {
-        const int nb_ = nbr(g, c, g4, h == 0);
-        cpx<float> u[9], psi[12];
-        if (h == 0) LinkIO<L_F32R12>::load(links, ya, g4, s, g.nb, u);
-        else LinkIO<L_F32R12>::load(links, 1 - ya, g4, nb_, g.nb, u);
-        SpinorIO<S_F32>::load(field + (1 - ya) * hb, nb_, npad, psi);
-        transport(u, psi, t, h == 1);
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            d[(2 * r) * DK_RS + 32 * a] = in.live ? t[4 * a + r].re : 0.f;
+            d[(2 * r + 1) * DK_RS + 32 * a] = in.live ? t[4 * a + r].im : 0.f;
+          }
       }
-      float *d = dst + (1 + 4 * h + g4) * DK_PS;
 #pragma unroll
-      for (int a = 0; a < 3; ++a)
+      for (int e = 0; e < 2; ++e)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          d[(2 * r) * DK_RS + 32 * a] = t[4 * a + r].re;
-          d[(2 * r + 1) * DK_RS + 32 * a] = t[4 * a + r].im;
-        }
+        for (int a = 0; a < 3; ++a) dst[h * DK_FS + (4 * e + g4) * DK_RS + 32 * a] = in.live ? in.own[e][a] : 0.f;
     }
-#pragma unroll
-    for (int e = 0; e < 2; ++e)   // path 0: lane group g4 copies the real 4 e + g4
-#pragma unroll
-      for (int a = 0; a < 3; ++a)
-        dst[(4 * e + g4) * DK_RS + 32 * a] =
-            live ? ((const float *)(field + ya * hb))[(((size_t)sb * 6 + 2 * a + e) * WAVE + sl) * 4 + g4] : 0.f;
     __syncthreads();
+    if (v + step < nitem) fetch(v + step);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int sh = 0; sh < 2; ++sh) {
         f32x4 A[MT32], B[2];
 #pragma unroll
-        for (int t = 0; t < MT32; ++t) A[t] = *(const f32x4 *)(ra[t] + 32 * a + 16 * h);
-        B[0] = *(const f32x4 *)(rb[0] + 32 * a + 16 * h);
-        B[1] = *(const f32x4 *)(rb[1] + 32 * a + 16 * h);
+        for (int t = 0; t < MT32; ++t) A[t] = *(const f32x4 *)(Tb + ra[t] + 32 * a + 16 * sh);
+        B[0] = *(const f32x4 *)(Tb + rb[0] + 32 * a + 16 * sh);
+        B[1] = *(const f32x4 *)(Tb + rb[1] + 32 * a + 16 * sh);
         f32x4 Aw = A[0];   // tile row w, for the last tile column
         if (w == 1) Aw = A[1];
         else if (w == 2) Aw = A[2];
@@ -631,7 +711,7 @@ __global__ __launch_bounds__(256, 2) void k_nn_dk(Geo g, const void *__restrict_
         for (int i = 0; i < 4; ++i) sum[t][i] += (double)acc[t][i];
         acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-    __syncthreads();   // the next sites overwrite T
+    __syncthreads();   // the next sites overwrite the transports
   }
   // tile (rt, ct) of this work-group: 256 doubles, register i of a lane at 64 i + lane
 #pragma unroll
@@ -1242,8 +1322,7 @@ hipError_t nn_fold(const qiral_nn *nn, hipStream_t s) {
 template <int SIO>
 void nn_pass_a(const qiral_nn *nn, const void *in0, const void *in1, bool adj, int zb, hipStream_t s) {
   const Geo &g = nn->lat->geo;
-  // three work-groups per compute unit (its register use) walk the blocks
-  const int wgs = std::min(2 * g.nb, 3 * 256);
+  const int wgs = std::min(2 * g.nb, 2 * 256);   // all resident: two per compute unit
   hipLaunchKernelGGL((k_nn_pass_a<SIO>), dim3(wgs), dim3(256), 0, s, g, nn->lat->g32,
                      (const float *)(nn->kfrag32 + (adj ? FRAG32 : 0)), in0, in1, nn->paths, full_bytes32(g), zb);
 }

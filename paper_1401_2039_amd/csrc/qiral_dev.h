@@ -163,11 +163,12 @@ template <> struct SpinorIO<S_F32> {
   static constexpr int UNITS = 6;
   static constexpr size_t SITE_BYTES = 96;
   struct Raw { float4 q[6]; };
+  template <bool NT = false>
   __device__ static void fetch(const void *base, int s, size_t npad, Raw &r) {
     (void)npad;
     const float4 *p = (const float4 *)base + (size_t)(s >> 6) * (6 * WAVE) + (s & 63);
 #pragma unroll
-    for (int j = 0; j < 6; ++j) r.q[j] = p[j * WAVE];
+    for (int j = 0; j < 6; ++j) r.q[j] = NT ? ld_nt(p + j * WAVE) : p[j * WAVE];
   }
   __device__ static void decode(const Raw &r, cpx<float> v[12]) {
 #pragma unroll
