@@ -193,7 +193,7 @@ __global__ __launch_bounds__(WG, HOP_MIN_WAVES(S, T, NR)) void k_hop(Geo g, cons
                                                              const void *__restrict__ in, void *__restrict__ out,
                                                              const void *__restrict__ xin, size_t fstride, int nrhs,
                                                              int p, size_t hoff, double a, int tile, int zb, int chio,
-                                                             int chix, double tmu) {
+                                                             int chix, double tmu, int ont) {
   using R = typename SpinorIO<S>::R;
   using LDS = HopLds<T, NR, R>;
   if (p < 0) {
@@ -244,7 +244,8 @@ __global__ __launch_bounds__(WG, HOP_MIN_WAVES(S, T, NR)) void k_hop(Geo g, cons
       for (int k = 0; k < 12; ++k) acc[r][k] = cadd(xv[k], cscale(ar, acc[r][k]));
     }
     apply_chi(acc[r], chio, tmu);
-    SpinorIO<S>::template store_fast<NT>((char *)out + (size_t)(r0 + r) * fstride, s, npad, acc[r]);
+    if (ont) SpinorIO<S>::template store_fast<true>((char *)out + (size_t)(r0 + r) * fstride, s, npad, acc[r]);
+    else SpinorIO<S>::template store_fast<false>((char *)out + (size_t)(r0 + r) * fstride, s, npad, acc[r]);
   }
 }
 
@@ -273,6 +274,27 @@ bool hop_stream(const Geo &g, int prec, long nrhs, long ngroups) {
   const double sp = prec == QIRAL_F64 ? 192 : prec == QIRAL_F32 ? 96 : 52;
   const double bytes = (double)g.vh * (8 * link + 2 * sp * nrhs);
   return bytes > 128e6;   // half the 256 MB last-level cache
+}
+
+// Both sides of these rules, in ms per FP64 CGNR solve unless said otherwise
+// (streaming stores of the hops' outputs off / on, then the vector kernels'
+// level 0 / 1 / 2 with the better of them):
+//   one system, 20^3x40 (31 MB a vector): 8.72 / 9.14, 8.72 / 8.81 / 8.86
+//   one system, 24^3x48 (64 MB): 16.7 / 17.2, 16.7 / 16.0 / 16.2
+//   one system, 32^3x64 (201 MB): 52.9 / 49.3, 49.3 / 47.4 / 49.0
+//   one system, 32^3x64 in FP32 (100 MB): 31.3 / 31.0, 31.0 / 30.1 / 30.0
+//   2 of 16^3x32 (25 MB): 6.86 / -, - / 6.82 / 6.83; 3 (38 MB): 10.4, 9.92 / 10.0
+//   2 of 24^3x48 (127 MB): level 1 28.6, level 2 29.2
+//   12 of 24^3x48 (764 MB): 163.9 / 162.5 / 159.5; FP32 102.8 / 101.6 / 99.3;
+//   F16S 69.9 / 68.6 / 66.7
+//   8 lattices of 4 sizes, FP32 (48 MB): 14.35 (off, 0), 13.6 (on, 1), 13.2 (on, 2)
+//   3 F32 fields of 24^3x48 through S: 207 / 172 us; 12: 640 / 621 us
+bool out_stream(size_t bytes, int nsys) { return bytes >= (nsys > 1 ? 16e6 : 80e6); }
+
+int vec_stream(size_t bytes, int nsys, bool same_lattice) {
+  if (nsys == 1) return bytes >= 48e6;
+  if (bytes < 16e6) return 0;
+  return bytes >= 200e6 || !same_lattice ? 2 : 1;
 }
 
 bool zb_valid(const Geo &g, int zb) {
@@ -342,7 +364,12 @@ static hipError_t launch_hop_ttt(const HopCfg &c, const qiral_lattice *lat, cons
   const long nitems = ntile * tile * ((h.nrhs + NR - 1) / NR);
   const int nwg = (int)((nitems * T + 3) / 4);
   const dim3 grid(nwg, h.p < 0 ? 2 : 1), block(WG);
-#define QARGS g, gauge, h.in, h.out, h.x, fstride, h.nrhs, h.p, hb, h.a, tile, zb, h.chio, h.chix, tmu
+  // several groups of right-hand sides: the rule of the solvers' vectors; one
+  // group: with its links, unless the next launch reads the output while the
+  // last-level cache still holds it
+  const size_t ob = hb * (size_t)h.nrhs;
+  const int ont = (h.nrhs + NR - 1) / NR > 1 ? out_stream(ob, h.nrhs) : NT && !(h.reread && !out_stream(ob, 1));
+#define QARGS g, gauge, h.in, h.out, h.x, fstride, h.nrhs, h.p, hb, h.a, tile, zb, h.chio, h.chix, tmu, ont
   if (!h.dagger) {
     if (h.epi == 0) hipLaunchKernelGGL((k_hop<S, L, false, 0, T, NR, NT>), grid, block, 0, h.st, QARGS);
     else hipLaunchKernelGGL((k_hop<S, L, false, 1, T, NR, NT>), grid, block, 0, h.st, QARGS);
@@ -391,9 +418,9 @@ hipError_t launch_hop_cfg(const HopCfg &c, const qiral_lattice *lat, int prec, c
 }
 
 hipError_t launch_hop(const qiral_lattice *lat, int prec, int dagger, int p, int epi, double a, const void *in,
-                      void *out, const void *x, int nrhs, hipStream_t st, int chio, int chix) {
+                      void *out, const void *x, int nrhs, hipStream_t st, int chio, int chix, bool reread) {
   return launch_hop_cfg(hop_config(lat, prec, nrhs), lat, prec,
-                        HopCall{dagger, p, epi, a, in, out, x, nrhs, st, chio, chix});
+                        HopCall{dagger, p, epi, a, in, out, x, nrhs, st, chio, chix, reread});
 }
 
 hipError_t launch_D(const qiral_lattice *lat, int prec, int dagger, void *out, const void *in, int nrhs,
@@ -604,7 +631,8 @@ extern "C" qiral_status qiral_apply_M(const qiral_lattice *lat, void *out, const
     QIRAL_HIP(launch_D(lat, prec, dag, out, in, nrhs, s));   // full fields: [rhs][even | odd]
   } else {
     // S = A - kappa^2 H_oe A^-1 H_eo (S^dagger: daggered hops and site factors)
-    QIRAL_HIP(launch_hop(lat, prec, dag, 0, 0, 1.0, in, tmp, nullptr, nrhs, s, dag ? CHI_AINVDAG : CHI_AINV, CHI_ONE));
+    QIRAL_HIP(launch_hop(lat, prec, dag, 0, 0, 1.0, in, tmp, nullptr, nrhs, s, dag ? CHI_AINVDAG : CHI_AINV, CHI_ONE,
+                         true));
     QIRAL_HIP(launch_hop(lat, prec, dag, 1, 1, -k * k, tmp, out, in, nrhs, s, CHI_ONE, dag ? CHI_ADAG : CHI_A));
   }
   return QIRAL_OK;

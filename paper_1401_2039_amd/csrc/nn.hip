@@ -1149,65 +1149,77 @@ __device__ __forceinline__ const double2 *sys_coef(const double2 *coef, size_t i
   return coef + (i / n2) * BQ_SLOTS;
 }
 
+// Loads and stores of the vector steps below at the streaming level LV (vec_stream).
+template <bool NT> __device__ __forceinline__ double2 vld(const double2 *p) { return NT ? ld_nt(p) : *p; }
+template <bool NT> __device__ __forceinline__ void vst(double2 *p, double2 v) {
+  if (NT) st_nt(p, v);
+  else *p = v;
+}
+
 // P = R + beta (P - omega V)
+template <int LV>
 __global__ __launch_bounds__(256) void k_bq_p(const double2 *__restrict__ coef, const double2 *__restrict__ R,
                                               const double2 *__restrict__ V, double2 *__restrict__ P, size_t n2,
                                               size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double2 *c = sys_coef(coef, i, n2);
-  const double2 be = c[BQ_C_BETA], om = c[BQ_C_OMEGA], r = R[i], v = V[i];
-  double2 p = P[i];
+  const double2 be = c[BQ_C_BETA], om = c[BQ_C_OMEGA], r = vld<(LV > 1)>(R + i), v = vld<(LV > 0)>(V + i);
+  double2 p = vld<(LV > 1)>(P + i);
   p.x -= om.x * v.x - om.y * v.y;
   p.y -= om.x * v.y + om.y * v.x;
-  P[i] = make_double2(r.x + (be.x * p.x - be.y * p.y), r.y + (be.x * p.y + be.y * p.x));
+  vst<(LV > 1)>(P + i, make_double2(r.x + (be.x * p.x - be.y * p.y), r.y + (be.x * p.y + be.y * p.x)));
 }
 
 // S = R - alpha V
+template <int LV>
 __global__ __launch_bounds__(256) void k_bq_s(const double2 *__restrict__ coef, const double2 *__restrict__ V,
                                               const double2 *__restrict__ R, double2 *__restrict__ S, size_t n2,
                                               size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const double2 a = sys_coef(coef, i, n2)[BQ_C_MALPHA], v = V[i], r = R[i];
-  S[i] = make_double2(r.x + (a.x * v.x - a.y * v.y), r.y + (a.x * v.y + a.y * v.x));
+  const double2 a = sys_coef(coef, i, n2)[BQ_C_MALPHA], v = vld<(LV > 1)>(V + i), r = vld<(LV > 0)>(R + i);
+  vst<(LV > 1)>(S + i, make_double2(r.x + (a.x * v.x - a.y * v.y), r.y + (a.x * v.y + a.y * v.x)));
 }
 
 // X += alpha PH + omega SH
+template <int LV>
 __global__ __launch_bounds__(256) void k_bq_x(const double2 *__restrict__ coef, const double2 *__restrict__ PH,
                                               const double2 *__restrict__ SH, double2 *__restrict__ X, size_t n2,
                                               size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double2 *c = sys_coef(coef, i, n2);
-  const double2 al = c[BQ_C_X], om = c[BQ_C_X2], ph = PH[i], sh = SH[i];
-  double2 x = X[i];
+  const double2 al = c[BQ_C_X], om = c[BQ_C_X2], ph = vld<(LV > 0)>(PH + i), sh = vld<(LV > 0)>(SH + i);
+  double2 x = vld<(LV > 0)>(X + i);
   x.x += al.x * ph.x - al.y * ph.y;
   x.y += al.x * ph.y + al.y * ph.x;
   x.x += om.x * sh.x - om.y * sh.y;
   x.y += om.x * sh.y + om.y * sh.x;
-  X[i] = x;
+  vst<(LV > 0)>(X + i, x);
 }
 
 // partial pairs of (a | b): part[block * 2 + re/im]
+template <int LV>
 __global__ __launch_bounds__(256) void k_dot1(const double2 *__restrict__ a, const double2 *__restrict__ b, size_t n,
                                               double *__restrict__ part) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   double2 ab = make_double2(0.0, 0.0);
   if (i < n) {
-    const double2 av = a[i], bv = b[i];
+    const double2 av = vld<(LV > 1)>(a + i), bv = vld<(LV > 1)>(b + i);
     ab = make_double2(av.x * bv.x + av.y * bv.y, av.x * bv.y - av.y * bv.x);
   }
   block_pair(ab.x, ab.y, part + (size_t)blockIdx.x * 2);
 }
 
 // partial pairs of (a | b) and (a | a): part[(q * gridDim.x + block) * 2 + re/im]
+template <int LV>
 __global__ __launch_bounds__(256) void k_dot2(const double2 *__restrict__ a, const double2 *__restrict__ b, size_t n,
                                               double *__restrict__ part) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   double2 ab = make_double2(0.0, 0.0), aa = ab;
   if (i < n) {
-    const double2 av = a[i], bv = b[i];
+    const double2 av = vld<(LV > 1)>(a + i), bv = vld<(LV > 1)>(b + i);
     ab = make_double2(av.x * bv.x + av.y * bv.y, av.x * bv.y - av.y * bv.x);
     aa = make_double2(av.x * av.x + av.y * av.y, av.x * av.y - av.y * av.x);
   }
@@ -1215,15 +1227,17 @@ __global__ __launch_bounds__(256) void k_dot2(const double2 *__restrict__ a, con
 }
 
 // R = S - omega T, with the partial pairs of (RT | R) and (R | R), laid out as k_dot2's
+template <int LV>
 __global__ __launch_bounds__(256) void k_bq_r(const double2 *__restrict__ coef, const double2 *__restrict__ S,
                                               const double2 *__restrict__ T, const double2 *__restrict__ RT,
                                               double2 *__restrict__ R, size_t n2, size_t n, double *__restrict__ part) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   double2 rr = make_double2(0.0, 0.0), tr = rr;
   if (i < n) {
-    const double2 a = sys_coef(coef, i, n2)[BQ_C_MOMEGA], sv = S[i], tv = T[i], rt = RT[i];
+    const double2 a = sys_coef(coef, i, n2)[BQ_C_MOMEGA], sv = vld<(LV > 0)>(S + i), tv = vld<(LV > 0)>(T + i),
+                  rt = vld<(LV > 1)>(RT + i);
     const double2 r = make_double2(sv.x + (a.x * tv.x - a.y * tv.y), sv.y + (a.x * tv.y + a.y * tv.x));
-    R[i] = r;
+    vst<(LV > 1)>(R + i, r);
     tr = make_double2(rt.x * r.x + rt.y * r.y, rt.x * r.y - rt.y * r.x);
     rr = make_double2(r.x * r.x + r.y * r.y, 0.0);
   }
@@ -1762,7 +1776,7 @@ hipError_t flex_A(const Flex &f, void *y, const void *x, bool dag, hipStream_t s
   if (!f.schur) return launch_D(lat, QIRAL_F64, dag, y, x, nsys, s);
   const double k = lat->kappa;
   hipError_t e = launch_hop(lat, QIRAL_F64, dag, 0, 0, 1.0, x, f.tmpE, nullptr, nsys, s,
-                            dag ? CHI_AINVDAG : CHI_AINV, CHI_ONE);
+                            dag ? CHI_AINVDAG : CHI_AINV, CHI_ONE, true);
   if (e != hipSuccess) return e;
   return launch_hop(lat, QIRAL_F64, dag, 1, 1, -k * k, f.tmpE, y, x, nsys, s, CHI_ONE, dag ? CHI_ADAG : CHI_A);
 }
@@ -2237,32 +2251,34 @@ qiral_status run_bicgstab_prec(qiral_lattice *lat, double *x_canon, const double
     return QIRAL_OK;
   };
   const size_t ntot = (size_t)nsys * f.n2;
+  const int lv = vec_stream((size_t)nsys * f.vb, nsys, true);
+#define QLV(K) (lv == 0 ? K<0> : lv == 1 ? K<1> : K<2>)
   const dim3 gv((unsigned)(nsys * f.nbk)), bv(256), gs((unsigned)((nsys + 63) / 64)), bs(64);
   auto any_active = [&]() { return std::find(active.begin(), active.end(), 1) != active.end(); };
   if (any_active()) {
     QIRAL_HIP(hipMemcpyAsync(blk(RT), blk(R), (size_t)nsys * f.vb, hipMemcpyDeviceToDevice, s));
     hipLaunchKernelGGL(k_bq_init, gs, bs, 0, s, f.coef, nsys);
-    hipLaunchKernelGGL(k_dot1, gv, bv, 0, s, blk(RT), blk(R), ntot, f.part);
+    hipLaunchKernelGGL(QLV(k_dot1), gv, bv, 0, s, blk(RT), blk(R), ntot, f.part);
     hipLaunchKernelGGL(k_pair_final, dim3(1, nsys), dim3(256), 0, s, f.part, f.nbk, f.coef, (int)BQ_RHO1,
                        (int)BQ_RHO1);
   }
   while (any_active()) {
     hipLaunchKernelGGL(k_bq_beta, gs, bs, 0, s, f.coef, nsys);
-    hipLaunchKernelGGL(k_bq_p, gv, bv, 0, s, f.coef, blk(R), blk(V), blk(P), f.n2, ntot);   // p = r + beta (p - omega v)
+    hipLaunchKernelGGL(QLV(k_bq_p), gv, bv, 0, s, f.coef, blk(R), blk(V), blk(P), f.n2, ntot);   // p = r + beta (p - omega v)
     QIRAL_HIP(flex_M(f, blk(PH), blk(P), false, s, nsys));
     QIRAL_HIP(flex_A(f, blk(V), blk(PH), false, s, nsys));
-    hipLaunchKernelGGL(k_dot1, gv, bv, 0, s, blk(RT), blk(V), ntot, f.part);
+    hipLaunchKernelGGL(QLV(k_dot1), gv, bv, 0, s, blk(RT), blk(V), ntot, f.part);
     hipLaunchKernelGGL(k_pair_final, dim3(1, nsys), dim3(256), 0, s, f.part, f.nbk, f.coef, (int)BQ_RV, (int)BQ_RV);
     hipLaunchKernelGGL(k_bq_alpha, gs, bs, 0, s, f.coef, nsys);
-    hipLaunchKernelGGL(k_bq_s, gv, bv, 0, s, f.coef, blk(V), blk(R), blk(S), f.n2, ntot);   // s = r - alpha v
+    hipLaunchKernelGGL(QLV(k_bq_s), gv, bv, 0, s, f.coef, blk(V), blk(R), blk(S), f.n2, ntot);   // s = r - alpha v
     QIRAL_HIP(flex_M(f, blk(SH), blk(S), false, s, nsys));
     QIRAL_HIP(flex_A(f, blk(T), blk(SH), false, s, nsys));
-    hipLaunchKernelGGL(k_dot2, gv, bv, 0, s, blk(T), blk(S), ntot, f.part);   // (t|s), ||t||^2
+    hipLaunchKernelGGL(QLV(k_dot2), gv, bv, 0, s, blk(T), blk(S), ntot, f.part);   // (t|s), ||t||^2
     hipLaunchKernelGGL(k_pair_final, dim3(2, nsys), dim3(256), 0, s, f.part, f.nbk, f.coef, (int)BQ_TS, (int)BQ_TT);
     hipLaunchKernelGGL(k_bq_omega, gs, bs, 0, s, f.coef, nsys);
     // x += alpha p^ + omega s^; r = s - omega t with (r~|r), the next rho, and ||r||^2
-    hipLaunchKernelGGL(k_bq_x, gv, bv, 0, s, f.coef, blk(PH), blk(SH), blk(X), f.n2, ntot);
-    hipLaunchKernelGGL(k_bq_r, gv, bv, 0, s, f.coef, blk(S), blk(T), blk(RT), blk(R), f.n2, ntot, f.part);
+    hipLaunchKernelGGL(QLV(k_bq_x), gv, bv, 0, s, f.coef, blk(PH), blk(SH), blk(X), f.n2, ntot);
+    hipLaunchKernelGGL(QLV(k_bq_r), gv, bv, 0, s, f.coef, blk(S), blk(T), blk(RT), blk(R), f.n2, ntot, f.part);
     hipLaunchKernelGGL(k_pair_final, dim3(2, nsys), dim3(256), 0, s, f.part, f.nbk, f.coef, (int)BQ_RHO1,
                        (int)BQ_RN2);
     if ((st = flex_read(hc.data(), f.coef, sizeof(double2) * hc.size(), s)) != QIRAL_OK) return st;
@@ -2300,6 +2316,7 @@ qiral_status run_bicgstab_prec(qiral_lattice *lat, double *x_canon, const double
       }
     }
   }
+#undef QLV
   // every solution out first (a CG fallback below reuses the workspace), with
   // ||b - D x||^2 in the coefficient slots: one host read for all systems
   if (f.schur) {

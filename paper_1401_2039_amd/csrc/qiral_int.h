@@ -59,11 +59,19 @@ constexpr int hop_nr_max(int S, int T) {
   return S == 0 ? (T == 4 ? 2 : 0) : T == 1 ? (S == 2 ? 1 : 0) : (S == 1 && T == 2) ? 2 : 4;
 }
 int hop_split(int prec, long nwork);
-// Streaming (non-temporal) link loads and output stores for hops whose working
-// set exceeds half the last-level cache and whose links are read by one group
-// of right-hand sides (several groups re-read each tile's links from the cache).
+// Streaming (non-temporal) link loads for hops whose working set exceeds half
+// the last-level cache and whose links are read by one group of right-hand
+// sides (several groups re-read each tile's links from the cache).
 // QIRAL_HOP_NT=0|1 overrides.
 bool hop_stream(const Geo &g, int prec, long nrhs, long ngroups);
+// Streaming stores of a hop's output that is `bytes` over all of nsys systems
+// and that later launches read.
+bool out_stream(size_t bytes, int nsys);
+// Streaming level of the vector kernels of a solve, one of whose vectors is
+// `bytes` over its nsys systems: 1: the accesses that no cache keeps until the
+// next (the solution, and a vector's last read before it is overwritten); 2: all
+// of them.
+int vec_stream(size_t bytes, int nsys, bool same_lattice);
 // Planes per z-tile of the hop's block order (block_order), 0 for the plain
 // order.  QIRAL_HOP_ORDER=0 forces the plain order, QIRAL_HOP_ORDER=n tiles of
 // n planes where the lattice allows them.
@@ -84,6 +92,7 @@ struct HopCall {
   int nrhs;
   hipStream_t st;
   int chio = 0, chix = 0;
+  bool reread = false;   // the next launch reads out
 };
 hipError_t launch_hop_cfg(const HopCfg &c, const qiral_lattice *lat, int prec, const HopCall &h);
 
@@ -95,7 +104,8 @@ inline int wg_count(long nwaves) { return (int)((nwaves + 3) / 4); }
 // C_o, C_x are the twisted-mass site factors selected by chio, chix (CHI_*;
 // the identity for CHI_ONE or mu = 0).
 hipError_t launch_hop(const qiral_lattice *lat, int prec, int dagger, int out_parity, int epi, double a,
-                      const void *in, void *out, const void *x, int nrhs, hipStream_t s, int chio = 0, int chix = 0);
+                      const void *in, void *out, const void *x, int nrhs, hipStream_t s, int chio = 0, int chix = 0,
+                      bool reread = false);
 // out = D in (or D^dagger in) on nrhs consecutive full fields.
 hipError_t launch_D(const qiral_lattice *lat, int prec, int dagger, void *out, const void *in, int nrhs, hipStream_t s);
 

@@ -253,6 +253,14 @@ qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, cons
   L.NR = hc.nr;
   L.NT = hop_stream(sys[0].lat->geo, prec, same_lattice ? nsys : 1, same_lattice ? (nsys + hc.nr - 1) / hc.nr : 1);
   L.NT64 = hop_stream(sys[0].lat->geo, QIRAL_F64, 1, 1);
+  size_t vec_it = 0, vec_64 = 0;   // one vector of every system, iterate precision and FP64
+  for (int i = 0; i < nsys; ++i) {
+    vec_it += half_bytes(sys[i].lat->geo, prec);
+    vec_64 += half_bytes(sys[i].lat->geo, QIRAL_F64);
+  }
+  L.vec = vec_stream(vec_it, nsys, same_lattice);
+  L.ont = out_stream(vec_it, nsys);
+  L.ont64 = out_stream(vec_64, nsys);
   L.stream = s;
 
   // ---- inputs

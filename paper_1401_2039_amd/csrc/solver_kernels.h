@@ -17,8 +17,10 @@ struct Launch {
   int prec;                  // iterate precision (S_F64, S_F32, S_F16S)
   int T;                     // waves per site block of the iterate-precision hop (2 or 4)
   int NR;                    // systems per item of the grouped table
-  int NT;                    // streaming accesses in the iterate-precision hop (see hop_stream)
+  int NT;                    // streaming link loads in the iterate-precision hop (see hop_stream)
   int NT64;                  // ... and in the FP64 hops of a mixed solve
+  int vec;                   // streaming level of the vector kernels (see vec_stream)
+  int ont, ont64;            // streaming stores of the hops' outputs, iterate precision and FP64
   int chio = 0, chix = 0;    // twisted-mass site factors of the hop's epilogue (set by hop_sys)
   hipStream_t stream;
 };

@@ -27,7 +27,8 @@ template <int S, int L, bool DAG, int EPI, int T, int NR, bool NT>
 __global__ __launch_bounds__(WG, HOP_MIN_WAVES(S, T, NR)) void k_hop_sys(const SysDesc *__restrict__ sdesc,
                                                                  const uint32_t *__restrict__ work, int nwork,
                                                                  int fin_id, int fout, int fx, int par, int amode,
-                                                                 int mask, int red, int slot, int chio, int chix) {
+                                                                 int mask, int red, int slot, int chio, int chix,
+                                                                 int ont) {
   using R = typename SpinorIO<S>::R;
   using LDS = HopLds<T, NR, R>;
   __shared__ typename LDS::V lds[LDS::VECS];
@@ -74,7 +75,8 @@ __global__ __launch_bounds__(WG, HOP_MIN_WAVES(S, T, NR)) void k_hop_sys(const S
         apply_chi(acc[r], chio, d0.tmu);
         if (red == 3) { dot12(acc[r], xv, v[0], v[1]); v[2] = norm12(acc[r]); }
       }
-      SpinorIO<S>::template store_fast<NT>(d.f[fout], it.s, npad, acc[r]);
+      if (ont) SpinorIO<S>::template store_fast<true>(d.f[fout], it.s, npad, acc[r]);
+      else SpinorIO<S>::template store_fast<false>(d.f[fout], it.s, npad, acc[r]);
       if (red == 1) v[0] = norm12(acc[r]);
       if (red == 2 || red == 4) {
         cpx<R> rt[12];
@@ -256,7 +258,7 @@ __global__ __launch_bounds__(WG) void k_bnorm(const SysDesc *__restrict__ sdesc,
 // to k_cg2, which reads P anyway: X += alpha P there, before P changes, is the
 // same arithmetic one pass over the vectors cheaper; k_cg_xfin applies the last
 // one when the solve stops here.
-template <int S, int XS>
+template <int S, int XS, int V>
 __global__ __launch_bounds__(WG) void k_cg1(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
                                             int nwork) {
   using R = typename SpinorIO<S>::R;
@@ -273,17 +275,17 @@ __global__ __launch_bounds__(WG) void k_cg1(const SysDesc *__restrict__ sdesc, c
     if (xhere) {
       cpx<R> p[12];
       cpx<RX> x[12];
-      SpinorIO<S>::load(d.f[F_P], it.s, d.npad, p);
-      SpinorIO<XS>::load(d.f[F_X], it.s, d.npad, x);
+      SpinorIO<S>::template load<(V > 1)>(d.f[F_P], it.s, d.npad, p);
+      SpinorIO<XS>::template load<(V > 0)>(d.f[F_X], it.s, d.npad, x);
 #pragma unroll
       for (int k = 0; k < 12; ++k) x[k] = cadd(x[k], cscale((RX)al, cmake((RX)p[k].re, (RX)p[k].im)));
-      SpinorIO<XS>::store(d.f[F_X], it.s, d.npad, x);
+      SpinorIO<XS>::template store<(V > 0)>(d.f[F_X], it.s, d.npad, x);
     }
-    SpinorIO<S>::load(d.f[F_R], it.s, d.npad, r);
-    SpinorIO<S>::load(d.f[F_AP], it.s, d.npad, ap);
+    SpinorIO<S>::template load<(V > 1)>(d.f[F_R], it.s, d.npad, r);
+    SpinorIO<S>::template load<(V > 0)>(d.f[F_AP], it.s, d.npad, ap);
 #pragma unroll
     for (int k = 0; k < 12; ++k) r[k] = csub(r[k], cscale((R)al, ap[k]));
-    SpinorIO<S>::store(d.f[F_R], it.s, d.npad, r);
+    SpinorIO<S>::template store<(V > 1)>(d.f[F_R], it.s, d.npad, r);
     v[0] = norm12(r);
   }
   sys_partial(d, SL_R, it, v);
@@ -373,7 +375,7 @@ __global__ __launch_bounds__(WG) void k_cr2(const SysDesc *__restrict__ sdesc, c
 
 // CGNR: P = Z + beta P; with XUPD (plain solves, in the iterations) first
 // X += alpha P with the old P (the update k_cg1 left).
-template <int S, bool XUPD>
+template <int S, bool XUPD, int V>
 __global__ __launch_bounds__(WG) void k_cg2(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
                                             int nwork) {
   using R = typename SpinorIO<S>::R;
@@ -384,23 +386,23 @@ __global__ __launch_bounds__(WG) void k_cg2(const SysDesc *__restrict__ sdesc, c
   if (it.s >= d.g.vh) return;
   const R be = (R)d.st->beta;
   cpx<R> p[12], z[12];
-  SpinorIO<S>::load(d.f[F_P], it.s, d.npad, p);
+  SpinorIO<S>::template load<(V > 1)>(d.f[F_P], it.s, d.npad, p);
   if (XUPD) {
     const double al = d.st->alpha;
     cpx<double> x[12];
-    SpinorIO<S_F64>::load(d.f[F_X], it.s, d.npad, x);
+    SpinorIO<S_F64>::load<(V > 0)>(d.f[F_X], it.s, d.npad, x);
 #pragma unroll
     for (int k = 0; k < 12; ++k) x[k] = cadd(x[k], cscale(al, cmake((double)p[k].re, (double)p[k].im)));
-    SpinorIO<S_F64>::store(d.f[F_X], it.s, d.npad, x);
+    SpinorIO<S_F64>::store<(V > 0)>(d.f[F_X], it.s, d.npad, x);
   }
-  SpinorIO<S>::load(d.f[F_Z], it.s, d.npad, z);
+  SpinorIO<S>::template load<(V > 0)>(d.f[F_Z], it.s, d.npad, z);
 #pragma unroll
   for (int k = 0; k < 12; ++k) p[k] = cadd(z[k], cscale(be, p[k]));
-  SpinorIO<S>::store(d.f[F_P], it.s, d.npad, p);
+  SpinorIO<S>::template store<(V > 1)>(d.f[F_P], it.s, d.npad, p);
 }
 
 // BiCGStab: P = R + beta (P - omega V)    (V lives in F_AP)
-template <int S>
+template <int S, int V>
 __global__ __launch_bounds__(WG) void k_bi_p(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
                                              int nwork) {
   using R = typename SpinorIO<S>::R;
@@ -411,16 +413,16 @@ __global__ __launch_bounds__(WG) void k_bi_p(const SysDesc *__restrict__ sdesc, 
   if (it.s >= d.g.vh) return;
   const cpx<R> be = cmake((R)d.st->be_re, (R)d.st->be_im), om = cmake((R)d.st->om_re, (R)d.st->om_im);
   cpx<R> p[12], r[12], vv[12];
-  SpinorIO<S>::load(d.f[F_P], it.s, d.npad, p);
-  SpinorIO<S>::load(d.f[F_R], it.s, d.npad, r);
-  SpinorIO<S>::load(d.f[F_AP], it.s, d.npad, vv);
+  SpinorIO<S>::template load<(V > 1)>(d.f[F_P], it.s, d.npad, p);
+  SpinorIO<S>::template load<(V > 1)>(d.f[F_R], it.s, d.npad, r);
+  SpinorIO<S>::template load<(V > 0)>(d.f[F_AP], it.s, d.npad, vv);
 #pragma unroll
   for (int k = 0; k < 12; ++k) p[k] = cadd(r[k], cmul(be, csub(p[k], cmul(om, vv[k]))));
-  SpinorIO<S>::store(d.f[F_P], it.s, d.npad, p);
+  SpinorIO<S>::template store<(V > 1)>(d.f[F_P], it.s, d.npad, p);
 }
 
 // BiCGStab: S = R - alpha V    (S lives in F_Z)
-template <int S>
+template <int S, int V>
 __global__ __launch_bounds__(WG) void k_bi_s(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
                                              int nwork) {
   using R = typename SpinorIO<S>::R;
@@ -431,15 +433,15 @@ __global__ __launch_bounds__(WG) void k_bi_s(const SysDesc *__restrict__ sdesc, 
   if (it.s >= d.g.vh) return;
   const cpx<R> al = cmake((R)d.st->al_re, (R)d.st->al_im);
   cpx<R> r[12], vv[12];
-  SpinorIO<S>::load(d.f[F_R], it.s, d.npad, r);
-  SpinorIO<S>::load(d.f[F_AP], it.s, d.npad, vv);
+  SpinorIO<S>::template load<(V > 0)>(d.f[F_R], it.s, d.npad, r);
+  SpinorIO<S>::template load<(V > 1)>(d.f[F_AP], it.s, d.npad, vv);
 #pragma unroll
   for (int k = 0; k < 12; ++k) r[k] = csub(r[k], cmul(al, vv[k]));
-  SpinorIO<S>::store(d.f[F_Z], it.s, d.npad, r);
+  SpinorIO<S>::template store<(V > 1)>(d.f[F_Z], it.s, d.npad, r);
 }
 
 // BiCGStab: X += alpha P + omega S; R = S - omega T; reduces (rt | R) and ||R||^2
-template <int S, int XS>
+template <int S, int XS, int V>
 __global__ __launch_bounds__(WG) void k_bi_xr(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
                                               int nwork) {
   using R = typename SpinorIO<S>::R;
@@ -453,19 +455,19 @@ __global__ __launch_bounds__(WG) void k_bi_xr(const SysDesc *__restrict__ sdesc,
     const cpx<RX> al = cmake((RX)d.st->al_re, (RX)d.st->al_im), om = cmake((RX)d.st->om_re, (RX)d.st->om_im);
     cpx<R> p[12], s[12], t[12], rt[12];
     cpx<RX> x[12];
-    SpinorIO<S>::load(d.f[F_P], it.s, d.npad, p);
-    SpinorIO<S>::load(d.f[F_Z], it.s, d.npad, s);
-    SpinorIO<XS>::load(d.f[F_X], it.s, d.npad, x);
+    SpinorIO<S>::template load<(V > 1)>(d.f[F_P], it.s, d.npad, p);
+    SpinorIO<S>::template load<(V > 0)>(d.f[F_Z], it.s, d.npad, s);
+    SpinorIO<XS>::template load<(V > 0)>(d.f[F_X], it.s, d.npad, x);
 #pragma unroll
     for (int k = 0; k < 12; ++k)
       x[k] = cadd(x[k], cadd(cmul(al, cmake((RX)p[k].re, (RX)p[k].im)), cmul(om, cmake((RX)s[k].re, (RX)s[k].im))));
-    SpinorIO<XS>::store(d.f[F_X], it.s, d.npad, x);
-    SpinorIO<S>::load(d.f[F_T], it.s, d.npad, t);
+    SpinorIO<XS>::template store<(V > 0)>(d.f[F_X], it.s, d.npad, x);
+    SpinorIO<S>::template load<(V > 0)>(d.f[F_T], it.s, d.npad, t);
     const cpx<R> omr = cmake((R)d.st->om_re, (R)d.st->om_im);
 #pragma unroll
     for (int k = 0; k < 12; ++k) s[k] = csub(s[k], cmul(omr, t[k]));
-    SpinorIO<S>::store(d.f[F_R], it.s, d.npad, s);
-    SpinorIO<S>::load(d.f[F_RT], it.s, d.npad, rt);
+    SpinorIO<S>::template store<(V > 1)>(d.f[F_R], it.s, d.npad, s);
+    SpinorIO<S>::template load<(V > 1)>(d.f[F_RT], it.s, d.npad, rt);
     dot12(rt, s, v[0], v[1]);
     v[2] = norm12(s);
   }
@@ -509,7 +511,7 @@ template <int S, int L, int T, int NR, bool NT>
 static void hop_sys_tt(const Launch &l, bool dag, int epi, int fi, int fo, int fx, int par, int amode, int mask,
                        int red, int slot) {
   const dim3 g = grid_of(l.nwork, T), b(WG);
-#define QARGS l.desc, l.work, l.nwork, fi, fo, fx, par, amode, mask, red, slot, l.chio, l.chix
+#define QARGS l.desc, l.work, l.nwork, fi, fo, fx, par, amode, mask, red, slot, l.chio, l.chix, l.ont
   if (!dag) {
     if (epi == 0) hipLaunchKernelGGL((k_hop_sys<S, L, false, 0, T, NR, NT>), g, b, 0, l.stream, QARGS);
     else hipLaunchKernelGGL((k_hop_sys<S, L, false, 1, T, NR, NT>), g, b, 0, l.stream, QARGS);
@@ -561,7 +563,7 @@ void hop_sys(const Launch &l, int prec, bool dag, int epi, int fi, int fo, int f
   lp.chio = chio;
   lp.chix = chix;
   if (grouped) { lp.work = l.work_hop; lp.nwork = l.nwork_hop; lp.T = l.T; lp.NR = l.NR; lp.NT = l.NT; }
-  else { lp.T = 4; lp.NR = 1; lp.NT = l.NT64; }
+  else { lp.T = 4; lp.NR = 1; lp.NT = l.NT64; lp.ont = l.ont64; }
   if (prec == S_F64) hop_sys_p<S_F64, L_F64R18>(lp, dag, epi, fi, fo, fx, par, amode, mask, red, slot);
   else if (prec == S_F32) hop_sys_p<S_F32, L_F32R12>(lp, dag, epi, fi, fo, fx, par, amode, mask, red, slot);
   else hop_sys_p<S_F16S, L_F16R12>(lp, dag, epi, fi, fo, fx, par, amode, mask, red, slot);
@@ -595,21 +597,24 @@ void bnorm(const Launch &l) {
   reduce(l, SL_B, FIN_BNORM, ST_ANY);
 }
 
+// A vector kernel in the form of the launch's streaming level (vec_stream).
+#define QVEC(KERNEL0, KERNEL1, KERNEL2)                                                                \
+  hipLaunchKernelGGL(l.vec == 0 ? (KERNEL0) : l.vec == 1 ? (KERNEL1) : (KERNEL2), grid_of(l.nwork), dim3(WG), 0, \
+                     l.stream, l.desc, l.work, l.nwork)
+
 void cg1(const Launch &l, int prec) {
-  const dim3 g = grid_of(l.nwork), b(WG);
-  if (prec == S_F64) hipLaunchKernelGGL((k_cg1<S_F64, S_F64>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
-  else if (prec == S_F32) hipLaunchKernelGGL((k_cg1<S_F32, S_F32>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
-  else hipLaunchKernelGGL((k_cg1<S_F16S, S_F32>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
+  if (prec == S_F64) QVEC((k_cg1<S_F64, S_F64, 0>), (k_cg1<S_F64, S_F64, 1>), (k_cg1<S_F64, S_F64, 2>));
+  else if (prec == S_F32) QVEC((k_cg1<S_F32, S_F32, 0>), (k_cg1<S_F32, S_F32, 1>), (k_cg1<S_F32, S_F32, 2>));
+  else QVEC((k_cg1<S_F16S, S_F32, 0>), (k_cg1<S_F16S, S_F32, 1>), (k_cg1<S_F16S, S_F32, 2>));
   reduce(l, SL_R, FIN_NR, ST_RUN);
 }
 
 void cg2(const Launch &l, int prec, bool xupd) {
-  const dim3 g = grid_of(l.nwork), b(WG);
   if (prec == S_F64) {
-    if (xupd) hipLaunchKernelGGL((k_cg2<S_F64, true>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
-    else hipLaunchKernelGGL((k_cg2<S_F64, false>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
-  } else if (prec == S_F32) hipLaunchKernelGGL((k_cg2<S_F32, false>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
-  else hipLaunchKernelGGL((k_cg2<S_F16S, false>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
+    if (xupd) QVEC((k_cg2<S_F64, true, 0>), (k_cg2<S_F64, true, 1>), (k_cg2<S_F64, true, 2>));
+    else QVEC((k_cg2<S_F64, false, 0>), (k_cg2<S_F64, false, 1>), (k_cg2<S_F64, false, 2>));
+  } else if (prec == S_F32) QVEC((k_cg2<S_F32, false, 0>), (k_cg2<S_F32, false, 1>), (k_cg2<S_F32, false, 2>));
+  else QVEC((k_cg2<S_F16S, false, 0>), (k_cg2<S_F16S, false, 1>), (k_cg2<S_F16S, false, 2>));
 }
 
 void cg_xfin(const Launch &l) {
@@ -628,26 +633,24 @@ void cr2(const Launch &l, bool init) {
 }
 
 void bi_p(const Launch &l, int prec) {
-  const dim3 g = grid_of(l.nwork), b(WG);
-  if (prec == S_F64) hipLaunchKernelGGL(k_bi_p<S_F64>, g, b, 0, l.stream, l.desc, l.work, l.nwork);
-  else if (prec == S_F32) hipLaunchKernelGGL(k_bi_p<S_F32>, g, b, 0, l.stream, l.desc, l.work, l.nwork);
-  else hipLaunchKernelGGL(k_bi_p<S_F16S>, g, b, 0, l.stream, l.desc, l.work, l.nwork);
+  if (prec == S_F64) QVEC((k_bi_p<S_F64, 0>), (k_bi_p<S_F64, 1>), (k_bi_p<S_F64, 2>));
+  else if (prec == S_F32) QVEC((k_bi_p<S_F32, 0>), (k_bi_p<S_F32, 1>), (k_bi_p<S_F32, 2>));
+  else QVEC((k_bi_p<S_F16S, 0>), (k_bi_p<S_F16S, 1>), (k_bi_p<S_F16S, 2>));
 }
 
 void bi_s(const Launch &l, int prec) {
-  const dim3 g = grid_of(l.nwork), b(WG);
-  if (prec == S_F64) hipLaunchKernelGGL(k_bi_s<S_F64>, g, b, 0, l.stream, l.desc, l.work, l.nwork);
-  else if (prec == S_F32) hipLaunchKernelGGL(k_bi_s<S_F32>, g, b, 0, l.stream, l.desc, l.work, l.nwork);
-  else hipLaunchKernelGGL(k_bi_s<S_F16S>, g, b, 0, l.stream, l.desc, l.work, l.nwork);
+  if (prec == S_F64) QVEC((k_bi_s<S_F64, 0>), (k_bi_s<S_F64, 1>), (k_bi_s<S_F64, 2>));
+  else if (prec == S_F32) QVEC((k_bi_s<S_F32, 0>), (k_bi_s<S_F32, 1>), (k_bi_s<S_F32, 2>));
+  else QVEC((k_bi_s<S_F16S, 0>), (k_bi_s<S_F16S, 1>), (k_bi_s<S_F16S, 2>));
 }
 
 void bi_xr(const Launch &l, int prec) {
-  const dim3 g = grid_of(l.nwork), b(WG);
-  if (prec == S_F64) hipLaunchKernelGGL((k_bi_xr<S_F64, S_F64>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
-  else if (prec == S_F32) hipLaunchKernelGGL((k_bi_xr<S_F32, S_F32>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
-  else hipLaunchKernelGGL((k_bi_xr<S_F16S, S_F32>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
+  if (prec == S_F64) QVEC((k_bi_xr<S_F64, S_F64, 0>), (k_bi_xr<S_F64, S_F64, 1>), (k_bi_xr<S_F64, S_F64, 2>));
+  else if (prec == S_F32) QVEC((k_bi_xr<S_F32, S_F32, 0>), (k_bi_xr<S_F32, S_F32, 1>), (k_bi_xr<S_F32, S_F32, 2>));
+  else QVEC((k_bi_xr<S_F16S, S_F32, 0>), (k_bi_xr<S_F16S, S_F32, 1>), (k_bi_xr<S_F16S, S_F32, 2>));
   reduce(l, SL_BI3, FIN_BI_RHO, ST_RUN);
 }
+#undef QVEC
 
 void copy_field(const Launch &l, int prec, int fsrc, int fdst, int mask, int chi) {
   const dim3 g = grid_of(l.nwork), b(WG);
