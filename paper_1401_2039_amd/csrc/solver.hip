@@ -28,7 +28,7 @@
 #include <vector>
 
 #include "qiral_int.h"
-#include "solver_dev.h"
+#include "solver_steps.h"
 #include "solver_kernels.h"
 
 namespace qiral {

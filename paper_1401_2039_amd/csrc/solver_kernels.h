@@ -25,8 +25,6 @@ struct Launch {
   hipStream_t stream;
 };
 
-enum : int { A_ONE = 0, A_KAPPA = 1, A_MKAPPA2 = 2, A_MKAPPA = 3 };
-
 // The hop over the system table (see k_hop_sys); chio / chix select the
 // twisted-mass site factors applied to the output and to x (CHI_*).
 void hop_sys(const Launch &l, int prec, bool dag, int epi, int fi, int fo, int fx, int par, int amode, int mask,

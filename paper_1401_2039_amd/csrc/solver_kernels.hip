@@ -3,24 +3,14 @@
 // and true-residual kernels.  Every kernel takes the system table and the work
 // table; see solver_dev.h.
 #include "qiral_int.h"
-#include "solver_dev.h"
+#include "solver_steps.h"
 #include "solver_kernels.h"
 
 namespace qiral {
 
-__device__ __forceinline__ double coef(int amode, double k) {
-  return amode == A_ONE ? 1.0 : amode == A_KAPPA ? k : amode == A_MKAPPA2 ? -k * k : -k;
-}
-
-template <int S> __device__ __forceinline__ const void *links_of(const SysDesc &d) {
-  return S == S_F64 ? d.g64 : d.glo;
-}
-
 // out = C_o (a H in) (EPI 0) or out = C_o (C_x x + a H in) (EPI 1), parity
 // `par` out, for the (up to NR) systems of a grouped work item (they share the
-// lattice, so each link is loaded once for all of them).  C_o and C_x are the
-// twisted-mass site factors chio and chix (CHI_*).
-// red: 0 none; 1 ||out||^2; 2 (rt | out); 3 (out | x) and ||out||^2; 4 (z | out).
+// lattice, so each link is loaded once for all of them); see hop_site.
 // T waves per item (see hop_wave); padded lanes compute on site 0 and store
 // nothing.  Every wave reaches wave_combine's barrier.
 template <int S, int L, bool DAG, int EPI, int T, int NR, bool NT>
@@ -58,32 +48,7 @@ __global__ __launch_bounds__(WG, HOP_MIN_WAVES(S, T, NR)) void k_hop_sys(const S
     if (!act[r]) continue;
     const SysDesc &d = sdesc[it.sys + r];
     double v[NV] = {0.0, 0.0, 0.0};
-    if (site_ok && it.grp == 0) {
-      if (EPI == 0) {
-#pragma unroll
-        for (int k = 0; k < 12; ++k) acc[r][k] = cscale(a, acc[r][k]);
-        apply_chi(acc[r], chio, d0.tmu);
-      } else {
-        cpx<R> xv[12];
-        SpinorIO<S>::load(d.f[fx], it.s, npad, xv);
-        cpx<R> ax[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) ax[k] = xv[k];
-        apply_chi(ax, chix, d0.tmu);
-#pragma unroll
-        for (int k = 0; k < 12; ++k) acc[r][k] = cadd(ax[k], cscale(a, acc[r][k]));
-        apply_chi(acc[r], chio, d0.tmu);
-        if (red == 3) { dot12(acc[r], xv, v[0], v[1]); v[2] = norm12(acc[r]); }
-      }
-      if (ont) SpinorIO<S>::template store_fast<true>(d.f[fout], it.s, npad, acc[r]);
-      else SpinorIO<S>::template store_fast<false>(d.f[fout], it.s, npad, acc[r]);
-      if (red == 1) v[0] = norm12(acc[r]);
-      if (red == 2 || red == 4) {
-        cpx<R> rt[12];
-        SpinorIO<S>::load(d.f[red == 2 ? F_RT : F_Z], it.s, npad, rt);
-        dot12(rt, acc[r], v[0], v[1]);
-      }
-    }
+    if (site_ok && it.grp == 0) hop_site<S>(d, acc[r], EPI, a, fx, fout, it.s, red, chio, chix, ont, v);
     if (red) sys_partial(d, slot, it, v);
   }
 }
@@ -122,7 +87,6 @@ __global__ __launch_bounds__(WG, 2) void k_hop_sum(const SysDesc *__restrict__ s
 template <int SO, bool HASLO, bool BICG>
 __global__ __launch_bounds__(WG, 2) void k_hop_upd(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
                                                 int nwork) {
-  using RO = typename SpinorIO<SO>::R;
   __shared__ Lds64::V lds[Lds64::VECS];
   const Item it = fetch_item<T64>(work, nwork);
   const SysDesc &d = sdesc[it.sys];
@@ -136,35 +100,7 @@ __global__ __launch_bounds__(WG, 2) void k_hop_upd(const SysDesc *__restrict__ s
   FieldLd<S_F64, 1> ld{{d.f[F_T64]}, d.npad};
   hop_wave<L_F64R18, false, T64, false>(d.g, d.g64, ld, site_ok ? it.s : 0, 1, it.grp, acc1);
   wave_combine<T64, 1>(acc1, it.slot, it.grp, lds);
-  cpx<double> *acc = acc1[0];
-  if (site_ok && it.grp == 0) {
-    cpx<double> y[12], b[12];
-    SumLd yl{d.f[F_XH], HASLO ? d.f[F_X] : nullptr, d.npad};
-    yl(0, it.s, y);
-    if (HASLO) {
-      SpinorIO<S_F64>::store(d.f[F_XH], it.s, d.npad, y);
-      cpx<float> z[12];
-#pragma unroll
-      for (int k = 0; k < 12; ++k) z[k] = cmake(0.f, 0.f);
-      SpinorIO<S_F32>::store(d.f[F_X], it.s, d.npad, z);
-    }
-    SpinorIO<S_F64>::load(d.f[F_BH], it.s, d.npad, b);
-    apply_chi(y, CHI_A, d.tmu);
-    const double k2 = d.kappa * d.kappa;
-#pragma unroll
-    for (int k = 0; k < 12; ++k) acc[k] = cadd(csub(b[k], y[k]), cscale(k2, acc[k]));
-    v[0] = norm12(acc);
-    cpx<RO> r[12];
-    cvt12(acc, r);
-    SpinorIO<SO>::store(d.f[F_R], it.s, d.npad, r);
-    if (BICG && d.st->iter > 0) {
-      cpx<RO> rt[12];
-      SpinorIO<SO>::load(d.f[F_RT], it.s, d.npad, rt);
-      cpx<double> rtd[12];
-      cvt12(rt, rtd);
-      dot12(rtd, acc, v[1], v[2]);
-    }
-  }
+  if (site_ok && it.grp == 0) upd_site<SO, HASLO, BICG>(d, d.st, acc1[0], it.s, v);
   sys_partial(d, SL_UPD, it, v);
 }
 
@@ -174,7 +110,7 @@ __global__ __launch_bounds__(WG, 2) void k_hop_res(const SysDesc *__restrict__ s
   __shared__ Lds64::V lds[Lds64::VECS];
   const Item it = fetch_item<T64>(work, nwork);
   const SysDesc &d = sdesc[it.sys];
-  const int fin_id = par ? F_XE : F_XH, fb = par ? F_BO : F_BE, fx = par ? F_XH : F_XE;
+  const int fin_id = par ? F_XE : F_XH;
   const bool site_ok = it.active && it.s < d.g.vh;
   double v[NV] = {0.0, 0.0, 0.0};
   cpx<double> acc1[1][12];
@@ -183,16 +119,7 @@ __global__ __launch_bounds__(WG, 2) void k_hop_res(const SysDesc *__restrict__ s
   else zero_acc<1>(acc1);
   wave_combine<T64, 1>(acc1, it.slot, it.grp, lds);
   if (!it.active) return;
-  cpx<double> *acc = acc1[0];
-  if (site_ok && it.grp == 0) {
-    cpx<double> x[12], b[12];
-    SpinorIO<S_F64>::load(d.f[fx], it.s, d.npad, x);
-    SpinorIO<S_F64>::load(d.f[fb], it.s, d.npad, b);
-    apply_chi(x, CHI_A, d.tmu);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) acc[k] = cadd(csub(b[k], x[k]), cscale(d.kappa, acc[k]));
-    v[0] = norm12(acc);
-  }
+  if (site_ok && it.grp == 0) res_site(d, acc1[0], par, it.s, v);
   sys_partial(d, par ? SL_RES_O : SL_RES_E, it, v);
 }
 
@@ -237,270 +164,48 @@ __global__ __launch_bounds__(RED_WG) void k_reduce(const SysDesc *__restrict__ s
   if (tid < NW8) ((unsigned long long *)d.st)[tid] = ((const unsigned long long *)&sst)[tid];
 }
 
-// ||b||^2 over both parities.
-__global__ __launch_bounds__(WG) void k_bnorm(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
-                                              int nwork) {
-  const Item it = fetch_item<1>(work, nwork);
-  if (!it.active) return;
-  const SysDesc &d = sdesc[it.sys];
-  double v[NV] = {0.0, 0.0, 0.0};
-  if (it.s < d.g.vh) {
-    cpx<double> a[12];
-    SpinorIO<S_F64>::load(d.f[F_BE], it.s, d.npad, a);
-    v[0] = norm12(a);
-    SpinorIO<S_F64>::load(d.f[F_BO], it.s, d.npad, a);
-    v[0] += norm12(a);
+// The vector steps (solver_steps.h), one wave per 64-site block of a system
+// whose status matches: SUM names the reduction slot of the step's sums, -1 for
+// none.
+#define QVECTOR_KERNEL(NAME, TEMPLATE, MASK, SUM, CALL)                                                              \
+  TEMPLATE __global__ __launch_bounds__(WG) void NAME(const SysDesc *__restrict__ sdesc,                             \
+                                                      const uint32_t *__restrict__ work, int nwork) {                \
+    const Item it = fetch_item<1>(work, nwork);                                                                      \
+    if (!it.active) return;                                                                                          \
+    const SysDesc &d = sdesc[it.sys];                                                                                \
+    if ((MASK) != ST_ANY && !(d.st->status & (MASK))) return;                                                        \
+    double v[NV] = {0.0, 0.0, 0.0};                                                                                  \
+    const int s = it.s;                                                                                              \
+    if (s < d.g.vh) CALL;                                                                                            \
+    if ((SUM) >= 0) sys_partial(d, SUM, it, v);                                                                      \
   }
-  sys_partial(d, SL_B, it, v);
-}
-
-// CGNR: X += alpha P; R -= alpha AP; ||R||^2.  A plain (FP64) solve leaves X
-// to k_cg2, which reads P anyway: X += alpha P there, before P changes, is the
-// same arithmetic one pass over the vectors cheaper; k_cg_xfin applies the last
-// one when the solve stops here.
-template <int S, int XS, int V>
-__global__ __launch_bounds__(WG) void k_cg1(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
-                                            int nwork) {
-  using R = typename SpinorIO<S>::R;
-  using RX = typename SpinorIO<XS>::R;
-  constexpr bool xhere = S != S_F64;
-  const Item it = fetch_item<1>(work, nwork);
-  if (!it.active) return;
-  const SysDesc &d = sdesc[it.sys];
-  if (!(d.st->status & ST_RUN)) return;
-  double v[NV] = {0.0, 0.0, 0.0};
-  if (it.s < d.g.vh) {
-    const double al = d.st->alpha;
-    cpx<R> r[12], ap[12];
-    if (xhere) {
-      cpx<R> p[12];
-      cpx<RX> x[12];
-      SpinorIO<S>::template load<(V > 1)>(d.f[F_P], it.s, d.npad, p);
-      SpinorIO<XS>::template load<(V > 0)>(d.f[F_X], it.s, d.npad, x);
-#pragma unroll
-      for (int k = 0; k < 12; ++k) x[k] = cadd(x[k], cscale((RX)al, cmake((RX)p[k].re, (RX)p[k].im)));
-      SpinorIO<XS>::template store<(V > 0)>(d.f[F_X], it.s, d.npad, x);
-    }
-    SpinorIO<S>::template load<(V > 1)>(d.f[F_R], it.s, d.npad, r);
-    SpinorIO<S>::template load<(V > 0)>(d.f[F_AP], it.s, d.npad, ap);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) r[k] = csub(r[k], cscale((R)al, ap[k]));
-    SpinorIO<S>::template store<(V > 1)>(d.f[F_R], it.s, d.npad, r);
-    v[0] = norm12(r);
-  }
-  sys_partial(d, SL_R, it, v);
-}
-
-// The x += alpha p that a plain CGNR solve stopped before (status done after
-// k_cg1, flag set by the residual check).
-__global__ __launch_bounds__(WG) void k_cg_xfin(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
-                                                int nwork) {
-  const Item it = fetch_item<1>(work, nwork);
-  if (!it.active) return;
-  const SysDesc &d = sdesc[it.sys];
-  if (!(d.st->status & ST_DONE) || !d.st->xpend || it.s >= d.g.vh) return;
-  const double al = d.st->alpha;
-  cpx<double> p[12], x[12];
-  SpinorIO<S_F64>::load(d.f[F_P], it.s, d.npad, p);
-  SpinorIO<S_F64>::load(d.f[F_X], it.s, d.npad, x);
-#pragma unroll
-  for (int k = 0; k < 12; ++k) x[k] = cadd(x[k], cscale(al, cmake(p[k].re, p[k].im)));
-  SpinorIO<S_F64>::store(d.f[F_X], it.s, d.npad, x);
-}
-
-// Conjugate residual on S^dagger S: X += alpha P; R -= alpha U (U = S P);
-// Z -= alpha Q (Q = S^dagger S P); reduces ||R||^2 (the Schur residual).
-template <int S>
-__global__ __launch_bounds__(WG) void k_cr1(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
-                                            int nwork) {
-  using R = typename SpinorIO<S>::R;
-  const Item it = fetch_item<1>(work, nwork);
-  if (!it.active) return;
-  const SysDesc &d = sdesc[it.sys];
-  if (!(d.st->status & ST_RUN)) return;
-  double v[NV] = {0.0, 0.0, 0.0};
-  if (it.s < d.g.vh) {
-    const R al = (R)d.st->alpha;
-    cpx<R> p[12], x[12], a[12], b[12];
-    SpinorIO<S>::load(d.f[F_P], it.s, d.npad, p);
-    SpinorIO<S>::load(d.f[F_X], it.s, d.npad, x);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) x[k] = cadd(x[k], cscale(al, p[k]));
-    SpinorIO<S>::store(d.f[F_X], it.s, d.npad, x);
-    SpinorIO<S>::load(d.f[F_R], it.s, d.npad, a);
-    SpinorIO<S>::load(d.f[F_T], it.s, d.npad, b);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) a[k] = csub(a[k], cscale(al, b[k]));
-    SpinorIO<S>::store(d.f[F_R], it.s, d.npad, a);
-    v[0] = norm12(a);
-    SpinorIO<S>::load(d.f[F_Z], it.s, d.npad, a);
-    SpinorIO<S>::load(d.f[F_AP], it.s, d.npad, b);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) a[k] = csub(a[k], cscale(al, b[k]));
-    SpinorIO<S>::store(d.f[F_Z], it.s, d.npad, a);
-  }
-  sys_partial(d, SL_R, it, v);
-}
-
-// Conjugate residual: P = Z + beta P; Q = W + beta Q; U = V + beta U (INIT:
-// beta = 0, old values not read); reduces ||Q||^2.
-template <int S, bool INIT>
-__global__ __launch_bounds__(WG) void k_cr2(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
-                                            int nwork) {
-  using R = typename SpinorIO<S>::R;
-  const Item it = fetch_item<1>(work, nwork);
-  if (!it.active) return;
-  const SysDesc &d = sdesc[it.sys];
-  if (!(d.st->status & ST_RUN)) return;
-  double v[NV] = {0.0, 0.0, 0.0};
-  if (it.s < d.g.vh) {
-    const R be = (R)d.st->beta;
-    const int src[3] = {F_Z, F_W, F_RT}, dst[3] = {F_P, F_AP, F_T};
-#pragma unroll
-    for (int f = 0; f < 3; ++f) {
-      cpx<R> a[12];
-      SpinorIO<S>::load(d.f[src[f]], it.s, d.npad, a);
-      if (!INIT) {
-        cpx<R> b[12];
-        SpinorIO<S>::load(d.f[dst[f]], it.s, d.npad, b);
-#pragma unroll
-        for (int k = 0; k < 12; ++k) a[k] = cadd(a[k], cscale(be, b[k]));
-      }
-      SpinorIO<S>::store(d.f[dst[f]], it.s, d.npad, a);
-      if (f == 1) v[0] = norm12(a);
-    }
-  }
-  sys_partial(d, SL_AP, it, v);
-}
-
-// CGNR: P = Z + beta P; with XUPD (plain solves, in the iterations) first
-// X += alpha P with the old P (the update k_cg1 left).
-template <int S, bool XUPD, int V>
-__global__ __launch_bounds__(WG) void k_cg2(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
-                                            int nwork) {
-  using R = typename SpinorIO<S>::R;
-  const Item it = fetch_item<1>(work, nwork);
-  if (!it.active) return;
-  const SysDesc &d = sdesc[it.sys];
-  if (!(d.st->status & ST_RUN)) return;
-  if (it.s >= d.g.vh) return;
-  const R be = (R)d.st->beta;
-  cpx<R> p[12], z[12];
-  SpinorIO<S>::template load<(V > 1)>(d.f[F_P], it.s, d.npad, p);
-  if (XUPD) {
-    const double al = d.st->alpha;
-    cpx<double> x[12];
-    SpinorIO<S_F64>::load<(V > 0)>(d.f[F_X], it.s, d.npad, x);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) x[k] = cadd(x[k], cscale(al, cmake((double)p[k].re, (double)p[k].im)));
-    SpinorIO<S_F64>::store<(V > 0)>(d.f[F_X], it.s, d.npad, x);
-  }
-  SpinorIO<S>::template load<(V > 0)>(d.f[F_Z], it.s, d.npad, z);
-#pragma unroll
-  for (int k = 0; k < 12; ++k) p[k] = cadd(z[k], cscale(be, p[k]));
-  SpinorIO<S>::template store<(V > 1)>(d.f[F_P], it.s, d.npad, p);
-}
-
-// BiCGStab: P = R + beta (P - omega V)    (V lives in F_AP)
-template <int S, int V>
-__global__ __launch_bounds__(WG) void k_bi_p(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
-                                             int nwork) {
-  using R = typename SpinorIO<S>::R;
-  const Item it = fetch_item<1>(work, nwork);
-  if (!it.active) return;
-  const SysDesc &d = sdesc[it.sys];
-  if (!(d.st->status & ST_RUN)) return;
-  if (it.s >= d.g.vh) return;
-  const cpx<R> be = cmake((R)d.st->be_re, (R)d.st->be_im), om = cmake((R)d.st->om_re, (R)d.st->om_im);
-  cpx<R> p[12], r[12], vv[12];
-  SpinorIO<S>::template load<(V > 1)>(d.f[F_P], it.s, d.npad, p);
-  SpinorIO<S>::template load<(V > 1)>(d.f[F_R], it.s, d.npad, r);
-  SpinorIO<S>::template load<(V > 0)>(d.f[F_AP], it.s, d.npad, vv);
-#pragma unroll
-  for (int k = 0; k < 12; ++k) p[k] = cadd(r[k], cmul(be, csub(p[k], cmul(om, vv[k]))));
-  SpinorIO<S>::template store<(V > 1)>(d.f[F_P], it.s, d.npad, p);
-}
-
-// BiCGStab: S = R - alpha V    (S lives in F_Z)
-template <int S, int V>
-__global__ __launch_bounds__(WG) void k_bi_s(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
-                                             int nwork) {
-  using R = typename SpinorIO<S>::R;
-  const Item it = fetch_item<1>(work, nwork);
-  if (!it.active) return;
-  const SysDesc &d = sdesc[it.sys];
-  if (!(d.st->status & ST_RUN)) return;
-  if (it.s >= d.g.vh) return;
-  const cpx<R> al = cmake((R)d.st->al_re, (R)d.st->al_im);
-  cpx<R> r[12], vv[12];
-  SpinorIO<S>::template load<(V > 0)>(d.f[F_R], it.s, d.npad, r);
-  SpinorIO<S>::template load<(V > 1)>(d.f[F_AP], it.s, d.npad, vv);
-#pragma unroll
-  for (int k = 0; k < 12; ++k) r[k] = csub(r[k], cmul(al, vv[k]));
-  SpinorIO<S>::template store<(V > 1)>(d.f[F_Z], it.s, d.npad, r);
-}
-
-// BiCGStab: X += alpha P + omega S; R = S - omega T; reduces (rt | R) and ||R||^2
-template <int S, int XS, int V>
-__global__ __launch_bounds__(WG) void k_bi_xr(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
-                                              int nwork) {
-  using R = typename SpinorIO<S>::R;
-  using RX = typename SpinorIO<XS>::R;
-  const Item it = fetch_item<1>(work, nwork);
-  if (!it.active) return;
-  const SysDesc &d = sdesc[it.sys];
-  if (!(d.st->status & ST_RUN)) return;
-  double v[NV] = {0.0, 0.0, 0.0};
-  if (it.s < d.g.vh) {
-    const cpx<RX> al = cmake((RX)d.st->al_re, (RX)d.st->al_im), om = cmake((RX)d.st->om_re, (RX)d.st->om_im);
-    cpx<R> p[12], s[12], t[12], rt[12];
-    cpx<RX> x[12];
-    SpinorIO<S>::template load<(V > 1)>(d.f[F_P], it.s, d.npad, p);
-    SpinorIO<S>::template load<(V > 0)>(d.f[F_Z], it.s, d.npad, s);
-    SpinorIO<XS>::template load<(V > 0)>(d.f[F_X], it.s, d.npad, x);
-#pragma unroll
-    for (int k = 0; k < 12; ++k)
-      x[k] = cadd(x[k], cadd(cmul(al, cmake((RX)p[k].re, (RX)p[k].im)), cmul(om, cmake((RX)s[k].re, (RX)s[k].im))));
-    SpinorIO<XS>::template store<(V > 0)>(d.f[F_X], it.s, d.npad, x);
-    SpinorIO<S>::template load<(V > 0)>(d.f[F_T], it.s, d.npad, t);
-    const cpx<R> omr = cmake((R)d.st->om_re, (R)d.st->om_im);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) s[k] = csub(s[k], cmul(omr, t[k]));
-    SpinorIO<S>::template store<(V > 1)>(d.f[F_R], it.s, d.npad, s);
-    SpinorIO<S>::template load<(V > 1)>(d.f[F_RT], it.s, d.npad, rt);
-    dot12(rt, s, v[0], v[1]);
-    v[2] = norm12(s);
-  }
-  sys_partial(d, SL_BI3, it, v);
-}
+#define QT(...) template <__VA_ARGS__>
+QVECTOR_KERNEL(k_bnorm, , ST_ANY, SL_B, bnorm_site(d, s, v))
+QVECTOR_KERNEL(k_cg1, QT(int S, int XS, int V), ST_RUN, SL_R, (cg1_site<S, XS, V>(d, d.st, s, v)))
+QVECTOR_KERNEL(k_cg2, QT(int S, bool XUPD, int V), ST_RUN, -1, (cg2_site<S, XUPD, V>(d, d.st, s)))
+QVECTOR_KERNEL(k_cg_xfin, , ST_DONE, -1, if (d.st->xpend) xfin_site(d, d.st, s))
+QVECTOR_KERNEL(k_cr1, QT(int S), ST_RUN, SL_R, cr1_site<S>(d, d.st, s, v))
+QVECTOR_KERNEL(k_cr2, QT(int S, bool INIT), ST_RUN, SL_AP, (cr2_site<S, INIT>(d, d.st, s, v)))
+QVECTOR_KERNEL(k_bi_p, QT(int S, int V), ST_RUN, -1, (bi_p_site<S, V>(d, d.st, s)))
+QVECTOR_KERNEL(k_bi_s, QT(int S, int V), ST_RUN, -1, (bi_s_site<S, V>(d, d.st, s)))
+QVECTOR_KERNEL(k_bi_xr, QT(int S, int XS, int V), ST_RUN, SL_BI3, (bi_xr_site<S, XS, V>(d, d.st, s, v)))
+#undef QT
+#undef QVECTOR_KERNEL
 
 // copy a half-field of the iterate precision: dst = src
 template <int S>
 __global__ __launch_bounds__(WG) void k_copy(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
                                              int nwork, int fsrc, int fdst, int mask, int chi) {
-  using R = typename SpinorIO<S>::R;
   const Item it = fetch_item<1>(work, nwork);
   if (!it.active) return;
   const SysDesc &d = sdesc[it.sys];
-  if (!(d.st->status & mask)) return;
-  if (it.s >= d.g.vh) return;
-  cpx<R> a[12];
-  SpinorIO<S>::load(d.f[fsrc], it.s, d.npad, a);
-  apply_chi(a, chi, d.tmu);
-  SpinorIO<S>::store(d.f[fdst], it.s, d.npad, a);
+  if (!(d.st->status & mask) || it.s >= d.g.vh) return;
+  copy_site<S>(d, fsrc, fdst, chi, it.s);
 }
 
-// BiCGStab start: rho = (r~ | r) = ||r||^2 with r~ = r, alpha = omega = 1, beta = 0.
 __global__ void k_bi_init(const SysDesc *__restrict__ sdesc, int nsys) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nsys) return;
-  SysState *st = sdesc[i].st;
-  if (!(st->status & ST_RUN)) return;
-  st->rho_re = st->nr; st->rho_im = 0.0;
-  st->rho0_re = st->nr; st->rho0_im = 0.0;
-  st->al_re = 1.0; st->al_im = 0.0;
-  st->om_re = 1.0; st->om_im = 0.0;
-  st->be_re = 0.0; st->be_im = 0.0;
+  if (i < nsys && (sdesc[i].st->status & ST_RUN)) bi_start(sdesc[i].st);
 }
 
 // ---------------------------------------------------------------------------
