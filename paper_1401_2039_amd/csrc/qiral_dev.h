@@ -508,7 +508,8 @@ __device__ __forceinline__ int nbr(const Geo &g, const SiteC &c, int mu, bool fw
 
 // Field loaders: NF packed fields (right-hand sides) read at one site and
 // converted to the compute type R.
-template <int S, int N> struct FieldLd {
+// AHEAD: issue the loads of both directions of a dimension together whatever S.
+template <int S, int N, bool AHEAD = false> struct FieldLd {
   using R = typename SpinorIO<S>::R;
   static constexpr int NF = N;
   const void *base[N];
@@ -525,7 +526,7 @@ template <int S, int N> struct FieldLd {
   // Measured: 6% off the latency-bound 16^3x32 hop; the F16S hop, bound by its
   // vector work, lost occupancy and ran up to 11% slower, and the FP64 hop has
   // no registers to spare.
-  static constexpr bool PAIR = N == 1 && S == S_F32;
+  static constexpr bool PAIR = N == 1 && (S == S_F32 || AHEAD);
   using Raw = typename SpinorIO<S>::Raw;
   __device__ __forceinline__ void fetch(int r, int s, Raw &w) const { SpinorIO<S>::fetch(base[r], s, npad, w); }
   __device__ __forceinline__ void decode(const Raw &w, cpx<R> v[12], R &sc) const {

@@ -30,6 +30,7 @@
 #include "qiral_int.h"
 #include "solver_steps.h"
 #include "solver_kernels.h"
+#include "solo.h"
 
 namespace qiral {
 
@@ -145,6 +146,14 @@ std::vector<const qiral_lattice *> lattices_of(const std::vector<SysIn> &sys) {
   return l;
 }
 
+// Whether small lattices take the one-work-group solver: not when a launch shape
+// of the grouped hops is asked for (QIRAL_HOP_*).
+bool solo_wanted() {
+  for (const char *e : {"QIRAL_HOP_SPLIT", "QIRAL_HOP_NR", "QIRAL_HOP_ORDER", "QIRAL_HOP_TILE", "QIRAL_HOP_NT"})
+    if (getenv(e)) return false;
+  return true;
+}
+
 qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, const qiral_solve_params *prm,
                        void *ws_base, size_t ws_bytes, qiral_solve_info *info, hipStream_t s) {
   auto t0 = std::chrono::steady_clock::now();
@@ -176,6 +185,8 @@ qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, cons
     d.g64 = lat->g64;
     d.glo = links_for(lat, prec);
     d.npad = npad_of(lat->geo);
+    d.b = sys[i].b;
+    d.x = sys[i].x;
     d.st = (SysState *)(ws + lay.off_state) + i;
     d.part = (double *)(ws + lay.off_part) + lay.part_off[i];
     char *p = ws + lay.off_sys[i];
@@ -187,6 +198,87 @@ qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, cons
     d.f[F_BE] = p; d.f[F_BO] = p + half_bytes(lat->geo, QIRAL_F64); p += 2 * sz[i].hb64;
     d.f[F_XE] = p; d.f[F_XH] = p + half_bytes(lat->geo, QIRAL_F64); p += 2 * sz[i].hb64;
     if (!mixed) d.f[F_X] = d.f[F_XH];
+  }
+  std::vector<SysState> hst(nsys);
+  for (int i = 0; i < nsys; ++i) {
+    SysState &x = hst[i];
+    memset(&x, 0, sizeof(x));
+    x.tol2 = prm->tol * prm->tol;
+    x.delta2 = prm->delta * prm->delta;
+    x.maxiter = prm->maxiter;
+    x.mixed = mixed;
+    x.solver = bicg ? SOLVER_BICG : cr ? SOLVER_CR : SOLVER_CG;
+    x.status = ST_UPDATE;
+  }
+  bool twisted = false, small = !prm->use_graph && solo_wanted();
+  for (int i = 0; i < nsys; ++i) {
+    twisted = twisted || sys[i].lat->mu != 0.0;
+    small = small && sys[i].lat->geo.nb <= solo_line(nsys, !mixed, bicg);
+  }
+  std::vector<double> true_rel(nsys, 0.0);
+  // The true residuals of the states in hst, and which systems go round again:
+  // true if any does (its status is then an update's, as at the start).
+  int restarts = 0;
+  auto again = [&]() {
+    bool any = false;
+    for (int i = 0; i < nsys; ++i) {
+      const SysState &x = hst[i];
+      const double r2 = x.res[SL_RES_E][0] + x.res[SL_RES_O][0];
+      true_rel[i] = x.bnorm2 > 0 ? std::sqrt(r2 / x.bnorm2) : std::sqrt(r2);
+      if (!x.nonfinite && true_rel[i] > prm->tol && x.iter < prm->maxiter) any = true;
+    }
+    if (!any || restarts >= 2) return false;
+    ++restarts;
+    for (int i = 0; i < nsys; ++i) {
+      hst[i].xpend = 0;   // its x += alpha p has been applied
+      if (!hst[i].nonfinite && true_rel[i] > prm->tol && hst[i].iter < prm->maxiter) {
+        hst[i].status = ST_UPDATE;
+        hst[i].final_update = 0;
+      }
+    }
+    return true;
+  };
+  auto finish = [&]() {
+    const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+    qiral_status result = QIRAL_OK;
+    for (int i = 0; i < nsys; ++i) {
+      const SysState &x = hst[i];
+      if (info) {
+        info[i].iterations = x.iter;
+        info[i].reliable_updates = mixed ? x.nupdates - 1 - restarts : 0;
+        if (info[i].reliable_updates < 0) info[i].reliable_updates = 0;
+        info[i].true_rel_resid = true_rel[i];
+        info[i].converged = x.nonfinite ? 0 : (true_rel[i] <= prm->tol);
+        info[i].fell_back = 0;
+        info[i].seconds = secs;
+        info[i].hop_applications = x.hops + 4 + (long long)restarts * 2;
+      }
+      if (x.nonfinite) result = QIRAL_ERR_NONFINITE;
+      else if (true_rel[i] > prm->tol && result == QIRAL_OK) result = QIRAL_ERR_NOT_CONVERGED;
+    }
+    if (result == QIRAL_ERR_NONFINITE) set_error("a NaN or Inf appeared in a reduction");
+    else if (result == QIRAL_ERR_NOT_CONVERGED) set_error("tolerance not reached within maxiter");
+    return result;
+  };
+  QIRAL_HIP(hipMemcpyAsync(ws + lay.off_desc, desc.data(), sizeof(SysDesc) * nsys, hipMemcpyHostToDevice, s));
+  if (small) {
+    // one work-group a system, from the source to the solution (solo.hip)
+    int mode = SOLO_NEW;
+    QIRAL_HIP(hipMemcpyAsync(ws + lay.off_state, hst.data(), sizeof(SysState) * nsys, hipMemcpyHostToDevice, s));
+    while (true) {
+      QIRAL_HIP(solo_launch((const SysDesc *)(ws + lay.off_desc), nsys, prm->solver, prec, twisted,
+                            prm->x0_is_guess != 0, mode, s));
+      QIRAL_HIP(hipMemcpyAsync(hst.data(), ws + lay.off_state, sizeof(SysState) * nsys, hipMemcpyDeviceToHost, s));
+      QIRAL_HIP(hipStreamSynchronize(s));
+      bool done = true;
+      for (int i = 0; i < nsys; ++i) done = done && (hst[i].status & ST_DONE);
+      mode = SOLO_MORE;
+      if (!done) continue;   // at most maxiter iterations in all: the device stops there
+      if (!again()) break;
+      mode = SOLO_RESTART;
+      QIRAL_HIP(hipMemcpyAsync(ws + lay.off_state, hst.data(), sizeof(SysState) * nsys, hipMemcpyHostToDevice, s));
+    }
+    return finish();
   }
   // ---- work tables.  Plain: one item per (system, block); right-hand sides of
   // one lattice interleave per block (they share links).  Grouped (the
@@ -224,18 +316,6 @@ qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, cons
     }
     work_hop = work;
   }
-  std::vector<SysState> hst(nsys);
-  for (int i = 0; i < nsys; ++i) {
-    SysState &x = hst[i];
-    memset(&x, 0, sizeof(x));
-    x.tol2 = prm->tol * prm->tol;
-    x.delta2 = prm->delta * prm->delta;
-    x.maxiter = prm->maxiter;
-    x.mixed = mixed;
-    x.solver = bicg ? SOLVER_BICG : cr ? SOLVER_CR : SOLVER_CG;
-    x.status = ST_UPDATE;
-  }
-  QIRAL_HIP(hipMemcpyAsync(ws + lay.off_desc, desc.data(), sizeof(SysDesc) * nsys, hipMemcpyHostToDevice, s));
   QIRAL_HIP(hipMemcpyAsync(ws + lay.off_work, work.data(), sizeof(uint32_t) * nwork, hipMemcpyHostToDevice, s));
   QIRAL_HIP(hipMemcpyAsync(ws + lay.off_work + sizeof(uint32_t) * nwork, work_hop.data(),
                            sizeof(uint32_t) * work_hop.size(), hipMemcpyHostToDevice, s));
@@ -276,8 +356,6 @@ qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, cons
   }
   bnorm(L);
   // b_hat = b_o + kappa H_oe A^-1 b_e (A = 1 without twisted mass)
-  bool twisted = false;
-  for (int i = 0; i < nsys; ++i) twisted = twisted || sys[i].lat->mu != 0.0;
   if (twisted) {
     copy_field(L, S_F64, F_BE, F_T64, ST_ANY, CHI_AINV);
     hop_sys(L, S_F64, false, 1, F_T64, F_BH, F_BO, 1, A_KAPPA, ST_ANY, 0, 0, FIN_NONE);
@@ -389,9 +467,6 @@ qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, cons
     return QIRAL_OK;
   };
 
-  int restarts = 0;
-  std::vector<double> true_rel(nsys, 0.0);
-  qiral_status result = QIRAL_OK;
   while (true) {
     start_krylov();
     QIRAL_HIP(hipGetLastError());
@@ -452,22 +527,7 @@ qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, cons
     QIRAL_HIP(hipGetLastError());
     st = read_states();
     if (st != QIRAL_OK) { free_graph(); return st; }
-    bool again = false;
-    for (int i = 0; i < nsys; ++i) {
-      const SysState &x = hst[i];
-      const double r2 = x.res[SL_RES_E][0] + x.res[SL_RES_O][0];
-      true_rel[i] = x.bnorm2 > 0 ? std::sqrt(r2 / x.bnorm2) : std::sqrt(r2);
-      if (!x.nonfinite && true_rel[i] > prm->tol && x.iter < prm->maxiter) again = true;
-    }
-    if (!again || restarts >= 2) break;
-    ++restarts;
-    for (int i = 0; i < nsys; ++i) {
-      hst[i].xpend = 0;   // k_cg_xfin has applied it
-      if (!hst[i].nonfinite && true_rel[i] > prm->tol && hst[i].iter < prm->maxiter) {
-        hst[i].status = ST_UPDATE;
-        hst[i].final_update = 0;
-      }
-    }
+    if (!again()) break;
     QIRAL_HIP(hipMemcpyAsync(ws + lay.off_state, hst.data(), sizeof(SysState) * nsys, hipMemcpyHostToDevice, s));
   }
   free_graph();
@@ -477,25 +537,7 @@ qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, cons
   }
   QIRAL_HIP(hipGetLastError());
   QIRAL_HIP(hipStreamSynchronize(s));
-  const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-  for (int i = 0; i < nsys; ++i) {
-    const SysState &x = hst[i];
-    if (info) {
-      info[i].iterations = x.iter;
-      info[i].reliable_updates = mixed ? x.nupdates - 1 - restarts : 0;
-      if (info[i].reliable_updates < 0) info[i].reliable_updates = 0;
-      info[i].true_rel_resid = true_rel[i];
-      info[i].converged = x.nonfinite ? 0 : (true_rel[i] <= prm->tol);
-      info[i].fell_back = 0;
-      info[i].seconds = secs;
-      info[i].hop_applications = x.hops + 4 + (long long)restarts * 2;
-    }
-    if (x.nonfinite) result = QIRAL_ERR_NONFINITE;
-    else if (true_rel[i] > prm->tol && result == QIRAL_OK) result = QIRAL_ERR_NOT_CONVERGED;
-  }
-  if (result == QIRAL_ERR_NONFINITE) set_error("a NaN or Inf appeared in a reduction");
-  else if (result == QIRAL_ERR_NOT_CONVERGED) set_error("tolerance not reached within maxiter");
-  return result;
+  return finish();
 }
 
 qiral_status check_params(const qiral_solve_params *p) {

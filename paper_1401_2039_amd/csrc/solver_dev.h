@@ -60,6 +60,8 @@ struct SysDesc {
   void *f[NF];
   SysState *st;
   double *part;       // [NSLOT][NV][4 nb] per-wave partial sums
+  const double *b;    // canonical source and solution (read and written by the one-work-group solver)
+  double *x;
   size_t npad;
 };
 

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import latgen
-from oracle import ptc, storage, wilson as W
+from oracle import ptc, solvers as S, storage, wilson as W
 import paper_1401_2039_amd as q
 from gpu_util import say, dev, host
 
@@ -80,3 +80,52 @@ def test_network_and_gradient_tiles(dims, H):
     want = np.concatenate([(2 * G[0]).ravel(), (2 * G[1]).ravel()])
     assert abs(loss - L) < 1e-6 * L
     assert np.abs(g[0::2] + 1j * g[1::2] - want).max() < 1e-5 * np.abs(want).max()
+
+
+# One work-group solves a lattice of up to four 64-site blocks; a captured graph
+# always takes the grouped kernels.  Both take the same steps with the same sums:
+# equal bit for bit in FP64, and to the tolerance of the solves in the reduced
+# precisions (their hops may split the directions over other waves).  One, two,
+# three and four blocks, a partly filled last one, one and five systems (the line
+# lies one block higher for several), with and without a twisted mass.
+@pytest.mark.parametrize("dims,mu,nrhs", [((2, 2, 2, 2), 0.0, 1), ((4, 4, 4, 4), 0.35, 1), ((4, 4, 4, 6), 0.0, 1),
+                                          ((4, 4, 4, 8), 0.0, 5), ((6, 2, 4, 10), 0.35, 2)])
+@pytest.mark.parametrize("solver", [q.CGNR_EO, q.BICGSTAB_EO, q.CRNR_EO], ids=["cgnr", "bicgstab", "crnr"])
+def test_one_work_group_solves(dims, mu, nrhs, solver):
+    say("one work-group", dims, mu, nrhs, solver)
+    cfg = latgen.small_config(dims, seed=85, kind="expih", eps=0.4, nrhs=nrhs)
+    lat = q.Lattice(dims, 0.12, cfg["U"], mu=mu)
+    b, side = dev(cfg["b"]), torch.cuda.Stream()
+    for prec in (q.F64, q.F32, q.F16S)[:1 if solver == q.CRNR_EO else 3]:
+        kw = dict(solver=solver, inner_prec=prec, tol=1e-10)
+        x, st, info = lat.solve(b, **kw)
+        with torch.cuda.stream(side):
+            xg, sg, ig = lat.solve(b, use_graph=1, **kw)
+        side.synchronize()
+        x, xg = host(x), host(xg)
+        assert st == 0 and sg == 0
+        for r in range(nrhs):
+            assert S.true_rel_residual(cfg["U"], 0.12, mu, x[r], cfg["b"][r]) <= 1e-10
+        if prec == q.F64:
+            assert np.array_equal(x, xg)
+            assert [i["iterations"] for i in info] == [i["iterations"] for i in ig]
+            assert [i["hop_applications"] for i in info] == [i["hop_applications"] for i in ig]
+            assert [i["true_rel_resid"] for i in info] == [i["true_rel_resid"] for i in ig]
+
+
+def test_one_work_group_goes_on():
+    """More iterations than one launch takes (256), from a guess, and a stop at
+    maxiter: the grouped solver's iterate bit for bit."""
+    say("one work-group, 300 iterations")
+    cfg = latgen.small_config((4, 4, 4, 4), seed=86, kind="haar", nrhs=1)
+    lat = q.Lattice((4, 4, 4, 4), 0.12, cfg["U"])
+    b, side = dev(cfg["b"]), torch.cuda.Stream()
+    x0 = dev(0.1 * cfg["b"])
+    for n in (3, 300):
+        kw = dict(tol=1e-200, maxiter=n, x0_is_guess=1)
+        x, st, info = lat.solve(b, x_canon=x0.clone(), **kw)
+        with torch.cuda.stream(side):
+            xg, sg, ig = lat.solve(b, x_canon=x0.clone(), use_graph=1, **kw)
+        side.synchronize()
+        assert st == sg and info[0]["iterations"] == ig[0]["iterations"] == n
+        assert torch.equal(x, xg)
