@@ -802,13 +802,17 @@ __device__ __forceinline__ void wave_combine(cpx<R> acc[NF][12], int slot, int g
 // on the upper spins and its conjugate-sign partner on the lower ones.
 enum { CHI_ONE = 0, CHI_A = 1, CHI_ADAG = 2, CHI_AINV = 3, CHI_AINVDAG = 4 };
 
-template <class R> __device__ __forceinline__ void apply_chi(cpx<R> v[12], int mode, double t) {
-  if (mode == CHI_ONE || t == 0.0) return;
+// The factor on one component of spin `spin`.
+template <class R> __device__ __forceinline__ cpx<R> chi1(cpx<R> z, int spin, int mode, double t) {
+  if (mode == CHI_ONE || t == 0.0) return z;
   const double n = (mode == CHI_AINV || mode == CHI_AINVDAG) ? 1.0 / (1.0 + t * t) : 1.0;
   const double sg = (mode == CHI_A || mode == CHI_AINVDAG) ? 1.0 : -1.0;
-  const cpx<R> cu = cmake((R)n, (R)(n * sg * t)), cl = cmake((R)n, (R)(-n * sg * t));
+  return cmul(spin < 2 ? cmake((R)n, (R)(n * sg * t)) : cmake((R)n, (R)(-n * sg * t)), z);
+}
+template <class R> __device__ __forceinline__ void apply_chi(cpx<R> v[12], int mode, double t) {
+  if (mode == CHI_ONE || t == 0.0) return;
 #pragma unroll
-  for (int k = 0; k < 12; ++k) v[k] = cmul((k & 3) < 2 ? cu : cl, v[k]);
+  for (int k = 0; k < 12; ++k) v[k] = chi1(v[k], k & 3, mode, t);
 }
 
 template <int NF, class R> __device__ __forceinline__ void zero_acc(cpx<R> acc[NF][12]) {

@@ -278,10 +278,10 @@ __host__ __device__ inline uint32_t work_item(int sys0, int cnt, int sb) {
 }
 constexpr int MAX_BLOCKS = 1 << 22;   // 64-site blocks per parity a work item can address
 
+// The item of a wave in the wg-th work-group of the table.
 template <int T>
-__device__ __forceinline__ Item fetch_item(const uint32_t *work, int nwork) {
+__device__ __forceinline__ Item fetch_item_at(const uint32_t *work, int nwork, int wg) {
   Item it;
-  const int wg = xcd_remap(blockIdx.x, gridDim.x);
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // wave-uniform
   const int idx = wg * (4 / T) + w / T;
   it.sub = it.grp = w % T;
@@ -296,6 +296,10 @@ __device__ __forceinline__ Item fetch_item(const uint32_t *work, int nwork) {
   return it;
 }
 
+template <int T>
+__device__ __forceinline__ Item fetch_item(const uint32_t *work, int nwork) {
+  return fetch_item_at<T>(work, nwork, xcd_remap(blockIdx.x, gridDim.x));
+}
 inline int grid_for(int nwork, int T) { return (nwork * T + 3) / 4; }
 
 // Store a work item's partial sums: one per 64-site block (index sb), each of

@@ -58,54 +58,76 @@ __global__ __launch_bounds__(WG, HOP_MIN_WAVES(S, T, NR)) void k_hop_sys(const S
 constexpr int T64 = 4;
 using Lds64 = HopLds<T64, 1, double>;
 
-// T64 = A^-1 H_eo (XH + X): the hop of the current solution for the FP64 residual.
-template <bool HASLO>
-__global__ __launch_bounds__(WG, 2) void k_hop_sum(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
-                                                int nwork) {
-  __shared__ Lds64::V lds[Lds64::VECS];
-  const Item it = fetch_item<T64>(work, nwork);
-  const SysDesc &d = sdesc[it.sys];
-  const bool on = it.active && (d.st->status & ST_UPDATE);
-  // One work item per block, so `on` is the same in every wave of the block and
-  // a block with no update pending (most iterations) leaves before the barrier.
-  static_assert(WG / WAVE == T64, "k_hop_sum: one work item per block");
-  if (!on) return;
-  const bool site_ok = it.s < d.g.vh;
-  cpx<double> acc[1][12];
-  SumLd ld{d.f[F_XH], HASLO ? d.f[F_X] : nullptr, d.npad};
-  hop_wave<L_F64R18, false, T64, false>(d.g, d.g64, ld, site_ok ? it.s : 0, 0, it.grp, acc);
-  wave_combine<T64, 1>(acc, it.slot, it.grp, lds);
-  if (site_ok && it.grp == 0) {
-    apply_chi(acc[0], CHI_AINV, d.tmu);
-    SpinorIO<S_F64>::store(d.f[F_T64], it.s, d.npad, acc[0]);
+// The `chunk` consecutive items of an update kernel's work-group: calls
+// each(item) for those whose system has an update pending.  Most iterations have
+// none, and a work-group then only has to find that out: for 12 systems at
+// 24^3x48, 62208 work-groups of one item of k_hop_upd took 42 us to come and go,
+// 15552 of four take 15 (a system's items follow one another, so one look at its
+// state serves the chunk).
+template <class Each>
+__device__ __forceinline__ void update_items(const SysDesc *sdesc, const uint32_t *work, int nwork, int chunk,
+                                             Each each) {
+  static_assert(WG / WAVE == T64, "one work item at a time");
+  const int i0 = xcd_remap(blockIdx.x, gridDim.x) * chunk;
+  int sys = -1;
+  bool on = false;
+#pragma unroll 1
+  for (int i = i0; i < i0 + chunk && i < nwork; ++i) {
+    const Item it = fetch_item_at<T64>(work, nwork, i);
+    if (it.sys != sys) {
+      sys = it.sys;
+      on = sdesc[sys].st->status & ST_UPDATE;   // uniform
+    }
+    if (!on) continue;
+    each(it);
+    if (chunk > 1) __syncthreads();   // the next item overwrites the combine buffer
   }
 }
 
-// Reliable update on the odd sites: y = XH + X; XH = y; X = 0;
-// r_hat = BH - (A y - kappa^2 H_oe T64) in FP64; R = r_hat rounded to the iterate
-// precision; reduces ||r_hat||^2 (and (rt | r_hat) for BiCGStab).
-template <int SO, bool HASLO, bool BICG>
-__global__ __launch_bounds__(WG, 2) void k_hop_upd(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
-                                                int nwork) {
+// T64 = A^-1 H_eo (XH + X): the hop of the current solution for the FP64 residual.
+// Two waves per SIMD: held to three its sums come a colour at a time and it runs
+// 1006 instead of 870 us (12 systems at 24^3x48).
+template <bool HASLO>
+__global__ __launch_bounds__(WG, 2) void k_hop_sum(const SysDesc *__restrict__ sdesc,
+                                                   const uint32_t *__restrict__ work, int nwork, int chunk) {
   __shared__ Lds64::V lds[Lds64::VECS];
-  const Item it = fetch_item<T64>(work, nwork);
-  const SysDesc &d = sdesc[it.sys];
-  const bool on = it.active && (d.st->status & ST_UPDATE);
-  // block-uniform, as in k_hop_sum
-  static_assert(WG / WAVE == T64, "k_hop_upd: one work item per block");
-  if (!on) return;
-  const bool site_ok = it.s < d.g.vh;
-  double v[NV] = {0.0, 0.0, 0.0};
-  cpx<double> acc1[1][12];
-  FieldLd<S_F64, 1> ld{{d.f[F_T64]}, d.npad};
-  hop_wave<L_F64R18, false, T64, false>(d.g, d.g64, ld, site_ok ? it.s : 0, 1, it.grp, acc1);
-  wave_combine<T64, 1>(acc1, it.slot, it.grp, lds);
-  if (site_ok && it.grp == 0) upd_site<SO, HASLO, BICG>(d, d.st, acc1[0], it.s, v);
-  sys_partial(d, SL_UPD, it, v);
+  update_items(sdesc, work, nwork, chunk, [&](const Item &it) {
+    const SysDesc &d = sdesc[it.sys];
+    const bool site_ok = it.s < d.g.vh;
+    cpx<double> acc[1][12];
+    SumLd ld{d.f[F_XH], HASLO ? d.f[F_X] : nullptr, d.npad};
+    hop_wave<L_F64R18, false, T64, false>(d.g, d.g64, ld, site_ok ? it.s : 0, 0, it.grp, acc);
+    wave_combine<T64, 1>(acc, it.slot, it.grp, lds);
+    if (site_ok && it.grp == 0) {
+      apply_chi(acc[0], CHI_AINV, d.tmu);
+      SpinorIO<S_F64>::store(d.f[F_T64], it.s, d.npad, acc[0]);
+    }
+  });
+}
+
+// Reliable update on the odd sites (upd_site), with its sums.  Three waves per
+// SIMD, which the epilogue allows by going a colour at a time: 1200 -> 1110 us for
+// 12 systems at 24^3x48, k_hop_res 800 -> 715.  Items of two systems (links read
+// once for both) were tried for the three and gained nothing: 890 to 1370 us.
+template <int SO, bool HASLO, bool BICG>
+__global__ __launch_bounds__(WG, 3) void k_hop_upd(const SysDesc *__restrict__ sdesc,
+                                                   const uint32_t *__restrict__ work, int nwork, int chunk) {
+  __shared__ Lds64::V lds[Lds64::VECS];
+  update_items(sdesc, work, nwork, chunk, [&](const Item &it) {
+    const SysDesc &d = sdesc[it.sys];
+    const bool site_ok = it.s < d.g.vh;
+    double v[NV] = {0.0, 0.0, 0.0};
+    cpx<double> acc1[1][12];
+    FieldLd<S_F64, 1> ld{{d.f[F_T64]}, d.npad};
+    hop_wave<L_F64R18, false, T64, false>(d.g, d.g64, ld, site_ok ? it.s : 0, 1, it.grp, acc1);
+    wave_combine<T64, 1>(acc1, it.slot, it.grp, lds);
+    if (site_ok && it.grp == 0) upd_site<SO, HASLO, BICG>(d, d.st, acc1[0], it.s, v);
+    sys_partial(d, SL_UPD, it, v);
+  });
 }
 
 // ||b - D x||^2 on the sites of parity p: B_p - A X_p + kappa H X_{1-p}.
-__global__ __launch_bounds__(WG, 2) void k_hop_res(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
+__global__ __launch_bounds__(WG, 3) void k_hop_res(const SysDesc *__restrict__ sdesc, const uint32_t *__restrict__ work,
                                                 int nwork, int par) {
   __shared__ Lds64::V lds[Lds64::VECS];
   const Item it = fetch_item<T64>(work, nwork);
@@ -275,15 +297,24 @@ void hop_sys(const Launch &l, int prec, bool dag, int epi, int fi, int fo, int f
   if (red) reduce(l, slot, fin, mask);
 }
 
+// Items per work-group of k_hop_upd: four while there are many times more than
+// the card holds, one where each should have its own (8^4 in FP32 with four: 3%
+// slower).  k_hop_sum takes one: with two waves per SIMD the items of a chunk
+// wait for each other (870 -> 1000 us), as much as the idle launches save.
+static int upd_chunk(const Launch &l) { return l.nwork >= 8192 ? 4 : 1; }
+
 void hop_sum(const Launch &l, bool haslo) {
-  const dim3 g = grid_of(l.nwork, T64), b(WG);
-  if (haslo) hipLaunchKernelGGL((k_hop_sum<true>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
-  else hipLaunchKernelGGL((k_hop_sum<false>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
+  const int c = 1;
+  const dim3 g(l.nwork), b(WG);
+  if (haslo) hipLaunchKernelGGL((k_hop_sum<true>), g, b, 0, l.stream, l.desc, l.work, l.nwork, c);
+  else hipLaunchKernelGGL((k_hop_sum<false>), g, b, 0, l.stream, l.desc, l.work, l.nwork, c);
 }
 
 void hop_upd(const Launch &l, int prec, bool bicg) {
-  const dim3 g = grid_of(l.nwork, T64), b(WG);
-#define QU(SO, LO, BI) hipLaunchKernelGGL((k_hop_upd<SO, LO, BI>), g, b, 0, l.stream, l.desc, l.work, l.nwork)
+  const int c = upd_chunk(l);
+  const dim3 g((l.nwork + c - 1) / c), b(WG);
+#define QU(SO, LO, BI) \
+  hipLaunchKernelGGL((k_hop_upd<SO, LO, BI>), g, b, 0, l.stream, l.desc, l.work, l.nwork, c)
   if (prec == S_F64) { if (bicg) QU(S_F64, false, true); else QU(S_F64, false, false); }
   else if (prec == S_F32) { if (bicg) QU(S_F32, true, true); else QU(S_F32, true, false); }
   else { if (bicg) QU(S_F16S, true, true); else QU(S_F16S, true, false); }

@@ -51,6 +51,9 @@ __device__ __forceinline__ void hop_site(const SysDesc &d, cpx<typename SpinorIO
   }
 }
 
+// Unit 0 of site s in a packed F64 half-field.
+__device__ __forceinline__ size_t f64_at(int s) { return (size_t)(s >> 6) * (12 * WAVE) + (s & 63); }
+
 // The reliable update at an odd site, acc = (H_oe T64)(s): y = XH + X; XH = y;
 // X = 0; r_hat = BH - (A y - kappa^2 acc) in FP64; R = r_hat rounded to the
 // iterate precision; ||r_hat||^2 (and (rt | r_hat) for BiCGStab).
@@ -58,21 +61,33 @@ template <int SO, bool HASLO, bool BICG>
 __device__ __forceinline__ void upd_site(const SysDesc &d, const SysState *st, cpx<double> acc[12], int s,
                                          double v[NV]) {
   using RO = typename SpinorIO<SO>::R;
-  cpx<double> y[12], b[12];
-  SumLd yl{d.f[F_XH], HASLO ? d.f[F_X] : nullptr, d.npad};
-  yl(0, s, y);
-  SpinorIO<S_F64>::load(d.f[F_BH], s, d.npad, b);
-  if (HASLO) {
-    SpinorIO<S_F64>::store(d.f[F_XH], s, d.npad, y);
-    cpx<float> z[12];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) z[k] = cmake(0.f, 0.f);
-    SpinorIO<S_F32>::store(d.f[F_X], s, d.npad, z);
-  }
-  apply_chi(y, CHI_A, d.tmu);
   const double k2 = d.kappa * d.kappa;
+  double2 *xh = (double2 *)d.f[F_XH] + f64_at(s);
+  const double2 *bh = (const double2 *)d.f[F_BH] + f64_at(s);
+  float4 *xl = HASLO ? (float4 *)d.f[F_X] + (size_t)(s >> 6) * (6 * WAVE) + (s & 63) : nullptr;
 #pragma unroll
-  for (int k = 0; k < 12; ++k) acc[k] = cadd(csub(b[k], y[k]), cscale(k2, acc[k]));
+  for (int c = 0; c < 3; ++c) {   // a colour at a time: three waves per SIMD keep their registers
+    double2 y[4], b[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { y[j] = xh[(4 * c + j) * WAVE]; b[j] = bh[(4 * c + j) * WAVE]; }
+    if (HASLO) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float4 l = xl[(2 * c + j) * WAVE];
+        y[2 * j] = make_double2(y[2 * j].x + (double)l.x, y[2 * j].y + (double)l.y);
+        y[2 * j + 1] = make_double2(y[2 * j + 1].x + (double)l.z, y[2 * j + 1].y + (double)l.w);
+        xl[(2 * c + j) * WAVE] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) xh[(4 * c + j) * WAVE] = y[j];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const cpx<double> ay = chi1(cmake(y[j].x, y[j].y), j, CHI_A, d.tmu);
+      acc[4 * c + j] = cadd(csub(cmake(b[j].x, b[j].y), ay), cscale(k2, acc[4 * c + j]));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
   v[0] = norm12(acc);
   cpx<RO> r[12];
   cvt12(acc, r);
@@ -88,12 +103,20 @@ __device__ __forceinline__ void upd_site(const SysDesc &d, const SysState *st, c
 
 // ||b - D x||^2 at a site of parity par, acc = (H x_{1-par})(s).
 __device__ __forceinline__ void res_site(const SysDesc &d, cpx<double> acc[12], int par, int s, double v[NV]) {
-  cpx<double> x[12], b[12];
-  SpinorIO<S_F64>::load(d.f[par ? F_XH : F_XE], s, d.npad, x);
-  SpinorIO<S_F64>::load(d.f[par ? F_BO : F_BE], s, d.npad, b);
-  apply_chi(x, CHI_A, d.tmu);
+  const double2 *xp = (const double2 *)d.f[par ? F_XH : F_XE] + f64_at(s);
+  const double2 *bp = (const double2 *)d.f[par ? F_BO : F_BE] + f64_at(s);
 #pragma unroll
-  for (int k = 0; k < 12; ++k) acc[k] = cadd(csub(b[k], x[k]), cscale(d.kappa, acc[k]));
+  for (int c = 0; c < 3; ++c) {
+    double2 x[4], b[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { x[j] = xp[(4 * c + j) * WAVE]; b[j] = bp[(4 * c + j) * WAVE]; }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const cpx<double> ax = chi1(cmake(x[j].x, x[j].y), j, CHI_A, d.tmu);
+      acc[4 * c + j] = cadd(csub(cmake(b[j].x, b[j].y), ax), cscale(d.kappa, acc[4 * c + j]));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
   v[0] = norm12(acc);
 }
 
