@@ -129,3 +129,23 @@ def test_one_work_group_goes_on():
         side.synchronize()
         assert st == sg and info[0]["iterations"] == ig[0]["iterations"] == n
         assert torch.equal(x, xg)
+
+
+# Packing moves runs of 128 canonical sites: a run shorter than a wave's share, a
+# ragged last one, whole ones; and, with 2 x 21 MB and 12 x 21 MB of FP64 fields of
+# 12x12x12x32, both streaming forms.  Half subsets leave the other parity alone.
+@pytest.mark.parametrize("dims,nrhs", [((2, 2, 2, 2), 2), ((6, 4, 2, 4), 3), ((4, 4, 4, 4), 1), ((6, 10, 2, 8), 2),
+                                       ((12, 12, 12, 32), 4), ((12, 12, 12, 32), 13)])
+def test_packing_runs(dims, nrhs):
+    say("packing", dims, nrhs)
+    lat = q.Lattice(dims, 0.12, latgen.gauge_field(1090, 0, dims, "unit"), lo_precs=0)
+    psi = dev(latgen.complex_gaussian(np.random.default_rng(9), (nrhs,) + W.site_shape(dims) + (3, 4)))
+    par = torch.from_numpy(W.parity_field(dims)).cuda().reshape(-1)
+    for prec, rnd in ((q.F64, lambda a: a), (q.F32, storage.round_f32), (q.F16S, storage.round_f16s)):
+        want = dev(rnd(host(psi)))
+        assert torch.equal(lat.export_field(lat.import_field(psi, q.FULL, prec), q.FULL, prec, nrhs), want)
+        for p in (0, 1):
+            out = torch.full_like(psi, 7.0)
+            lat.export_field(lat.import_field(psi, p, prec), p, prec, nrhs, out=out)
+            o, w = out.reshape(nrhs, -1, 12), want.reshape(nrhs, -1, 12)
+            assert torch.equal(o[:, par == p], w[:, par == p]) and bool((o[:, par != p] == 7.0).all())
