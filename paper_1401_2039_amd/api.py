@@ -8,6 +8,7 @@ types and sizes, pass raw pointers and the current torch stream, and raise
 QiralError on a non-OK status; they compute nothing themselves.
 """
 import ctypes
+import functools
 
 import torch
 
@@ -29,8 +30,8 @@ def _need_cuda(t, name, dtype=None, nbytes=None):
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} must have dtype {dtype}, not {t.dtype}")
-    if nbytes is not None and t.numel() * t.element_size() < nbytes:
-        raise ValueError(f"{name} holds {t.numel() * t.element_size()} bytes, needs {nbytes}")
+    if nbytes is not None and t.nbytes < nbytes:
+        raise ValueError(f"{name} holds {t.nbytes} bytes, needs {nbytes}")
     return ctypes.c_void_p(t.data_ptr())
 
 
@@ -41,8 +42,15 @@ def _volume(dims):
     return v
 
 
-def qiral_field_bytes(dims, subset, prec, nrhs=1):
+@functools.lru_cache(maxsize=1024)
+def _field_bytes(dims, subset, prec, nrhs):
+    # a pure function of its arguments, asked for on every operator call: 3.3 us
+    # through ctypes, against 5 us of a small hop
     return int(L.load().qiral_field_bytes(L.dims_arg(dims), subset, prec, nrhs))
+
+
+def qiral_field_bytes(dims, subset, prec, nrhs=1):
+    return _field_bytes(tuple(int(d) for d in dims), int(subset), int(prec), int(nrhs))
 
 
 def qiral_gauge_bytes(dims, prec, recon=None):
