@@ -288,11 +288,29 @@ __global__ __launch_bounds__(WG, HOP_MIN_WAVES(S, T, NR)) void k_hop(Geo g, cons
 }
 
 namespace qiral {
-HopCfg hop_config(const qiral_lattice *lat, int prec, long nrhs) {
+// Right-hand sides per lane of a hop that was not tuned.  Two read each link once
+// for both, but keep two thirds of the waves: while the items are few, or in a
+// solver's hops (whose links the last-level cache serves and whose epilogues read
+// more), one is faster.  One / two per lane, us:
+//   S, FP64: 12 fields of 12^3x24 78 / 83, 2 of 20^3x40 118 / 123, 12 of 16^3x32
+//     248 / 249, 2 of 24^3x48 261 / 231, 12 of 20^3x40 721 / 690
+//   S, FP32: 12 of 12^3x24 40 / 42, 2 of 24^3x48 96 / 123, 4 of 24^3x48 228 / 224
+//   S, F16S: 2 of 16^3x32 20.6 / 22.3, 2 of 24^3x48 71 / 76, 12 of 16^3x32 80 / 76, 4
+//     of 24^3x48 134 / 124; D on 5 of 14x10x18x22 18.9 / 21.9
+//   CGNR in ms, FP64: 12 of 12^3x24 9.7 / 11.4, 4 of 16^3x32 10.3 / 11.9, 2 of 24^3x48
+//     28.9 / 28.3, 4 52.3 / 55.9, 12 147 / 158; FP32: 3 of 20^3x40 12.3 / 13.8, 12 of
+//     24^3x48 93.5 / 97.3; F16S: 12 of 12^3x24 6.05 / 6.27, 2 of 24^3x48 12.9 / 13.7, 12
+//     of 16^3x32 14.2 / 13.8, 4 of 24^3x48 22.8 / 22.0
+static int default_nr(int prec, long items, bool solver) {
+  if (solver && prec != QIRAL_F16S) return 1;
+  return items < (prec == QIRAL_F64 ? 8000 : 11000) ? 1 : 2;
+}
+
+HopCfg hop_config(const qiral_lattice *lat, int prec, long nrhs, bool solver) {
   HopCfg c;
   const long nb = lat->geo.nb;
   if (const char *e = getenv("QIRAL_HOP_NR")) c.nr = atoi(e);
-  else c.nr = tuned_nr(lat, prec, (int)nrhs);
+  else if (!(c.nr = tuned_nr(lat, prec, (int)nrhs))) c.nr = default_nr(prec, nb * nrhs, solver);
   c.nr = std::max(1, std::min(c.nr, 4));
   if (c.nr > nrhs) c.nr = (int)nrhs;
   const long nitems = nb * ((nrhs + c.nr - 1) / c.nr);

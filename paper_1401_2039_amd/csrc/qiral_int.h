@@ -48,7 +48,7 @@ const void *links_for(const qiral_lattice *lat, int prec);
 // Launch shape of a hop: t waves per 64-site block (1, 2 or 4) and nr
 // right-hand sides per lane (1..4; see hop_nr_max).  hop_split picks t for `nwork` 64-site work items
 // (enough waves to give every SIMD, 256 CUs x 4, a few); tuned_nr gives the
-// autotuned nr of a lattice (a heuristic until tuned).  QIRAL_HOP_SPLIT and
+// autotuned nr of a lattice, 0 until tuned (then hop_config's rule).  QIRAL_HOP_SPLIT and
 // QIRAL_HOP_NR override.
 struct HopCfg { int t = 4, nr = 1, tile = 0; };   // tile 0: hop_tile's default
 // Largest number of right-hand sides per lane that a hop of storage precision
@@ -80,7 +80,8 @@ int hop_zb(const Geo &g);
 // autotuned size.
 int hop_tile(const Geo &g, int ngroups, int tuned = 0);
 int tuned_nr(const qiral_lattice *lat, int prec, int nrhs);
-HopCfg hop_config(const qiral_lattice *lat, int prec, long nrhs);
+// solver: for the grouped solver's hops.
+HopCfg hop_config(const qiral_lattice *lat, int prec, long nrhs, bool solver = false);
 // What a hop computes: see launch_hop.  p = -1: in, out and x are full fields
 // and both output parities are computed.
 struct HopCall {

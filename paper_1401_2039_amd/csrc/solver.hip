@@ -286,7 +286,7 @@ qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, cons
   bool same_lattice = true;
   for (int i = 1; i < nsys; ++i) same_lattice = same_lattice && sys[i].lat == sys[0].lat;
   HopCfg hc;
-  if (same_lattice) hc = hop_config(sys[0].lat, prec, nsys);
+  if (same_lattice) hc = hop_config(sys[0].lat, prec, nsys, true);
   else { hc.nr = 1; hc.t = hop_split(prec, nwork); }
   if (hc.t == 1) hc.t = 2;   // the solver's hop kernel carries more state: one wave per block spills
   std::vector<uint32_t> work, work_hop;

@@ -77,12 +77,7 @@ void cache_store(const std::string &key, int t, int nr, int tile, double us) {
 }  // namespace
 
 namespace qiral {
-int tuned_nr(const qiral_lattice *lat, int prec, int nrhs) {
-  const int idx = nrhs < 4 ? nrhs : 4;
-  if (lat->tuned_nr[prec][idx]) return lat->tuned_nr[prec][idx];
-  // untuned: share each link between two right-hand sides when there are several
-  return nrhs >= 2 ? 2 : 1;
-}
+int tuned_nr(const qiral_lattice *lat, int prec, int nrhs) { return lat->tuned_nr[prec][nrhs < 4 ? nrhs : 4]; }
 }  // namespace qiral
 
 extern "C" qiral_status qiral_tune(qiral_lattice *lat, qiral_prec prec, int32_t nrhs, void *in, void *out,
