@@ -1156,6 +1156,16 @@ template <bool NT> __device__ __forceinline__ void vst(double2 *p, double2 v) {
   else *p = v;
 }
 
+// a v + c and conj(a) v with the fused forms written out: the compiler's own choice
+// of which product to fuse differs with LV, and a system's iterates may not depend
+// on how many others are solved with it.
+__device__ __forceinline__ double2 zfma(double2 a, double2 v, double2 c) {
+  return make_double2(fma(a.x, v.x, fma(-a.y, v.y, c.x)), fma(a.x, v.y, fma(a.y, v.x, c.y)));
+}
+__device__ __forceinline__ double2 zdot(double2 a, double2 v) {
+  return make_double2(fma(a.x, v.x, a.y * v.y), fma(a.x, v.y, -(a.y * v.x)));
+}
+
 // P = R + beta (P - omega V)
 template <int LV>
 __global__ __launch_bounds__(256) void k_bq_p(const double2 *__restrict__ coef, const double2 *__restrict__ R,
@@ -1165,10 +1175,8 @@ __global__ __launch_bounds__(256) void k_bq_p(const double2 *__restrict__ coef, 
   if (i >= n) return;
   const double2 *c = sys_coef(coef, i, n2);
   const double2 be = c[BQ_C_BETA], om = c[BQ_C_OMEGA], r = vld<(LV > 1)>(R + i), v = vld<(LV > 0)>(V + i);
-  double2 p = vld<(LV > 1)>(P + i);
-  p.x -= om.x * v.x - om.y * v.y;
-  p.y -= om.x * v.y + om.y * v.x;
-  vst<(LV > 1)>(P + i, make_double2(r.x + (be.x * p.x - be.y * p.y), r.y + (be.x * p.y + be.y * p.x)));
+  const double2 p = zfma(make_double2(-om.x, -om.y), v, vld<(LV > 1)>(P + i));
+  vst<(LV > 1)>(P + i, zfma(be, p, r));
 }
 
 // S = R - alpha V
@@ -1179,7 +1187,7 @@ __global__ __launch_bounds__(256) void k_bq_s(const double2 *__restrict__ coef, 
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double2 a = sys_coef(coef, i, n2)[BQ_C_MALPHA], v = vld<(LV > 1)>(V + i), r = vld<(LV > 0)>(R + i);
-  vst<(LV > 1)>(S + i, make_double2(r.x + (a.x * v.x - a.y * v.y), r.y + (a.x * v.y + a.y * v.x)));
+  vst<(LV > 1)>(S + i, zfma(a, v, r));
 }
 
 // X += alpha PH + omega SH
@@ -1191,12 +1199,7 @@ __global__ __launch_bounds__(256) void k_bq_x(const double2 *__restrict__ coef, 
   if (i >= n) return;
   const double2 *c = sys_coef(coef, i, n2);
   const double2 al = c[BQ_C_X], om = c[BQ_C_X2], ph = vld<(LV > 0)>(PH + i), sh = vld<(LV > 0)>(SH + i);
-  double2 x = vld<(LV > 0)>(X + i);
-  x.x += al.x * ph.x - al.y * ph.y;
-  x.y += al.x * ph.y + al.y * ph.x;
-  x.x += om.x * sh.x - om.y * sh.y;
-  x.y += om.x * sh.y + om.y * sh.x;
-  vst<(LV > 0)>(X + i, x);
+  vst<(LV > 0)>(X + i, zfma(om, sh, zfma(al, ph, vld<(LV > 0)>(X + i))));
 }
 
 // partial pairs of (a | b): part[block * 2 + re/im]
@@ -1207,7 +1210,7 @@ __global__ __launch_bounds__(256) void k_dot1(const double2 *__restrict__ a, con
   double2 ab = make_double2(0.0, 0.0);
   if (i < n) {
     const double2 av = vld<(LV > 1)>(a + i), bv = vld<(LV > 1)>(b + i);
-    ab = make_double2(av.x * bv.x + av.y * bv.y, av.x * bv.y - av.y * bv.x);
+    ab = zdot(av, bv);
   }
   block_pair(ab.x, ab.y, part + (size_t)blockIdx.x * 2);
 }
@@ -1220,8 +1223,8 @@ __global__ __launch_bounds__(256) void k_dot2(const double2 *__restrict__ a, con
   double2 ab = make_double2(0.0, 0.0), aa = ab;
   if (i < n) {
     const double2 av = vld<(LV > 1)>(a + i), bv = vld<(LV > 1)>(b + i);
-    ab = make_double2(av.x * bv.x + av.y * bv.y, av.x * bv.y - av.y * bv.x);
-    aa = make_double2(av.x * av.x + av.y * av.y, av.x * av.y - av.y * av.x);
+    ab = zdot(av, bv);
+    aa = zdot(av, av);
   }
   block_pair2(ab.x, ab.y, aa.x, aa.y, part + (size_t)blockIdx.x * 2, part + ((size_t)gridDim.x + blockIdx.x) * 2);
 }
@@ -1236,10 +1239,10 @@ __global__ __launch_bounds__(256) void k_bq_r(const double2 *__restrict__ coef, 
   if (i < n) {
     const double2 a = sys_coef(coef, i, n2)[BQ_C_MOMEGA], sv = vld<(LV > 0)>(S + i), tv = vld<(LV > 0)>(T + i),
                   rt = vld<(LV > 1)>(RT + i);
-    const double2 r = make_double2(sv.x + (a.x * tv.x - a.y * tv.y), sv.y + (a.x * tv.y + a.y * tv.x));
+    const double2 r = zfma(a, tv, sv);
     vst<(LV > 1)>(R + i, r);
-    tr = make_double2(rt.x * r.x + rt.y * r.y, rt.x * r.y - rt.y * r.x);
-    rr = make_double2(r.x * r.x + r.y * r.y, 0.0);
+    tr = zdot(rt, r);
+    rr = make_double2(zdot(r, r).x, 0.0);
   }
   block_pair2(tr.x, tr.y, rr.x, rr.y, part + (size_t)blockIdx.x * 2, part + ((size_t)gridDim.x + blockIdx.x) * 2);
 }

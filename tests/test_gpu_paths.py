@@ -82,6 +82,25 @@ def test_network_and_gradient_tiles(dims, H):
     assert np.abs(g[0::2] + 1j * g[1::2] - want).max() < 1e-5 * np.abs(want).max()
 
 
+def test_network_streamed_for_several_systems():
+    """The path fields of four systems of 12^3x16 (48 MB) are streamed, of one (12 MB)
+    cached: the iterates in lockstep are those alone bit for bit."""
+    dims = (12, 12, 12, 16)
+    say("network streamed", dims)
+    cfg = latgen.small_config(dims, seed=88, kind="expih", eps=0.4, nrhs=4)
+    lat = q.Lattice(dims, 0.12, cfg["U"])
+    net = q.Network(lat, 2)
+    kw = dict(tol=1e-10, solver=q.BICGSTAB_EO, system=q.SYSTEM_SCHUR, precond=net.handle, fallback_cg=0)
+    b = dev(cfg["b"])
+    x, st, info = lat.solve(b, **kw)
+    x = x.clone()
+    assert st == 0
+    for r in (0, 3):
+        x1, st1, i1 = lat.solve(b[r:r + 1], **kw)
+        assert st1 == 0 and i1[0]["iterations"] == info[r]["iterations"] and torch.equal(x[r:r + 1], x1)
+    assert S.true_rel_residual(cfg["U"], 0.12, 0.0, host(x)[3], cfg["b"][3]) <= 1e-10
+
+
 # One work-group solves a lattice of up to four 64-site blocks; a captured graph
 # always takes the grouped kernels.  Both take the same steps with the same sums:
 # equal bit for bit in FP64, and to the tolerance of the solves in the reduced
