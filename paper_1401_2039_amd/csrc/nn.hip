@@ -236,7 +236,7 @@ __device__ __forceinline__ void path_use(const PathIn<SIN> &in, int h, cpx<float
 //
 // Work-groups of four waves walk the 64-site blocks of both parities in the
 // hop's XCD-mapped order, `nblk` of them, and keep the fragments.
-template <int SIN>
+template <int SIN, bool NT>
 __global__ __launch_bounds__(256, 2) void k_nn_pass_a(Geo g, const void *__restrict__ links,
                                                       const float *__restrict__ frag, const void *__restrict__ in0,
                                                       const void *__restrict__ in1, void *__restrict__ m,
@@ -322,7 +322,11 @@ __global__ __launch_bounds__(256, 2) void k_nn_pass_a(Geo g, const void *__restr
       if (p >= NPATH) continue;
       float4 *dst = (float4 *)((char *)m + (size_t)p * mstride + ya * hb) + ((size_t)sb * 6 + (g4 & 1)) * WAVE + sl;
 #pragma unroll
-      for (int a = 0; a < 3; ++a) st_nt(dst + 2 * a * WAVE, make_float4(D[mt][a][0], D[mt][a][1], D[mt][a][2], D[mt][a][3]));
+      for (int a = 0; a < 3; ++a) {
+        const float4 q = make_float4(D[mt][a][0], D[mt][a][1], D[mt][a][2], D[mt][a][3]);
+        if (NT) st_nt(dst + 2 * a * WAVE, q);
+        else dst[2 * a * WAVE] = q;
+      }
     }
   }
 }
@@ -371,7 +375,7 @@ __global__ void k_nn_frag(const float2 *__restrict__ K, __bf16 *__restrict__ f) 
   f[adj * 4 * 2 * 2 * 64 * 8 + idx] = hl == 0 ? hi : (__bf16)(v - (float)hi);
 }
 
-template <int SIN>
+template <int SIN, bool NT>
 __global__ __launch_bounds__(256, 3) void k_nn_pass_a_mfma(Geo g, const void *__restrict__ links,
                                                         const float2 *__restrict__ K, const bf16x8 *__restrict__ frag,
                                                         const void *__restrict__ in, size_t istride,
@@ -488,7 +492,9 @@ __global__ __launch_bounds__(256, 3) void k_nn_pass_a_mfma(Geo g, const void *__
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         const f32x4 d = D[j][a];
-        st_nt(base + ((size_t)sb * 6 + 2 * a + (g4 & 1)) * WAVE + 16 * j + n, make_float4(d[0], d[1], d[2], d[3]));
+        float4 *dst = base + ((size_t)sb * 6 + 2 * a + (g4 & 1)) * WAVE + 16 * j + n;
+        if (NT) st_nt(dst, make_float4(d[0], d[1], d[2], d[3]));
+        else *dst = make_float4(d[0], d[1], d[2], d[3]);
       }
     }
   }
@@ -498,10 +504,11 @@ __global__ __launch_bounds__(256, 3) void k_nn_pass_a_mfma(Geo g, const void *__
 // spinor of m is read once in the whole pass: streaming loads, which took pass B
 // over both parities at 24^3x48 from 190 to 131 us (6.8 TB/s) and the lockstep
 // solver's pass over 12 systems from 1100 to 923 us.
+template <bool NT>
 __device__ __forceinline__ void path_sum(const Geo &g, const void *links, const char *m, size_t mstride, size_t hoff,
                                          size_t npad, const SiteC &c, int px, cpx<float> acc[12]) {
   SpinorIO<S_F32>::Raw r;
-  SpinorIO<S_F32>::fetch<true>(m + px * hoff, c.s, npad, r);
+  SpinorIO<S_F32>::fetch<NT>(m + px * hoff, c.s, npad, r);
   SpinorIO<S_F32>::decode(r, acc);
 #pragma unroll 1
   for (int p = 1; p < NPATH; ++p) {
@@ -512,7 +519,7 @@ __device__ __forceinline__ void path_sum(const Geo &g, const void *links, const 
     cpx<float> u[9], psi[12], t[12];
     if (fwd) LinkIO<L_F32R12>::load(links, px, mu, c.s, g.nb, u);
     else LinkIO<L_F32R12>::load(links, 1 - px, mu, n, g.nb, u);
-    SpinorIO<S_F32>::fetch<true>(m + (size_t)p * mstride + (1 - px) * hoff, n, npad, r);
+    SpinorIO<S_F32>::fetch<NT>(m + (size_t)p * mstride + (1 - px) * hoff, n, npad, r);
     SpinorIO<S_F32>::decode(r, psi);
     transport(u, psi, t, !fwd);
 #pragma unroll
@@ -525,7 +532,7 @@ __device__ __forceinline__ void path_sum(const Geo &g, const void *links, const 
 // XCD-mapped order), written in storage SOUT to out0 (even half) or out1 (odd
 // half).  Path fields as in pass A; nsys systems one after the other (outputs
 // ostride bytes apart), reusing the block's links from the cache.
-template <int SOUT, bool MULTI>
+template <int SOUT, bool MULTI, bool NT>
 __global__ __launch_bounds__(256) void k_nn_pass_b(Geo g, const void *__restrict__ links, const void *__restrict__ m,
                                                    size_t mstride, size_t hoff, size_t msys, void *__restrict__ out0,
                                                    void *__restrict__ out1, size_t ostride, int nsys, int out_par,
@@ -542,7 +549,7 @@ __global__ __launch_bounds__(256) void k_nn_pass_b(Geo g, const void *__restrict
 #pragma unroll 1
   for (int sy = 0; sy < ns; ++sy) {
     cpx<float> acc[12];
-    path_sum(g, links, (const char *)m + sy * msys, mstride, hoff, npad, c, px, acc);
+    path_sum<NT>(g, links, (const char *)m + sy * msys, mstride, hoff, npad, c, px, acc);
     void *dst = (char *)(px ? out1 : out0) + sy * ostride;
     if constexpr (SOUT == S_F32) {
       SpinorIO<S_F32>::store(dst, s, npad, acc);
@@ -557,6 +564,7 @@ __global__ __launch_bounds__(256) void k_nn_pass_b(Geo g, const void *__restrict
 // Pass B of a training step: with y(x) = sum_p (T_p m_p)(x) the network's
 // output, g = (y - v) / ||v||^2 and partials of ||y - v||^2, one per work-group;
 // y itself is not stored.  Grid (ceil(nb / 4), 2 parities) as pass B.
+template <bool NT>
 __global__ __launch_bounds__(256) void k_nn_pass_b_loss(Geo g, const void *__restrict__ links,
                                                         const void *__restrict__ m, size_t mstride,
                                                         const void *__restrict__ v, const double *__restrict__ vnorm,
@@ -569,7 +577,7 @@ __global__ __launch_bounds__(256) void k_nn_pass_b_loss(Geo g, const void *__res
   if (s < g.vh) {
     const SiteC c = site_c(g, s, px);
     cpx<float> a[12], b[12];
-    path_sum(g, links, (const char *)m, mstride, hb, npad, c, px, a);
+    path_sum<NT>(g, links, (const char *)m, mstride, hb, npad, c, px, a);
     SpinorIO<S_F32>::load((const char *)v + px * hb, s, npad, b);
     const float inv = (float)(1.0 / vnorm[0]);
 #pragma unroll
@@ -1335,12 +1343,23 @@ hipError_t nn_fold(const qiral_nn *nn, hipStream_t s) {
   return nn_frag32(nn, 0, 2, s);
 }
 
+// Streaming stores and loads of the path fields, where all nine of `halves` F32
+// half-fields are more than the L2s of the eight dies hold (4 MB each): below that
+// pass B finds what pass A wrote in them and the hint only sends it past, above it
+// pass A's lines would push out what is still to be read.  Streaming against cached:
+// 12 systems of 8^4 (21 MB) 4.90 against 4.44 ms a solve, one of 12^3 x 24 (18 MB)
+// 1.62 / 1.58; one of 16^3 x 32 (57 MB) 2.38 / 2.45, the forward pass on 20^3 x 40
+// (276 MB) 189 / 209 us and on 24^3 x 48 (573 MB) 365 / 455.
+bool paths_stream(long halves, const Geo &g) {
+  return (double)halves * NPATH * half_bytes(g, QIRAL_F32) >= 40e6;
+}
+
 // Pass A on both parities: the path fields of the F32 or F64 full field (in0, in1).
 template <int SIO>
 void nn_pass_a(const qiral_nn *nn, const void *in0, const void *in1, bool adj, int zb, hipStream_t s) {
   const Geo &g = nn->lat->geo;
   const int wgs = std::min(2 * g.nb, 2 * 256);   // all resident: two per compute unit
-  hipLaunchKernelGGL((k_nn_pass_a<SIO>), dim3(wgs), dim3(256), 0, s, g, nn->lat->g32,
+  hipLaunchKernelGGL(paths_stream(2, g) ? (k_nn_pass_a<SIO, true>) : (k_nn_pass_a<SIO, false>), dim3(wgs), dim3(256), 0, s, g, nn->lat->g32,
                      (const float *)(nn->kfrag32 + (adj ? FRAG32 : 0)), in0, in1, nn->paths, full_bytes32(g), zb);
 }
 
@@ -1362,18 +1381,19 @@ hipError_t nn_apply_folded(const qiral_nn *nn, void *out0, void *out1, const voi
   if (par >= 0) {
     // path field p is the one parity it is used on: m_0 on par, m_1..m_8 on 1 - par
     void *m = mbuf ? mbuf : nn->paths;
-    hipLaunchKernelGGL((k_nn_pass_a_mfma<SIO>), dim3(g.nb, 2), dim3(256), 0, s, g, nn->lat->g32, K,
+    const bool nt = paths_stream(nsys, g);
+    hipLaunchKernelGGL(nt ? (k_nn_pass_a_mfma<SIO, true>) : (k_nn_pass_a_mfma<SIO, false>), dim3(g.nb, 2), dim3(256), 0, s, g, nn->lat->g32, K,
                        (const bf16x8 *)nn->kfrag + (adj ? 4 * 2 * 2 * WAVE : 0), par ? in1 : in0, iostride, m, hb,
                        (size_t)0, NPATH * hb, nsys, par, zb);
     if (nsys > 1)
-      hipLaunchKernelGGL((k_nn_pass_b<SIO, true>), dim3((g.nb + 3) / 4, 1), dim3(256), 0, s, g, nn->lat->g32,
+      hipLaunchKernelGGL(nt ? (k_nn_pass_b<SIO, true, true>) : (k_nn_pass_b<SIO, true, false>), dim3((g.nb + 3) / 4, 1), dim3(256), 0, s, g, nn->lat->g32,
                          (const void *)m, hb, (size_t)0, NPATH * hb, out0, out1, iostride, nsys, par, zb);
     else
-      hipLaunchKernelGGL((k_nn_pass_b<SIO, false>), dim3((g.nb + 3) / 4, 1), dim3(256), 0, s, g, nn->lat->g32,
+      hipLaunchKernelGGL(nt ? (k_nn_pass_b<SIO, false, true>) : (k_nn_pass_b<SIO, false, false>), dim3((g.nb + 3) / 4, 1), dim3(256), 0, s, g, nn->lat->g32,
                          (const void *)m, hb, (size_t)0, NPATH * hb, out0, out1, (size_t)0, 1, par, zb);
   } else {
     nn_pass_a<SIO>(nn, in0, in1, adj, zb, s);
-    hipLaunchKernelGGL((k_nn_pass_b<SIO, false>), dim3((g.nb + 3) / 4, 2), dim3(256), 0, s, g, nn->lat->g32,
+    hipLaunchKernelGGL(paths_stream(2, g) ? (k_nn_pass_b<SIO, false, true>) : (k_nn_pass_b<SIO, false, false>), dim3((g.nb + 3) / 4, 2), dim3(256), 0, s, g, nn->lat->g32,
                        (const void *)nn->paths, fs, hb, (size_t)0, out0, out1, (size_t)0, 1, par, zb);
   }
   return hipGetLastError();
@@ -1589,7 +1609,7 @@ hipError_t train_step(qiral_nn *nn, const void *src, const void *target, double 
   hipError_t e = nn_frag32(nn, 0, 1, s);
   if (e != hipSuccess) return e;
   nn_pass_a<S_F32>(nn, src, (const char *)src + hb, false, zb, s);
-  hipLaunchKernelGGL(k_nn_pass_b_loss, gb, bd, 0, s, g, nn->lat->g32, nn->paths, fs, target, nn->scal, nn->fg, zb,
+  hipLaunchKernelGGL(paths_stream(2, g) ? k_nn_pass_b_loss<true> : k_nn_pass_b_loss<false>, gb, bd, 0, s, g, nn->lat->g32, nn->paths, fs, target, nn->scal, nn->fg, zb,
                      nn->part);
   hipLaunchKernelGGL(k_sum, dim3(1), bd, 0, s, nn->part, (int)(2 * gb.x), loss_dev, nn->scal);
   hipLaunchKernelGGL(k_nn_dk, dim3(nwg), bd, 0, s, g, nn->lat->g32, nn->fg, src, zb, nn->part);
