@@ -44,8 +44,8 @@ struct SoloProg {
 enum : int { SOLO_NEW = 0, SOLO_RESTART = 1, SOLO_MORE = 2 };
 
 // Solves nsys systems of at most SOLO_BLOCKS blocks, one work-group each, or
-// goes on with them; the states say which are done.  At most 256 iterations a
-// launch.
+// goes on with those that the states do not say are done.  At most 256
+// iterations a launch.
 hipError_t solo_launch(const SysDesc *desc, int nsys, int solver, int prec, bool twisted, bool guess, int mode,
                        hipStream_t s);
 

@@ -243,6 +243,9 @@ template <int S> __global__ __launch_bounds__(SW *WAVE, 2) void k_solo(const Sys
   for (int i = threadIdx.x; i < (int)(sizeof(SysState) / 8); i += SW * WAVE)
     ((unsigned long long *)&so.st)[i] = ((const unsigned long long *)dg->st)[i];
   __syncthreads();
+  // done in an earlier launch, its end steps with it: they must not run again (the
+  // last x += alpha p would be added twice)
+  if (mode != SOLO_NEW && (so.st.status & ST_DONE)) return;
 
   auto run = [&](const SoloStep &q) {
     if (!(so.st.status & q.mask)) return;   // uniform: the state changes between barriers only

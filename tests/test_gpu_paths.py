@@ -168,3 +168,34 @@ def test_packing_runs(dims, nrhs):
             lat.export_field(lat.import_field(psi, p, prec), p, prec, nrhs, out=out)
             o, w = out.reshape(nrhs, -1, 12), want.reshape(nrhs, -1, 12)
             assert torch.equal(o[:, par == p], w[:, par == p]) and bool((o[:, par != p] == 7.0).all())
+
+
+def _batch(cfgs, kappas, dims, prec, xs=None, **kw):
+    """qiral_solve_batch of one source per lattice: solutions, status, infos."""
+    lats = [q.Lattice(dims, k, c["U"]) for k, c in zip(kappas, cfgs)]
+    bs = [dev(c["b"]) for c in cfgs]
+    xs = xs(bs) if xs else [lat.canon() for lat in lats]
+    st, info = q.qiral_solve_batch([lat.handle for lat in lats], [dims] * len(lats), xs, bs,
+                                   q.solve_params(inner_prec=prec, **kw))
+    return xs, st, info
+
+
+# Systems of one call that end in different launches of the one-work-group solver
+# (256 iterations each): what is done stays as it is, and the others go on.  The
+# grouped solver's results, bit for bit in FP64.
+@pytest.mark.parametrize("dims,kappas", [((4, 4, 4, 4), (0.12, 0.24)), ((4, 4, 4, 8), (0.24, 0.12, 0.21, 0.1))])
+def test_one_work_group_systems_end_apart(dims, kappas):
+    say("one work-group, several launches", dims, kappas)
+    cfgs = [latgen.small_config(dims, seed=89 + i, kind="haar", nrhs=1) for i in range(len(kappas))]
+    kw = dict(tol=1e-10, maxiter=5000)
+    xs, st, info = _batch(cfgs, kappas, dims, q.F64, **kw)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        xg, sg, ig = _batch(cfgs, kappas, dims, q.F64, use_graph=1, **kw)
+    side.synchronize()
+    its = [i["iterations"] for i in ig]
+    assert st == sg == 0 and min(its) < 256 < max(its)
+    for key in ("iterations", "hop_applications", "true_rel_resid"):
+        assert [i[key] for i in info] == [i[key] for i in ig], key
+    for x, y in zip(xs, xg):
+        assert torch.equal(x, y)
