@@ -154,6 +154,27 @@ bool solo_wanted() {
   return true;
 }
 
+// Whether no system's solution lies in memory of another's source or solution.
+// The grouped solver reads every source before it writes any solution; the
+// work-groups of the one-work-group solver read and write each at its own time.
+bool solutions_apart(const std::vector<SysIn> &sys) {
+  struct Span { const double *lo, *hi; int sys; };
+  const int n = (int)sys.size();
+  std::vector<Span> x(n);
+  auto doubles = [&](int i) { return (size_t)sys[i].lat->geo.vh * 2 * 24; };
+  for (int i = 0; i < n; ++i) x[i] = Span{sys[i].x, sys[i].x + doubles(i), i};
+  std::sort(x.begin(), x.end(), [](const Span &a, const Span &b) { return a.lo < b.lo; });
+  for (int i = 1; i < n; ++i)
+    if (x[i].lo < x[i - 1].hi) return false;
+  for (int i = 0; i < n; ++i) {
+    const double *lo = sys[i].b, *hi = lo + doubles(i);
+    auto at = std::partition_point(x.begin(), x.end(), [&](const Span &s) { return s.hi <= lo; });
+    for (; at != x.end() && at->lo < hi; ++at)
+      if (at->sys != i) return false;
+  }
+  return true;
+}
+
 qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, const qiral_solve_params *prm,
                        void *ws_base, size_t ws_bytes, qiral_solve_info *info, hipStream_t s) {
   auto t0 = std::chrono::steady_clock::now();
@@ -215,6 +236,7 @@ qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, cons
     twisted = twisted || sys[i].lat->mu != 0.0;
     small = small && sys[i].lat->geo.nb <= solo_line(nsys, !mixed, bicg);
   }
+  small = small && solutions_apart(sys);
   std::vector<double> true_rel(nsys, 0.0);
   // The true residuals of the states in hst, and which systems go round again:
   // true if any does (its status is then an update's, as at the start).

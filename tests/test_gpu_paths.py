@@ -199,3 +199,30 @@ def test_one_work_group_systems_end_apart(dims, kappas):
         assert [i[key] for i in info] == [i[key] for i in ig], key
     for x, y in zip(xs, xg):
         assert torch.equal(x, y)
+
+
+# A solution may lie where another system's source was: every source is read
+# before any solution is written.
+@pytest.mark.parametrize("prec", [q.F64, q.F32], ids=["f64", "f32"])
+def test_small_systems_sharing_memory(prec):
+    say("one work-group, a solution in another's source", prec)
+    dims, n = (4, 4, 4, 4), 3
+    cfg = latgen.small_config(dims, seed=93, kind="expih", eps=0.4, nrhs=n)
+    lat = q.Lattice(dims, 0.12, cfg["U"])
+    kw = dict(inner_prec=prec, tol=1e-10)
+    want, st, info = lat.solve(dev(cfg["b"]), use_graph=0, **kw)
+    assert st == 0
+    # the solutions one field before the sources
+    buf = lat.canon(n + 1)
+    buf[1:] = dev(cfg["b"])
+    x, st, info = lat.solve(buf[1:], x_canon=buf[:n], **kw)
+    assert st == 0
+    # a batch: the first solution in the last source, each source read as it was given
+    bs = [dev(cfg["b"][i:i + 1]) for i in range(n)]
+    xs = [bs[n - 1], lat.canon(), lat.canon()]
+    st, _ = q.qiral_solve_batch([lat.handle] * n, [dims] * n, xs, bs, q.solve_params(**kw))
+    assert st == 0
+    for i in range(n):
+        for got in (x[i:i + 1], xs[i]):
+            assert S.true_rel_residual(cfg["U"], 0.12, 0.0, host(got)[0], cfg["b"][i]) <= 1e-10
+            assert prec != q.F64 or torch.equal(got, want[i:i + 1])
