@@ -309,7 +309,7 @@ template <int S> __global__ __launch_bounds__(SW *WAVE, 2) void k_solo(const Sys
       case SK_BIP: solo_vec(so, false, w, [&](int s, double *) { bi_p_site<S, 0>(so.d, &so.st, s); }); break;
       case SK_BIS: solo_vec(so, false, w, [&](int s, double *) { bi_s_site<S, 0>(so.d, &so.st, s); }); break;
       case SK_BIXR:
-        solo_vec(so, true, w, [&](int s, double v[NV]) { bi_xr_site<S, XS, 0>(so.d, &so.st, s, v); });
+        solo_vec(so, true, w, [&](int s, double v[NV]) { bi_xr_site<S, XS, 0, !MIXED>(so.d, &so.st, s, v); });
         break;
       case SK_COPY:
         if (q.f64) solo_vec(so, false, w, [&](int s, double *) { copy_site<S_F64>(so.d, q.fin, q.fout, q.chio, s); });
@@ -351,20 +351,17 @@ template <int S> __global__ __launch_bounds__(SW *WAVE, 2) void k_solo(const Sys
     __syncthreads();
   };
 
-  if (mode == SOLO_NEW)
+  // One place that runs a step: with several the body becomes a function, and its
+  // call a stack, for which the runtime would allocate device memory.
 #pragma unroll 1
-    for (int i = 0; i < prog.start; ++i) run(prog.step[i]);
-  if (mode != SOLO_MORE)
-#pragma unroll 1
-    for (int i = prog.start; i < prog.iter; ++i) run(prog.step[i]);
-#pragma unroll 1
-  for (int k = 0, i = prog.iter; k < MAX_RUN && !(so.st.status & ST_DONE);) {
+  for (int i = mode == SOLO_NEW ? 0 : mode == SOLO_RESTART ? prog.start : prog.iter, k = 0; i < prog.end;) {
+    if (i >= prog.iter && i < prog.post) {   // in the iterations: to the end once done
+      if (so.st.status & ST_DONE) i = prog.post;
+      else if (k == MAX_RUN) break;
+    }
     run(prog.step[i]);
     if (++i == prog.post) { i = prog.iter; ++k; }
   }
-  if (so.st.status & ST_DONE)
-#pragma unroll 1
-    for (int i = prog.post; i < prog.end; ++i) run(prog.step[i]);
   __syncthreads();
   for (int i = threadIdx.x; i < (int)(sizeof(SysState) / 8); i += SW * WAVE)
     ((unsigned long long *)so.d.st)[i] = ((const unsigned long long *)&so.st)[i];

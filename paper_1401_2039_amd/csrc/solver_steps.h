@@ -259,8 +259,10 @@ template <int S, int V> __device__ __forceinline__ void bi_s_site(const SysDesc 
   SpinorIO<S>::template store<(V > 1)>(d.f[F_Z], s, d.npad, r);
 }
 
-// BiCGStab: X += alpha P + omega S; R = S - omega T; (rt | R) and ||R||^2
-template <int S, int XS, int V>
+// BiCGStab: X += alpha P + omega S; R = S - omega T; (rt | R) and ||R||^2.
+// LATE: T and rt are loaded once P and X are used up, for a kernel without registers
+// for five FP64 vectors at once.
+template <int S, int XS, int V, bool LATE = false>
 __device__ __forceinline__ void bi_xr_site(const SysDesc &d, const SysState *st, int site, double v[NV]) {
   using R = typename SpinorIO<S>::R;
   using RX = typename SpinorIO<XS>::R;
@@ -271,12 +273,19 @@ __device__ __forceinline__ void bi_xr_site(const SysDesc &d, const SysState *st,
   SpinorIO<S>::template load<(V > 1)>(d.f[F_P], site, d.npad, p);
   SpinorIO<S>::template load<(V > 0)>(d.f[F_Z], site, d.npad, s);
   SpinorIO<XS>::template load<(V > 0)>(d.f[F_X], site, d.npad, x);
-  SpinorIO<S>::template load<(V > 0)>(d.f[F_T], site, d.npad, t);
-  SpinorIO<S>::template load<(V > 1)>(d.f[F_RT], site, d.npad, rt);
+  auto second = [&]() {
+    SpinorIO<S>::template load<(V > 0)>(d.f[F_T], site, d.npad, t);
+    SpinorIO<S>::template load<(V > 1)>(d.f[F_RT], site, d.npad, rt);
+  };
+  if (!LATE) second();
 #pragma unroll
   for (int k = 0; k < 12; ++k)
     x[k] = cadd(x[k], cadd(cmul(al, cmake((RX)p[k].re, (RX)p[k].im)), cmul(om, cmake((RX)s[k].re, (RX)s[k].im))));
   SpinorIO<XS>::template store<(V > 0)>(d.f[F_X], site, d.npad, x);
+  if (LATE) {
+    __builtin_amdgcn_sched_barrier(0);
+    second();
+  }
 #pragma unroll
   for (int k = 0; k < 12; ++k) s[k] = csub(s[k], cmul(omr, t[k]));
   SpinorIO<S>::template store<(V > 1)>(d.f[F_R], site, d.npad, s);

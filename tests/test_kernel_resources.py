@@ -55,3 +55,13 @@ def test_hop_kernels_do_not_spill(src, reports):
            if r.get("ScratchSize [bytes/lane]") != "0" or r.get("VGPRs Spill") != "0"
            or int(r.get("LDS Size [bytes/block]", "-1")) != e]
     assert not bad, f"{len(bad)} hop kernels use scratch or unexpected LDS: {bad[:4]}"
+
+
+@pytest.mark.parametrize("src", [os.path.basename(s) for s in build.sources()])
+def test_kernels_use_no_scratch(src, reports):
+    """No kernel has a stack or spills: for scratch memory the runtime would allocate
+    device memory, which the library's calls do not."""
+    rows = reports[src] if src in reports else build.kernel_resources(os.path.join(build.CSRC, src))
+    bad = [(r["name"][:60], r.get("ScratchSize [bytes/lane]"), r.get("VGPRs Spill")) for r in rows
+           if r.get("ScratchSize [bytes/lane]") != "0" or r.get("VGPRs Spill") != "0"]
+    assert not bad, f"{len(bad)} kernels of {src} use scratch: {bad[:4]}"
