@@ -226,3 +226,28 @@ def test_small_systems_sharing_memory(prec):
         for got in (x[i:i + 1], xs[i]):
             assert S.true_rel_residual(cfg["U"], 0.12, 0.0, host(got)[0], cfg["b"][i]) <= 1e-10
             assert prec != q.F64 or torch.equal(got, want[i:i + 1])
+
+
+# The gradient's FP32 sums go on in FP64 after 32 products.  Integer fields on unit
+# links, with the identity for a network and a target of norm^2 2^k, make every
+# product (just under 2^19, one sign) and every sum of 32 an FP32 integer: nothing is
+# rounded, where runs of 96 would leave the integers.  One item of 32 sites per
+# work-group, and two.
+@pytest.mark.parametrize("dims", [(8, 8, 8, 8), (16, 16, 16, 8)])
+def test_gradient_sums_leave_fp32_early(dims):
+    say("gradient sums", dims)
+    H, shape = 2, W.site_shape(dims) + (3, 4)
+    U = latgen.gauge_field(1091, 0, dims, "unit")
+    lat = q.Lattice(dims, 0.12, U, lo_precs=q.LINKS_F32)
+    net = q.Network(lat, H)
+    w1, w2 = np.zeros((9, H, 1, 4, 4), complex), np.zeros((9, 1, H, 4, 4), complex)
+    w1[0, 0, 0] = w2[0, 0, 0] = np.eye(4)
+    net.set_weights(w1, w2)
+    rng = np.random.default_rng(11)
+    src = rng.integers(719, 724, shape) + 1j * rng.integers(719, 724, shape)
+    tgt = np.zeros(shape, complex)
+    tgt[..., 0, :] = 1 + 1j   # 8 per site
+    loss, g = net.grad(*(lat.import_field(dev(f[None]), q.FULL, q.F32) for f in (src, tgt)))
+    L, G = ptc.loss_and_grad(U, [w1, w2], src, tgt)
+    assert loss == L
+    assert np.array_equal(g[0::2] + 1j * g[1::2], np.concatenate([(2 * G[0]).ravel(), (2 * G[1]).ravel()]))
