@@ -32,6 +32,7 @@ struct qiral_nn {
   float2 *kmat = nullptr;   // folded path-pair weights K, then K' (scratch)
   void *kfrag = nullptr;    // bf16 MFMA A fragments of K's hop pairs, then of K' (scratch)
   float *kfrag32 = nullptr; // FP32 MFMA A fragments of K, then of K' (scratch)
+  void *kfraglo = nullptr;  // bf16 MFMA A fragments of what K loses in FP32 (training; scratch)
   float *am = nullptr, *av = nullptr;   // Adam moments, [2 (nw1 + nw2)]
   double *grad = nullptr;   // dL/dRe, dL/dIm interleaved, [2 (nw1 + nw2)]
   double *part = nullptr;   // partial sums of the gradient, the loss and the norms
@@ -49,6 +50,7 @@ constexpr int NPATH = 9;
 constexpr int MT32 = 5;          // 16-row tiles of the real form of K (9 paths x 4 spins x re/im = 72 rows)
 constexpr int KS32 = 18;         // its 4-column steps
 constexpr int FRAG32 = MT32 * KS32 * 64;   // floats of its FP32 MFMA fragments
+constexpr int FRAGLO = MT32 * 3 * 64;      // lanes' pieces of eight of its bf16 remainder's fragments
 constexpr int DK_VALUES = MT32 * MT32 * 256;   // doubles of the gradient of K as MFMA tiles
 constexpr int DK_WGS = 512;      // most work-groups of the gradient kernel: two per compute unit
 constexpr int LOSS_CAP = 256;    // training losses kept on the device between copies to the host
@@ -107,8 +109,8 @@ __device__ __forceinline__ int mirror_path(int p) { return p == 0 ? 0 : (p <= 4 
 
 // Entry (r, c) of K_pq (adj = 0) or K'_pq (adj = 1), summed over the H channels
 // in FP64.
-__device__ __forceinline__ float2 fold_entry(const float2 *__restrict__ w1, const float2 *__restrict__ w2, int hidden,
-                                             int adj, int p, int q, int r, int c) {
+__device__ __forceinline__ double2 fold_entry64(const float2 *__restrict__ w1, const float2 *__restrict__ w2,
+                                                int hidden, int adj, int p, int q, int r, int c) {
   const int P = adj ? mirror_path(q) : p, Q = adj ? mirror_path(p) : q;
   const int rr = adj ? c : r, cc = adj ? r : c;
   double re = 0.0, im = 0.0;
@@ -121,7 +123,12 @@ __device__ __forceinline__ float2 fold_entry(const float2 *__restrict__ w1, cons
       im += (double)x.x * y.y + (double)x.y * y.x;
     }
   }
-  return make_float2((float)re, (float)(adj ? -im : im));
+  return make_double2(re, adj ? -im : im);
+}
+__device__ __forceinline__ float2 fold_entry(const float2 *__restrict__ w1, const float2 *__restrict__ w2, int hidden,
+                                             int adj, int p, int q, int r, int c) {
+  const double2 k = fold_entry64(w1, w2, hidden, adj, p, q, r, c);
+  return make_float2((float)k.x, (float)k.y);
 }
 
 // K (blockIdx.y = 0) and K' (1) into k[adj][p][p'][4][4]; one thread per entry.
@@ -145,10 +152,27 @@ __device__ __forceinline__ float real_form(float2 k, int row, int col) {
 // the 72nd.  The four columns of step ks, one per lane group lane / 16: for
 // ks < 16 the real ks % 8 (spin, re/im) of the input paths 1 + 4 (ks / 8) +
 // group, for ks = 16, 17 the reals 4 (ks - 16) + group of path 0.
+//
+// lo, if not NULL, takes the bf16 (16x16x32) fragments of K - (K in FP32):
+// lo[((mt * 3 + ks) * 64 + lane) * 8 + kk], kk the reals of path 1 + 4 ks + group for
+// ks < 2, and for ks = 2 the reals group and 4 + group of path 0, then zeros.
 __global__ void k_nn_frag32(const float2 *__restrict__ w1, const float2 *__restrict__ w2, int hidden, int adj0,
-                            float *__restrict__ f) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x, adj = adj0 + blockIdx.y;
-  if (idx >= FRAG32) return;
+                            float *__restrict__ f, __bf16 *__restrict__ lo) {
+  int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  const int adj = adj0 + blockIdx.y;
+  if (idx >= FRAG32) {
+    idx -= FRAG32;
+    if (!lo || idx >= FRAGLO * 8) return;
+    const int kk = idx & 7, lane = (idx >> 3) & 63, ks = (idx >> 9) % 3, mt = (idx >> 9) / 3, g = lane >> 4;
+    const int row = 16 * mt + (lane & 15), p = row >> 3, q = ks < 2 ? 1 + 4 * ks + g : 0, e = ks < 2 ? kk : 4 * kk + g;
+    float v = 0.f;
+    if (p < NPATH && e < 8) {
+      const double2 k = fold_entry64(w1, w2, hidden, adj, p, q, (row & 7) >> 1, e >> 1);
+      v = real_form(make_float2((float)(k.x - (double)(float)k.x), (float)(k.y - (double)(float)k.y)), row & 1, e & 1);
+    }
+    lo[idx] = (__bf16)v;
+    return;
+  }
   const int lane = idx & 63, ks = (idx >> 6) % KS32, mt = (idx >> 6) / KS32, g = lane >> 4;
   const int row = 16 * mt + (lane & 15), p = row >> 3;
   const int q = ks < 16 ? 1 + 4 * (ks >> 3) + g : 0, e = ks < 16 ? ks & 7 : 4 * (ks - 16) + g;
@@ -156,6 +180,8 @@ __global__ void k_nn_frag32(const float2 *__restrict__ w1, const float2 *__restr
   if (p < NPATH) v = real_form(fold_entry(w1, w2, hidden, adj, p, q, (row & 7) >> 1, e >> 1), row & 1, e & 1);
   f[adj * FRAG32 + idx] = v;
 }
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // A spinor of a field in storage class S (F32, or F64 rounded to F32).
 template <int S>
@@ -236,13 +262,23 @@ __device__ __forceinline__ void path_use(const PathIn<SIN> &in, int h, cpx<float
 //
 // Work-groups of four waves walk the 64-site blocks of both parities in the
 // hop's XCD-mapped order, `nblk` of them, and keep the fragments.
-template <int SIN, bool NT>
+//
+// LO: with the products of what K loses in FP32, on the bf16 matrix cores (lane
+// (g, n)'s eight reals of a path and colour are a 16x16x32 B operand as they stand).
+// K's rounding is the same at every site, so in the loss and the gradient it does
+// not average out: the loss at 24^3x48 is 2.2e-9 off its 64-bit value without and
+// 3.3e-11 with, the largest gradient entry on 8^4 9.3e-8 and 3.9e-8.  Four training
+// steps at 24^3x48: 3.33 / 3.41 ms.
+template <int SIN, bool NT, bool LO>
 __global__ __launch_bounds__(256, 2) void k_nn_pass_a(Geo g, const void *__restrict__ links,
-                                                      const float *__restrict__ frag, const void *__restrict__ in0,
-                                                      const void *__restrict__ in1, void *__restrict__ m,
-                                                      size_t mstride, int zb) {
+                                                      const float *__restrict__ frag, const void *__restrict__ frag_lo,
+                                                      const void *__restrict__ in0, const void *__restrict__ in1,
+                                                      void *__restrict__ m, size_t mstride, int zb) {
   __shared__ float lds_frag[FRAG32];
+  __shared__ bf16x8 lds_lo[LO ? FRAGLO : 1];
   for (int i = threadIdx.x; i < FRAG32; i += 256) lds_frag[i] = frag[i];
+  if (LO)
+    for (int i = threadIdx.x; i < FRAGLO; i += 256) lds_lo[i] = ((const bf16x8 *)frag_lo)[i];
   __syncthreads();
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & (WAVE - 1), g4 = lane >> 4, n = lane & 15;
@@ -288,6 +324,25 @@ __global__ __launch_bounds__(256, 2) void k_nn_pass_a(Geo g, const void *__restr
     for (int mt = 0; mt < MT32; ++mt)
 #pragma unroll
       for (int a = 0; a < 3; ++a) D[mt][a] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (LO) {
+#pragma unroll
+      for (int ks = 0; ks < 3; ++ks) {
+        bf16x8 af[MT32];
+#pragma unroll
+        for (int mt = 0; mt < MT32; ++mt) af[mt] = lds_lo[(mt * 3 + ks) * WAVE + lane];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          bf16x8 b;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            b[2 * r] = (__bf16)(ks < 2 ? t[ks & 1][4 * a + r].re : r == 0 ? own[0][a] : 0.f);
+            b[2 * r + 1] = (__bf16)(ks < 2 ? t[ks & 1][4 * a + r].im : r == 0 ? own[1][a] : 0.f);
+          }
+#pragma unroll
+          for (int mt = 0; mt < MT32; ++mt) D[mt][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[mt], b, D[mt][a], 0, 0, 0);
+        }
+      }
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
@@ -358,7 +413,6 @@ __global__ __launch_bounds__(256, 2) void k_nn_pass_a(Geo g, const void *__restr
 // reads for the first system are kept in LDS for the others.
 // Path field p of a system starts at p * mstride and its parity-x half at
 // x * hoff (hoff = 0: each path field holds only the parity it is used on).
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // A fragments of the real form of K (or K') over the hop pairs, bf16 hi and lo:
 // f[(((mt * 2 + ks) * 2 + hl) * 64 + lane) * 8 + kk]; row lane % 16 of M-tile mt
@@ -1330,10 +1384,11 @@ inline int nblk(size_t n) { return (int)((n + 255) / 256); }
 size_t full_bytes32(const Geo &g) { return 2 * half_bytes(g, QIRAL_F32); }
 size_t full_bytes64(const Geo &g) { return 2 * half_bytes(g, QIRAL_F64); }
 
-// The FP32 fragments of K (adj0 = 0) and / or K' of the current weights.
-hipError_t nn_frag32(const qiral_nn *nn, int adj0, int count, hipStream_t s) {
-  hipLaunchKernelGGL(k_nn_frag32, dim3(nblk(FRAG32), count), dim3(256), 0, s, nn->w, nn->w + nn->nw1, nn->hidden, adj0,
-                     nn->kfrag32);
+// The FP32 fragments of K (adj0 = 0) and / or K' of the current weights; train:
+// those of K's remainder too.
+hipError_t nn_frag32(const qiral_nn *nn, int adj0, int count, hipStream_t s, bool train = false) {
+  hipLaunchKernelGGL(k_nn_frag32, dim3(nblk(FRAG32 + (train ? FRAGLO * 8 : 0)), count), dim3(256), 0, s, nn->w,
+                     nn->w + nn->nw1, nn->hidden, adj0, nn->kfrag32, (__bf16 *)(train ? nn->kfraglo : nullptr));
   return hipGetLastError();
 }
 
@@ -1358,12 +1413,14 @@ bool paths_stream(long halves, const Geo &g) {
 }
 
 // Pass A on both parities: the path fields of the F32 or F64 full field (in0, in1).
-template <int SIO>
+template <int SIO, bool LO = false>
 void nn_pass_a(const qiral_nn *nn, const void *in0, const void *in1, bool adj, int zb, hipStream_t s) {
   const Geo &g = nn->lat->geo;
   const int wgs = std::min(2 * g.nb, 2 * 256);   // all resident: two per compute unit
-  hipLaunchKernelGGL(paths_stream(2, g) ? (k_nn_pass_a<SIO, true>) : (k_nn_pass_a<SIO, false>), dim3(wgs), dim3(256), 0, s, g, nn->lat->g32,
-                     (const float *)(nn->kfrag32 + (adj ? FRAG32 : 0)), in0, in1, nn->paths, full_bytes32(g), zb);
+  const auto kernel = paths_stream(2, g) ? k_nn_pass_a<SIO, true, LO> : k_nn_pass_a<SIO, false, LO>;
+  hipLaunchKernelGGL(kernel, dim3(wgs), dim3(256), 0, s, g, nn->lat->g32,
+                     (const float *)(nn->kfrag32 + (adj ? FRAG32 : 0)), nn->kfraglo, in0, in1, nn->paths,
+                     full_bytes32(g), zb);
 }
 
 // out = N(in) (adj = false) or N^dagger(in), folded, with the fragments of the
@@ -1447,7 +1504,7 @@ void neumann2(int hidden, double kappa, std::vector<float2> &w) {
 namespace {
 // Offsets of the network's device memory (one caller-owned buffer).
 struct NnLayout {
-  size_t w, kmat, kfrag, kfrag32, am, av, grad, part, dk, scal, paths, fv, fb, fg, loss, total;
+  size_t w, kmat, kfrag, kfrag32, kfraglo, am, av, grad, part, dk, scal, paths, fv, fb, fg, loss, total;
 };
 inline size_t al256(size_t v) { return (v + 255) / 256 * 256; }
 // Work-groups of the gradient kernel: one per 32 sites while they are few.
@@ -1463,6 +1520,7 @@ NnLayout nn_layout(const Geo &g, int hidden) {
   l.kmat = take(sizeof(float2) * 2 * NPATH * NPATH * 16);
   l.kfrag = take(2 * 4 * 2 * 2 * 64 * 8 * sizeof(__bf16));
   l.kfrag32 = take(2 * FRAG32 * sizeof(float));
+  l.kfraglo = take(FRAGLO * 8 * sizeof(__bf16));
   l.am = take(sizeof(float) * 2 * nw);
   l.av = take(sizeof(float) * 2 * nw);
   l.grad = take(sizeof(double) * 2 * nw);
@@ -1506,6 +1564,7 @@ extern "C" qiral_status qiral_nn_create(qiral_nn **out, qiral_lattice *lat, int3
   nn->kmat = (float2 *)(m + l.kmat);
   nn->kfrag = m + l.kfrag;
   nn->kfrag32 = (float *)(m + l.kfrag32);
+  nn->kfraglo = m + l.kfraglo;
   nn->am = (float *)(m + l.am);
   nn->av = (float *)(m + l.av);
   nn->grad = (double *)(m + l.grad);
@@ -1609,9 +1668,9 @@ hipError_t train_step(qiral_nn *nn, const void *src, const void *target, double 
   const dim3 gb((g.nb + 3) / 4, 2), bd(256);
   if (!have_norm) hipLaunchKernelGGL(k_norm32, dim3(nb), bd, 0, s, g, target, nn->part);
   hipLaunchKernelGGL(k_sum, dim3(1), bd, 0, s, nn->part, nb, nn->scal, (const double *)nullptr);
-  hipError_t e = nn_frag32(nn, 0, 1, s);
+  hipError_t e = nn_frag32(nn, 0, 1, s, true);
   if (e != hipSuccess) return e;
-  nn_pass_a<S_F32>(nn, src, (const char *)src + hb, false, zb, s);
+  nn_pass_a<S_F32, true>(nn, src, (const char *)src + hb, false, zb, s);
   hipLaunchKernelGGL(paths_stream(2, g) ? k_nn_pass_b_loss<true> : k_nn_pass_b_loss<false>, gb, bd, 0, s, g, nn->lat->g32, nn->paths, fs, target, nn->scal, nn->fg, zb,
                      nn->part);
   hipLaunchKernelGGL(k_sum, dim3(1), bd, 0, s, nn->part, (int)(2 * gb.x), loss_dev, nn->scal);
