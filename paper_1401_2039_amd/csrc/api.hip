@@ -143,8 +143,9 @@ __global__ __launch_bounds__(WG) void k_pack_gauge(Geo g, const double *__restri
 // side as one contiguous 24 KB piece and passes it through LDS to one lane per
 // site, whose packed accesses are contiguous over a wave as everywhere.  A lane
 // that reads its 192 bytes of the canonical field itself has its wave touch every
-// line twelve times.  Bound by memory; see canon_stream for the rates.  The LDS rows are 13 units long: a wave's reads of one component (every second
-// row, 104 words apart) then fall on different banks.
+// line twelve times.  Bound by memory; see canon_stream for the rates.  The LDS rows
+// are 13 units long: a wave's reads of one component (every second row, 104 words
+// apart) then fall on different banks.
 constexpr int PK_ROW = 13;
 
 // Parity of canonical site `lex` (x fastest, Lx even).
@@ -154,25 +155,38 @@ __device__ __forceinline__ int lex_parity(const Geo &g, int lex) {
   return (lex + (q1 - q2 * g.ly) + (q2 - t * g.lz) + t) & 1;
 }
 
-// half: 0 or 1 for that parity alone, 2 for both; parity p's packed half-field
-// starts at dst + p * hoff.
+// Both parities; parity p's packed half-field starts at dst + p * hoff.
 template <int S, int NT>
 __global__ __launch_bounds__(2 * WAVE) void k_import(Geo g, const double *__restrict__ canon, size_t canon_stride,
-                                                     void *__restrict__ dst, size_t dst_stride, size_t hoff, int half) {
+                                                     void *__restrict__ dst, size_t dst_stride, size_t hoff) {
   using R = typename SpinorIO<S>::R;
   __shared__ double2 lds[2 * WAVE * PK_ROW];
   const int r = blockIdx.x / g.nb, b = blockIdx.x - r * g.nb;
   const int l0 = 2 * WAVE * b, n = min(2 * WAVE, 2 * g.vh - l0);   // sites of the run
   const double2 *src = (const double2 *)(canon + r * canon_stride) + (size_t)l0 * 12;
-#pragma unroll
-  for (int m = 0; m < 12; ++m) {
+  auto put = [&](int m, double2 q) {
     const int i = m * 2 * WAVE + threadIdx.x, j = i / 12;
-    if (j < n && (half == 2 || lex_parity(g, l0 + j) == half))
-      lds[j * PK_ROW + (i - 12 * j)] = NT ? ld_nt(src + i) : src[i];
+    lds[j * PK_ROW + (i - 12 * j)] = q;
+  };
+  auto get = [&](int m) {
+    const double2 *at = src + m * 2 * WAVE + threadIdx.x;
+    return NT ? ld_nt(at) : *at;
+  };
+  // A whole run has all twelve loads in flight; under a test each they go one after
+  // the other: one F16S field of 24^3x48 27 / 42 us, 3 FP64 of 16^3x32 26 / 35.
+  if (n == 2 * WAVE) {
+    double2 q[12];
+#pragma unroll
+    for (int m = 0; m < 12; ++m) q[m] = get(m);
+#pragma unroll
+    for (int m = 0; m < 12; ++m) put(m, q[m]);
+  } else {
+#pragma unroll
+    for (int m = 0; m < 12; ++m)
+      if (m * 2 * WAVE + (int)threadIdx.x < 12 * n) put(m, get(m));
   }
   __syncthreads();
   const int p = threadIdx.x >> 6, lane = threadIdx.x & (WAVE - 1), s = b * WAVE + lane;
-  if (half != 2 && p != half) return;
   cpx<R> v[12];
   if (s < g.vh) {
     const double2 *row = lds + (2 * lane + (lex_parity(g, 2 * s) ^ p)) * PK_ROW;
@@ -185,6 +199,32 @@ __global__ __launch_bounds__(2 * WAVE) void k_import(Geo g, const double *__rest
   SpinorIO<S>::template store<(NT > 1)>((char *)dst + r * dst_stride + p * hoff, s, (size_t)g.nb * WAVE, v);
 }
 
+// Parity p alone: every second site of a run is skipped, so it is no contiguous
+// piece, and a lane reads its own 192 bytes, all twelve loads at once.  Through LDS,
+// each load under the test of its site's parity, this half took 42 us for one FP64
+// field of 24^3x48 and this takes 25; 12 F16S fields 390 and 235.
+template <int S>
+__global__ __launch_bounds__(WG) void k_import_half(Geo g, const double *__restrict__ canon, size_t canon_stride,
+                                                    void *__restrict__ dst, size_t dst_stride, int p, int nrhs) {
+  using R = typename SpinorIO<S>::R;
+  const size_t npad = (size_t)g.nb * WAVE;
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= npad * nrhs) return;
+  const int s = (int)(i % npad), r = (int)(i / npad);
+  cpx<R> v[12];
+  if (s < g.vh) {
+    const double2 *src = (const double2 *)(canon + r * canon_stride) + (size_t)(2 * s + (lex_parity(g, 2 * s) ^ p)) * 12;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) v[k] = cmake((R)src[k].x, (R)src[k].y);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) v[k] = cmake((R)0, (R)0);
+  }
+  SpinorIO<S>::store((char *)dst + r * dst_stride, s, npad, v);
+}
+
+// half: 0 or 1 for that parity alone, 2 for both; parity p's packed half-field
+// starts at src + p * hoff.
 template <int S, int NT>
 __global__ __launch_bounds__(2 * WAVE) void k_export(Geo g, double *__restrict__ canon, size_t canon_stride,
                                                      const void *__restrict__ src, size_t src_stride, size_t hoff,
@@ -600,11 +640,16 @@ static int canon_stream(const Geo &g, int nrhs) {
 template <int S>
 static void launch_import(const Geo &g, const double *src, void *dst, int subset, int nrhs, hipStream_t s) {
   const size_t canon_stride = (size_t)g.vh * 2 * 24;   // doubles per canonical field
-  const size_t hb = half_bytes(g, S), hoff = subset == QIRAL_FULL ? hb : 0, stride = hb + hoff;
+  const size_t hb = half_bytes(g, S);
+  if (subset != QIRAL_FULL) {
+    const dim3 grid((unsigned)((npad_of(g) * nrhs + WG - 1) / WG)), block(WG);
+    hipLaunchKernelGGL(k_import_half<S>, grid, block, 0, s, g, src, canon_stride, dst, hb, subset, nrhs);
+    return;
+  }
   const dim3 grid((unsigned)((long)g.nb * nrhs)), block(2 * WAVE);
   const int nt = canon_stream(g, nrhs);
-  hipLaunchKernelGGL(nt == 0 ? (k_import<S, 0>) : nt == 1 ? (k_import<S, 1>) : (k_import<S, 2>), grid, block, 0, s, g, src, canon_stride, dst, stride,
-                     hoff, subset);
+  const auto kernel = nt == 0 ? k_import<S, 0> : nt == 1 ? k_import<S, 1> : k_import<S, 2>;
+  hipLaunchKernelGGL(kernel, grid, block, 0, s, g, src, canon_stride, dst, 2 * hb, hb);
 }
 
 template <int S>
@@ -613,8 +658,8 @@ static void launch_export(const Geo &g, double *dst, const void *src, int subset
   const size_t hb = half_bytes(g, S), hoff = subset == QIRAL_FULL ? hb : 0, stride = hb + hoff;
   const dim3 grid((unsigned)((long)g.nb * nrhs)), block(2 * WAVE);
   const int nt = canon_stream(g, nrhs);
-  hipLaunchKernelGGL(nt == 0 ? (k_export<S, 0>) : nt == 1 ? (k_export<S, 1>) : (k_export<S, 2>), grid, block, 0, s, g, dst, canon_stride, src, stride,
-                     hoff, subset);
+  const auto kernel = nt == 0 ? k_export<S, 0> : nt == 1 ? k_export<S, 1> : k_export<S, 2>;
+  hipLaunchKernelGGL(kernel, grid, block, 0, s, g, dst, canon_stride, src, stride, hoff, subset);
 }
 
 namespace qiral {
