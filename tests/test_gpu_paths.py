@@ -299,3 +299,27 @@ def test_import_keeps_its_loads_in_flight():
                  for sub in (q.FULL, q.ODD))
     exp = _least_us(lambda: lat.export_field(buf, q.FULL, q.F16S, out=psi))
     assert imp < 1.5 * exp and half < 0.8 * imp, (imp, half, exp)
+
+
+# The streaming forms on a ragged lattice (a last block of 8 sites): 7 fields of
+# 14x10x18x22 (75 MB, the canonical side streamed) and 25 (266 MB, both sides), whole
+# and one parity at a time.  The largest of the test above is 138 MB.
+@pytest.mark.parametrize("nrhs", [7, 25])
+def test_packing_streams_ragged_fields(nrhs):
+    dims = (14, 10, 18, 22)
+    say("packing, streamed, ragged", dims, nrhs)
+    unit = torch.eye(3, dtype=torch.complex128, device="cuda").expand(W.site_shape(dims) + (4, 3, 3))
+    lat = q.Lattice(dims, 0.12, unit, lo_precs=0)
+    psi = dev(latgen.complex_gaussian(np.random.default_rng(10), (nrhs,) + W.site_shape(dims) + (3, 4)))
+    par = torch.from_numpy(W.parity_field(dims)).cuda().reshape(-1)
+    for prec, rnd in ((q.F64, lambda a: a), (q.F32, storage.round_f32), (q.F16S, storage.round_f16s)):
+        want = dev(rnd(host(psi)))
+        full = lat.import_field(psi, q.FULL, prec)
+        assert torch.equal(lat.export_field(full, q.FULL, prec, nrhs), want)
+        for p in (0, 1):
+            half = lat.import_field(psi, p, prec)
+            assert torch.equal(half.reshape(nrhs, -1), full.reshape(nrhs, 2, -1)[:, p])
+            out = torch.full_like(psi, 7.0)
+            lat.export_field(half, p, prec, nrhs, out=out)
+            o, w = out.reshape(nrhs, -1, 12), want.reshape(nrhs, -1, 12)
+            assert torch.equal(o[:, par == p], w[:, par == p]) and bool((o[:, par != p] == 7.0).all())
