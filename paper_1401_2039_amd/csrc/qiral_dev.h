@@ -147,7 +147,10 @@ template <> struct SpinorIO<S_F64> {
     (void)npad;
     const double2 *p = (const double2 *)base + (size_t)(s >> 6) * (12 * WAVE) + (s & 63);
 #pragma unroll
-    for (int k = 0; k < 12; ++k) r.q[k] = NT ? ld_nt(p + k * WAVE) : p[k * WAVE];
+    for (int k = 0; k < 12; ++k) {   // a conditional expression's temporaries take the FP64 hop past 128 registers
+      if (NT) r.q[k] = ld_nt(p + k * WAVE);
+      else r.q[k] = p[k * WAVE];
+    }
   }
   __device__ static void decode(const Raw &r, cpx<double> v[12]) {
 #pragma unroll
