@@ -731,7 +731,13 @@ extern "C" qiral_status qiral_apply_M(const qiral_lattice *lat, void *out, const
   const double k = lat->kappa;
   const int dag = (op == QIRAL_OP_DDAG || op == QIRAL_OP_SCHUR_DAG);
   if (op == QIRAL_OP_D || op == QIRAL_OP_DDAG) {
-    QIRAL_HIP(launch_D(lat, prec, dag, out, in, nrhs, s));   // full fields: [rhs][even | odd]
+    // full fields, [rhs][even | odd]; one after the other where a result lies in an
+    // earlier right-hand side's place (out n fields below in), whose input is then used up
+    const size_t fb = 2 * half_bytes(lat->geo, prec);
+    const uintptr_t i = (uintptr_t)in, o = (uintptr_t)out, all = fb * (size_t)nrhs;
+    const int step = i < o + all && o < i + all ? 1 : nrhs;
+    for (int r = 0; r < nrhs; r += step)
+      QIRAL_HIP(launch_D(lat, prec, dag, (char *)out + r * fb, (const char *)in + r * fb, step, s));
   } else {
     // S = A - kappa^2 H_oe A^-1 H_eo (S^dagger: daggered hops and site factors)
     QIRAL_HIP(launch_hop(lat, prec, dag, 0, 0, 1.0, in, tmp, nullptr, nrhs, s, dag ? CHI_AINVDAG : CHI_AINV, CHI_ONE,

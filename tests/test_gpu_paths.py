@@ -323,3 +323,22 @@ def test_packing_streams_ragged_fields(nrhs):
             lat.export_field(half, p, prec, nrhs, out=out)
             o, w = out.reshape(nrhs, -1, 12), want.reshape(nrhs, -1, 12)
             assert torch.equal(o[:, par == p], w[:, par == p]) and bool((o[:, par != p] == 7.0).all())
+
+
+@pytest.mark.parametrize("prec", [q.F64, q.F32, q.F16S], ids=["f64", "f32", "f16s"])
+def test_full_operator_into_used_up_fields(prec):
+    """D writes each field into the place of the one before it, field by field."""
+    dims, n = (4, 4, 6, 8), 3
+    say("D in place, one field on", dims, prec)
+    cfg = latgen.small_config(dims, seed=95, kind="expih", eps=0.4, nrhs=n)
+    lat = q.Lattice(dims, 0.12, cfg["U"], mu=0.35)
+    Ur, br = _rounded(cfg, prec)
+    one = q.qiral_field_bytes(dims, q.FULL, prec)
+    buf = lat.field(q.FULL, prec, n + 1)
+    buf[one:] = lat.import_field(dev(cfg["b"]), q.FULL, prec)
+    for op, ref in ((q.OP_D, W.apply_D), (q.OP_DDAG, W.apply_Ddag)):
+        work = buf.clone()
+        lat.apply_M(work[:n * one], work[one:], None, op, prec, n)
+        got = host(lat.export_field(work[:n * one].clone(), q.FULL, prec, nrhs=n))
+        for r in range(n):
+            _check(got[r], ref(Ur, 0.12, 0.35, br[r]), prec)
