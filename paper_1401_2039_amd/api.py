@@ -9,6 +9,7 @@ QiralError on a non-OK status; they compute nothing themselves.
 """
 import ctypes
 import functools
+import operator
 
 import torch
 
@@ -50,7 +51,7 @@ def _field_bytes(dims, subset, prec, nrhs):
 
 
 def qiral_field_bytes(dims, subset, prec, nrhs=1):
-    return _field_bytes(tuple(int(d) for d in dims), int(subset), int(prec), int(nrhs))
+    return _field_bytes(tuple(int(d) for d in dims), operator.index(subset), operator.index(prec), operator.index(nrhs))
 
 
 def qiral_gauge_bytes(dims, prec, recon=None):

@@ -179,3 +179,11 @@ def test_batch_rejects_learned_solvers():
                                      None) == L.ERR_UNSUPPORTED
         assert b"one lattice" in lib.qiral_last_error()
 
+
+
+def test_field_bytes_takes_whole_numbers_only():
+    """A fraction or a text for the subset, the precision or the number of fields is
+    refused, not rounded."""
+    for bad in ((L.ODD, L.F64, 1.5), (L.ODD, 1.0, 1), (0.0, L.F64, 1), (L.ODD, L.F64, "1")):
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            api.qiral_field_bytes((4, 4, 4, 4), *bad)
