@@ -349,15 +349,21 @@ static int default_nr(int prec, long items, bool solver) {
 HopCfg hop_config(const qiral_lattice *lat, int prec, long nrhs, bool solver) {
   HopCfg c;
   const long nb = lat->geo.nb;
+  // The tuner times the plain hop.  Its shape with several right-hand sides per lane
+  // and more than one group of them is none for a solver whose hops take one: CGNR on
+  // 12 FP64 sources of 24^3x48 took 182 ms with it and takes 170 (2 sources, one group:
+  // 32.5 ms with it, 33.3 without).
+  const int tnr = tuned_nr(lat, prec, (int)nrhs);
+  const bool tuned = !(solver && prec != QIRAL_F16S && tnr > 1 && nrhs > tnr);
   if (const char *e = getenv("QIRAL_HOP_NR")) c.nr = atoi(e);
-  else if (!(c.nr = tuned_nr(lat, prec, (int)nrhs))) c.nr = default_nr(prec, nb * nrhs, solver);
+  else if (!(c.nr = tuned ? tnr : 0)) c.nr = default_nr(prec, nb * nrhs, solver);
   c.nr = std::max(1, std::min(c.nr, 4));
   if (c.nr > nrhs) c.nr = (int)nrhs;
   const long nitems = nb * ((nrhs + c.nr - 1) / c.nr);
   c.t = hop_split(prec, nitems);
-  const int tt = lat->tuned_t[prec][nrhs < 4 ? nrhs : 4];
+  const int tt = tuned ? lat->tuned_t[prec][nrhs < 4 ? nrhs : 4] : 0;
   if (tt && !getenv("QIRAL_HOP_SPLIT") && hop_nr_max(prec, tt) >= 1) c.t = tt;
-  c.tile = lat->tuned_tile[prec][nrhs < 4 ? nrhs : 4];
+  c.tile = tuned ? lat->tuned_tile[prec][nrhs < 4 ? nrhs : 4] : 0;
   if (c.nr > hop_nr_max(prec, c.t)) c.t = (c.t == 1 && c.nr <= hop_nr_max(prec, 2)) ? 2 : 4;
   c.nr = std::min(c.nr, hop_nr_max(prec, c.t));   // FP64 takes at most 2
   return c;

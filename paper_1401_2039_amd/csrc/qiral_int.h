@@ -80,7 +80,8 @@ int hop_zb(const Geo &g);
 // autotuned size.
 int hop_tile(const Geo &g, int ngroups, int tuned = 0);
 int tuned_nr(const qiral_lattice *lat, int prec, int nrhs);
-// solver: for the grouped solver's hops.
+// solver: for the grouped solver's hops, which take a tuned shape only where it is
+// one of theirs.
 HopCfg hop_config(const qiral_lattice *lat, int prec, long nrhs, bool solver = false);
 // What a hop computes: see launch_hop.  p = -1: in, out and x are full fields
 // and both output parities are computed.

@@ -1,0 +1,72 @@
+"""The rules that choose a hop's launch shape are host code: a small program links the
+library and asks them, without a GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_1401_2039_amd import _lib as L
+from paper_1401_2039_amd import build
+
+pytestmark = pytest.mark.skipif(not os.path.exists(L.LIB_PATH) or
+                                (not os.path.exists(build.HIPCC) and shutil.which("hipcc") is None),
+                                reason="library not built or hipcc not available")
+
+SOURCE = r"""
+#include <cstdio>
+#include "qiral_int.h"
+using namespace qiral;
+int main() {
+  int nb, prec, nrhs, solver, nr, t, tile;
+  while (scanf("%d %d %d %d %d %d %d", &nb, &prec, &nrhs, &solver, &nr, &t, &tile) == 7) {
+    qiral_lattice lat{};
+    lat.geo.nb = nb;
+    lat.geo.vh = nb * WAVE;
+    const int i = nrhs < 4 ? nrhs : 4;
+    lat.tuned_nr[prec][i] = nr;
+    lat.tuned_t[prec][i] = t;
+    lat.tuned_tile[prec][i] = tile;
+    const HopCfg c = hop_config(&lat, prec, nrhs, solver);
+    printf("%d %d %d\n", c.nr, c.t, c.tile);
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def shapes(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, exe = d / "rules.hip", d / "rules"
+    src.write_text(SOURCE)
+    flags = [f for f in build.CFLAGS if f != "-fPIC"] + ["-I", build.CSRC]
+    lib = os.path.dirname(L.LIB_PATH)
+    r = subprocess.run([build.HIPCC, *flags, str(src), "-o", str(exe), "-L", lib, "-lqiral_hip", f"-Wl,-rpath,{lib}"],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+    def ask(*cases):
+        text = "\n".join(" ".join(str(int(v)) for v in c) for c in cases)
+        env = {k: v for k, v in os.environ.items() if not k.startswith("QIRAL_HOP_")}
+        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, env=env, timeout=60)
+        assert out.returncode == 0, out.stderr[-2000:]
+        return [tuple(int(v) for v in line.split()) for line in out.stdout.split("\n") if line]
+    return ask
+
+
+@pytest.mark.parametrize("prec,t", [(L.F64, 4), (L.F32, 4), (L.F32, 2)])
+def test_solver_hops_keep_one_right_hand_side_per_lane_on_a_tuned_handle(shapes, prec, t):
+    """A plain hop tuned to two right-hand sides per lane does not set the grouped
+    solver's shape, unless they are all there are; one tuned to one does."""
+    nb = 5184   # 24^3x48
+    plain, solver, untuned, all_in_one, one = shapes((nb, prec, 12, 0, 2, t, 8), (nb, prec, 12, 1, 2, t, 8),
+                                                     (nb, prec, 12, 1, 0, 0, 0), (nb, prec, 2, 1, 2, t, 0),
+                                                     (nb, prec, 12, 1, 1, t, 8))
+    assert plain == (2, t, 8)
+    assert solver == untuned and solver[0] == 1
+    assert all_in_one[0] == 2
+    assert one == (1, t, 8)
+
+
+def test_f16s_solver_hops_take_the_tuned_shape(shapes):
+    assert shapes((5184, L.F16S, 12, 1, 2, 4, 32)) == [(2, 4, 32)]
