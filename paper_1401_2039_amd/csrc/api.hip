@@ -331,18 +331,25 @@ namespace qiral {
 // Right-hand sides per lane of a hop that was not tuned.  Two read each link once
 // for both, but keep two thirds of the waves: while the items are few, or in a
 // solver's hops (whose links the last-level cache serves and whose epilogues read
-// more), one is faster.  One / two per lane, us:
+// more), one is faster.  The F16S hop is bound by its vector work and gains from two
+// much earlier, where the right-hand sides come in pairs (with an odd number half of
+// the last group's work is for nothing).  One / two per lane, us:
 //   S, FP64: 12 fields of 12^3x24 78 / 83, 2 of 20^3x40 118 / 123, 12 of 16^3x32
 //     248 / 249, 2 of 24^3x48 261 / 231, 12 of 20^3x40 721 / 690
 //   S, FP32: 12 of 12^3x24 40 / 42, 2 of 24^3x48 96 / 123, 4 of 24^3x48 228 / 224
-//   S, F16S: 2 of 16^3x32 20.6 / 22.3, 2 of 24^3x48 71 / 76, 12 of 16^3x32 80 / 76, 4
-//     of 24^3x48 134 / 124; D on 5 of 14x10x18x22 18.9 / 21.9
+//   S, F16S: 2 of 16^3x32 18.6 / 20.3, 5 35.1 / 37.8, 7 47.0 / 48.8, 2 of 24^3x48
+//     69 / 75; in pairs 6 of 14^3x28 28.4 / 29.3, 12 of 12^3x24 29.2 / 29.2, 8 of
+//     14^3x28 34.4 / 33.2, 6 of 16^3x32 41.1 / 39.6, 10 66.3 / 62.4, 4 of 20^3x40
+//     67 / 62; H on 4 of 20^3x40 31.9 / 29.8, D on 4 of 16^3x32 27.5 / 25.9, on 8 of
+//     12^3x24 19.0 / 19.4
 //   CGNR in ms, FP64: 12 of 12^3x24 9.7 / 11.4, 4 of 16^3x32 10.3 / 11.9, 2 of 24^3x48
 //     28.9 / 28.3, 4 52.3 / 55.9, 12 147 / 158; FP32: 3 of 20^3x40 12.3 / 13.8, 12 of
-//     24^3x48 93.5 / 97.3; F16S: 12 of 12^3x24 6.05 / 6.27, 2 of 24^3x48 12.9 / 13.7, 12
-//     of 16^3x32 14.2 / 13.8, 4 of 24^3x48 22.8 / 22.0
-static int default_nr(int prec, long items, bool solver) {
+//     24^3x48 93.5 / 97.3; F16S: 12 of 12^3x24 6.73 / 6.78, 6 of 16^3x32 8.85 / 8.98, 12
+//     of 14^3x28 10.32 / 10.30, 8 of 16^3x32 11.07 / 10.99, 10 13.37 / 13.14, 2 of
+//     24^3x48 12.9 / 13.7, 4 22.8 / 22.0
+static int default_nr(int prec, long items, long nrhs, bool solver) {
   if (solver && prec != QIRAL_F16S) return 1;
+  if (prec == QIRAL_F16S && nrhs >= 4 && nrhs % 2 == 0) return items < (solver ? 7000 : 3800) ? 1 : 2;
   return items < (prec == QIRAL_F64 ? 8000 : 11000) ? 1 : 2;
 }
 
@@ -356,7 +363,7 @@ HopCfg hop_config(const qiral_lattice *lat, int prec, long nrhs, bool solver) {
   const int tnr = tuned_nr(lat, prec, (int)nrhs);
   const bool tuned = !(solver && prec != QIRAL_F16S && tnr > 1 && nrhs > tnr);
   if (const char *e = getenv("QIRAL_HOP_NR")) c.nr = atoi(e);
-  else if (!(c.nr = tuned ? tnr : 0)) c.nr = default_nr(prec, nb * nrhs, solver);
+  else if (!(c.nr = tuned ? tnr : 0)) c.nr = default_nr(prec, nb * nrhs, nrhs, solver);
   c.nr = std::max(1, std::min(c.nr, 4));
   if (c.nr > nrhs) c.nr = (int)nrhs;
   const long nitems = nb * ((nrhs + c.nr - 1) / c.nr);

@@ -70,3 +70,14 @@ def test_solver_hops_keep_one_right_hand_side_per_lane_on_a_tuned_handle(shapes,
 
 def test_f16s_solver_hops_take_the_tuned_shape(shapes):
     assert shapes((5184, L.F16S, 12, 1, 2, 4, 32)) == [(2, 4, 32)]
+
+
+def test_f16s_right_hand_sides_go_in_pairs(shapes):
+    """An even number of F16S fields of 16^3x32 or more takes two right-hand sides per
+    lane, an odd number or two of them one (per-lane numbers, untuned)."""
+    nb = 1024   # 16^3x32
+    got = shapes(*((nb, L.F16S, n, 0, 0, 0, 0) for n in (1, 2, 3, 4, 5, 6, 8, 10, 12)))
+    assert [c[0] for c in got] == [1, 1, 1, 2, 1, 2, 2, 2, 2]
+    got = shapes(*((nb, L.F16S, n, 1, 0, 0, 0) for n in (4, 6, 8, 10, 12)))
+    assert [c[0] for c in got] == [1, 1, 2, 2, 2]
+    assert shapes((324, L.F16S, 8, 0, 0, 0, 0))[0][0] == 1   # 12^3x24: too few items
