@@ -400,6 +400,23 @@ bool hop_stream(const Geo &g, int prec, long nrhs, long ngroups) {
 //   3 F32 fields of 24^3x48 through S: 207 / 172 us; 12: 640 / 621 us
 bool out_stream(size_t bytes, int nsys) { return bytes >= (nsys > 1 ? 16e6 : 80e6); }
 
+// Several groups of right-hand sides stream from 16 MB on, one group with its links;
+// neither while the next launch finds the output in the last-level cache (one field's
+// line, 80 MB).  Cached / streamed, us:
+//   the next launch reads it, S: 5 F32 of 16^3x32 (31 MB) 47.0 / 47.7, 12 FP64 of
+//     12^3x24 (48 MB) 71.8 / 75.3, 2 FP64 of 20^3x40 (61 MB) 112.9 / 115.5, 12 F32 of
+//     16^3x32 (75 MB) 111.4 / 113.6, 5 F32 of 20^3x40 (77 MB) 124.7 / 128.7; 3 FP64 of
+//     20^3x40 (92 MB) 174.1 / 171.3, 3 F32 of 24^3x48 (95 MB) 202 / 171, 8 F32 of
+//     20^3x40 (123 MB) 211 / 205
+//   it does not: S on 4 FP64 of 12^3x24 (16 MB) 31.4 / 31.3, D on 2 FP64 of 16^3x32
+//     (25 MB a parity) 46.0 / 45.5, H on 3 (38 MB) 30.8 / 30.1, on 4 F32 of 24^3x48
+//     (127 MB) 109 / 78.5, D on 5 F32 of 20^3x40 (77 MB a parity) 140 / 126
+// D's both parities count as one here: doubling its bytes changed none of 13 cases.
+bool op_out_stream(size_t bytes, int ngroups, bool nt, bool reread) {
+  if (reread && !out_stream(bytes, 1)) return false;
+  return ngroups > 1 ? bytes >= 16e6 : nt;
+}
+
 int vec_stream(size_t bytes, int nsys, bool same_lattice) {
   if (nsys == 1) return bytes >= 48e6;
   if (bytes < 16e6) return 0;
@@ -473,11 +490,7 @@ static hipError_t launch_hop_ttt(const HopCfg &c, const qiral_lattice *lat, cons
   const long nitems = ntile * tile * ((h.nrhs + NR - 1) / NR);
   const int nwg = (int)((nitems * T + 3) / 4);
   const dim3 grid(nwg, h.p < 0 ? 2 : 1), block(WG);
-  // several groups of right-hand sides: the rule of the solvers' vectors; one
-  // group: with its links, unless the next launch reads the output while the
-  // last-level cache still holds it
-  const size_t ob = hb * (size_t)h.nrhs;
-  const int ont = (h.nrhs + NR - 1) / NR > 1 ? out_stream(ob, h.nrhs) : NT && !(h.reread && !out_stream(ob, 1));
+  const int ont = op_out_stream(hb * (size_t)h.nrhs, (h.nrhs + NR - 1) / NR, NT, h.reread);
 #define QARGS g, gauge, h.in, h.out, h.x, fstride, h.nrhs, h.p, hb, h.a, tile, zb, h.chio, h.chix, tmu, ont
   if (!h.dagger) {
     if (h.epi == 0) hipLaunchKernelGGL((k_hop<S, L, false, 0, T, NR, NT>), grid, block, 0, h.st, QARGS);

@@ -67,6 +67,10 @@ bool hop_stream(const Geo &g, int prec, long nrhs, long ngroups);
 // Streaming stores of a hop's output that is `bytes` over all of nsys systems
 // and that later launches read.
 bool out_stream(size_t bytes, int nsys);
+// Streaming stores of an operator call's hop whose output is `bytes` over its ngroups
+// groups of right-hand sides; nt: its link loads stream, reread: the next launch
+// reads the output.
+bool op_out_stream(size_t bytes, int ngroups, bool nt, bool reread);
 // Streaming level of the vector kernels of a solve, one of whose vectors is
 // `bytes` over its nsys systems: 1: the accesses that no cache keeps until the
 // next (the solution, and a vector's last read before it is overwritten); 2: all

@@ -34,11 +34,10 @@ int main() {
 """
 
 
-@pytest.fixture(scope="module")
-def shapes(tmp_path_factory):
-    d = tmp_path_factory.mktemp("rules")
+def _program(d, source):
+    """Builds `source` against the library; a function from cases to rows of numbers."""
     src, exe = d / "rules.hip", d / "rules"
-    src.write_text(SOURCE)
+    src.write_text(source)
     flags = [f for f in build.CFLAGS if f != "-fPIC"] + ["-I", build.CSRC]
     lib = os.path.dirname(L.LIB_PATH)
     r = subprocess.run([build.HIPCC, *flags, str(src), "-o", str(exe), "-L", lib, "-lqiral_hip", f"-Wl,-rpath,{lib}"],
@@ -52,6 +51,11 @@ def shapes(tmp_path_factory):
         assert out.returncode == 0, out.stderr[-2000:]
         return [tuple(int(v) for v in line.split()) for line in out.stdout.split("\n") if line]
     return ask
+
+
+@pytest.fixture(scope="module")
+def shapes(tmp_path_factory):
+    return _program(tmp_path_factory.mktemp("rules"), SOURCE)
 
 
 @pytest.mark.parametrize("prec,t", [(L.F64, 4), (L.F32, 4), (L.F32, 2)])
@@ -81,3 +85,26 @@ def test_f16s_right_hand_sides_go_in_pairs(shapes):
     got = shapes(*((nb, L.F16S, n, 1, 0, 0, 0) for n in (4, 6, 8, 10, 12)))
     assert [c[0] for c in got] == [1, 1, 2, 2, 2]
     assert shapes((324, L.F16S, 8, 0, 0, 0, 0))[0][0] == 1   # 12^3x24: too few items
+
+
+STREAMING = r"""
+#include <cstdio>
+#include "qiral_int.h"
+using namespace qiral;
+int main() {
+  double mb;
+  int groups, nt, reread;
+  while (scanf("%lf %d %d %d", &mb, &groups, &nt, &reread) == 4)
+    printf("%d\n", (int)op_out_stream((size_t)(mb * 1e6), groups, nt, reread));
+}
+"""
+
+
+def test_an_intermediate_that_fits_the_cache_is_kept_there(tmp_path):
+    """Schur's intermediate over several groups of right-hand sides is streamed only
+    where the last-level cache would not keep it; one group as its links."""
+    ask = _program(tmp_path, STREAMING)
+    several = ask((31, 6, 0, 1), (75, 6, 0, 1), (95, 2, 0, 1), (15, 6, 0, 0), (38, 2, 0, 0))
+    assert [v for (v,) in several] == [0, 0, 1, 0, 1]
+    one = ask((64, 1, 1, 1), (64, 1, 1, 0), (201, 1, 1, 1), (25, 1, 0, 0))
+    assert [v for (v,) in one] == [0, 1, 1, 0]
