@@ -385,7 +385,7 @@ bool hop_stream(const Geo &g, int prec, long nrhs, long ngroups) {
   return bytes > 128e6;   // half the 256 MB last-level cache
 }
 
-// Both sides of these rules, in ms per FP64 CGNR solve unless said otherwise
+// Both sides of the solvers' rules, in ms per FP64 CGNR solve unless said otherwise
 // (streaming stores of the hops' outputs off / on, then the vector kernels'
 // level 0 / 1 / 2 with the better of them):
 //   one system, 20^3x40 (31 MB a vector): 8.72 / 9.14, 8.72 / 8.81 / 8.86
@@ -397,8 +397,21 @@ bool hop_stream(const Geo &g, int prec, long nrhs, long ngroups) {
 //   12 of 24^3x48 (764 MB): 163.9 / 162.5 / 159.5; FP32 102.8 / 101.6 / 99.3;
 //   F16S 69.9 / 68.6 / 66.7
 //   8 lattices of 4 sizes, FP32 (48 MB): 14.35 (off, 0), 13.6 (on, 1), 13.2 (on, 2)
-//   3 F32 fields of 24^3x48 through S: 207 / 172 us; 12: 640 / 621 us
-bool out_stream(size_t bytes, int nsys) { return bytes >= (nsys > 1 ? 16e6 : 80e6); }
+// Systems on lattices of their own do not meet in the cache as those of one lattice do
+// (whose links they share).  Stores off / on, then level 0 / 1 / 2, stores off:
+//   12^3x24 with 16^3x32, FP64 (17 MB): 5.86 / 5.98, 5.72 / 5.76 / 5.83, BiCGStab 2.99 /
+//     3.04 / 3.15; 5 of 12^3x24 (20 MB) 6.58 / 6.71, 6.62 / 6.50 / 6.56
+//   4 of 16^3x32, FP32 (25 MB): 9.05 / 9.09, 9.09 / 8.90 / 9.02
+//   4 of two sizes, FP64 (33 MB): 9.53 / 9.50, 10.04 / 9.45 / 9.51, BiCGStab 5.33 / 5.10 /
+//     4.99; 3 of three sizes, FP32 (33 MB), all stores / none: level 2 12.51 / - , level 1
+//     - / 12.75
+//   6 of 16^3x32, FP32 (38 MB): 12.97 / 12.80, 13.89 / 13.37 / 12.92
+//   20^3x40 with 16^3x32, FP64 (43 MB): 13.55 / 13.06, 13.78 / 13.06 / 13.04
+// Vectors of several right-hand sides of one lattice, level 0 / 1: 3 FP32 of 16^3x32 (19
+// MB) 6.40 / 6.28, 2 FP64 (25 MB) 6.96 / 6.86, 2 FP32 of 20^3x40 (31 MB) 10.06 / 9.97
+bool out_stream(size_t bytes, int nsys, bool same_lattice) {
+  return bytes >= (nsys == 1 ? 80e6 : same_lattice ? 16e6 : 30e6);
+}
 
 // Several groups of right-hand sides stream from 16 MB on, one group with its links;
 // neither while the next launch finds the output in the last-level cache (one field's
@@ -413,14 +426,14 @@ bool out_stream(size_t bytes, int nsys) { return bytes >= (nsys > 1 ? 16e6 : 80e
 //     (127 MB) 109 / 78.5, D on 5 F32 of 20^3x40 (77 MB a parity) 140 / 126
 // D's both parities count as one here: doubling its bytes changed none of 13 cases.
 bool op_out_stream(size_t bytes, int ngroups, bool nt, bool reread) {
-  if (reread && !out_stream(bytes, 1)) return false;
+  if (reread && !out_stream(bytes, 1, true)) return false;
   return ngroups > 1 ? bytes >= 16e6 : nt;
 }
 
 int vec_stream(size_t bytes, int nsys, bool same_lattice) {
   if (nsys == 1) return bytes >= 48e6;
-  if (bytes < 16e6) return 0;
-  return bytes >= 200e6 || !same_lattice ? 2 : 1;
+  if (bytes < 17e6) return 0;
+  return bytes >= (same_lattice ? 200e6 : 30e6) ? 2 : 1;
 }
 
 bool zb_valid(const Geo &g, int zb) {

@@ -64,9 +64,9 @@ int hop_split(int prec, long nwork);
 // sides (several groups re-read each tile's links from the cache).
 // QIRAL_HOP_NT=0|1 overrides.
 bool hop_stream(const Geo &g, int prec, long nrhs, long ngroups);
-// Streaming stores of a hop's output that is `bytes` over all of nsys systems
-// and that later launches read.
-bool out_stream(size_t bytes, int nsys);
+// Streaming stores of the hops' output in a solve, `bytes` over all of its nsys
+// systems (right-hand sides of one lattice, or lattices of their own).
+bool out_stream(size_t bytes, int nsys, bool same_lattice);
 // Streaming stores of an operator call's hop whose output is `bytes` over its ngroups
 // groups of right-hand sides; nt: its link loads stream, reread: the next launch
 // reads the output.

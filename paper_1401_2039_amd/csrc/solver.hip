@@ -361,8 +361,8 @@ qiral_status run_solve(qiral_lattice *owner, const std::vector<SysIn> &sys, cons
     vec_64 += half_bytes(sys[i].lat->geo, QIRAL_F64);
   }
   L.vec = vec_stream(vec_it, nsys, same_lattice);
-  L.ont = out_stream(vec_it, nsys);
-  L.ont64 = out_stream(vec_64, nsys);
+  L.ont = out_stream(vec_it, nsys, same_lattice);
+  L.ont64 = out_stream(vec_64, nsys, same_lattice);
   L.stream = s;
 
   // ---- inputs

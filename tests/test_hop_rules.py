@@ -108,3 +108,25 @@ def test_an_intermediate_that_fits_the_cache_is_kept_there(tmp_path):
     assert [v for (v,) in several] == [0, 0, 1, 0, 1]
     one = ask((64, 1, 1, 1), (64, 1, 1, 0), (201, 1, 1, 1), (25, 1, 0, 0))
     assert [v for (v,) in one] == [0, 1, 1, 0]
+
+
+SOLVE_STREAMING = r"""
+#include <cstdio>
+#include "qiral_int.h"
+using namespace qiral;
+int main() {
+  double mb;
+  int nsys, same;
+  while (scanf("%lf %d %d", &mb, &nsys, &same) == 3)
+    printf("%d %d\n", (int)out_stream((size_t)(mb * 1e6), nsys, same), vec_stream((size_t)(mb * 1e6), nsys, same));
+}
+"""
+
+
+def test_small_batches_of_lattices_stay_cached(tmp_path):
+    """(streamed hop outputs, level of the vector kernels) of a solve, by the bytes of a
+    vector over its systems: lattices of their own stream everything from 30 MB only."""
+    ask = _program(tmp_path, SOLVE_STREAMING)
+    assert ask((16, 2, 0), (25, 4, 0), (33, 4, 0), (38, 6, 0), (48, 8, 0)) == [(0, 0), (0, 1), (1, 2), (1, 2), (1, 2)]
+    assert ask((12, 3, 1), (19, 3, 1), (48, 12, 1), (382, 12, 1)) == [(0, 0), (1, 1), (1, 1), (1, 2)]
+    assert ask((31, 1, 1), (64, 1, 1), (100, 1, 1)) == [(0, 0), (0, 1), (1, 1)]
