@@ -1438,23 +1438,24 @@ hipError_t nn_apply_folded(const qiral_nn *nn, void *out0, void *out1, const voi
   const size_t fs = full_bytes32(g), hb = fs / 2;
   const float2 *K = nn->kmat + (adj ? NPATH * NPATH * 16 : 0);
   const int zb = hop_zb(g);   // the hops' z-tiles: neighbours stay in one XCD's L2
+  const dim3 blocks((g.nb + 3) / 4, par >= 0 ? 1 : 2), wg(256);
   if (par >= 0) {
     // path field p is the one parity it is used on: m_0 on par, m_1..m_8 on 1 - par
     void *m = mbuf ? mbuf : nn->paths;
-    const bool nt = paths_stream(nsys, g);
-    hipLaunchKernelGGL(nt ? (k_nn_pass_a_mfma<SIO, true>) : (k_nn_pass_a_mfma<SIO, false>), dim3(g.nb, 2), dim3(256), 0, s, g, nn->lat->g32, K,
+    const bool nt = paths_stream(nsys, g), multi = nsys > 1;
+    const auto pass_a = nt ? k_nn_pass_a_mfma<SIO, true> : k_nn_pass_a_mfma<SIO, false>;
+    const auto pass_b = multi ? (nt ? k_nn_pass_b<SIO, true, true> : k_nn_pass_b<SIO, true, false>)
+                              : (nt ? k_nn_pass_b<SIO, false, true> : k_nn_pass_b<SIO, false, false>);
+    hipLaunchKernelGGL(pass_a, dim3(g.nb, 2), wg, 0, s, g, nn->lat->g32, K,
                        (const bf16x8 *)nn->kfrag + (adj ? 4 * 2 * 2 * WAVE : 0), par ? in1 : in0, iostride, m, hb,
                        (size_t)0, NPATH * hb, nsys, par, zb);
-    if (nsys > 1)
-      hipLaunchKernelGGL(nt ? (k_nn_pass_b<SIO, true, true>) : (k_nn_pass_b<SIO, true, false>), dim3((g.nb + 3) / 4, 1), dim3(256), 0, s, g, nn->lat->g32,
-                         (const void *)m, hb, (size_t)0, NPATH * hb, out0, out1, iostride, nsys, par, zb);
-    else
-      hipLaunchKernelGGL(nt ? (k_nn_pass_b<SIO, false, true>) : (k_nn_pass_b<SIO, false, false>), dim3((g.nb + 3) / 4, 1), dim3(256), 0, s, g, nn->lat->g32,
-                         (const void *)m, hb, (size_t)0, NPATH * hb, out0, out1, (size_t)0, 1, par, zb);
+    hipLaunchKernelGGL(pass_b, blocks, wg, 0, s, g, nn->lat->g32, (const void *)m, hb, (size_t)0, NPATH * hb, out0,
+                       out1, multi ? iostride : (size_t)0, nsys, par, zb);
   } else {
+    const auto pass_b = paths_stream(2, g) ? k_nn_pass_b<SIO, false, true> : k_nn_pass_b<SIO, false, false>;
     nn_pass_a<SIO>(nn, in0, in1, adj, zb, s);
-    hipLaunchKernelGGL(paths_stream(2, g) ? (k_nn_pass_b<SIO, false, true>) : (k_nn_pass_b<SIO, false, false>), dim3((g.nb + 3) / 4, 2), dim3(256), 0, s, g, nn->lat->g32,
-                       (const void *)nn->paths, fs, hb, (size_t)0, out0, out1, (size_t)0, 1, par, zb);
+    hipLaunchKernelGGL(pass_b, blocks, wg, 0, s, g, nn->lat->g32, (const void *)nn->paths, fs, hb, (size_t)0, out0,
+                       out1, (size_t)0, 1, par, zb);
   }
   return hipGetLastError();
 }
@@ -1671,8 +1672,8 @@ hipError_t train_step(qiral_nn *nn, const void *src, const void *target, double 
   hipError_t e = nn_frag32(nn, 0, 1, s, true);
   if (e != hipSuccess) return e;
   nn_pass_a<S_F32, true>(nn, src, (const char *)src + hb, false, zb, s);
-  hipLaunchKernelGGL(paths_stream(2, g) ? k_nn_pass_b_loss<true> : k_nn_pass_b_loss<false>, gb, bd, 0, s, g, nn->lat->g32, nn->paths, fs, target, nn->scal, nn->fg, zb,
-                     nn->part);
+  const auto pass_b = paths_stream(2, g) ? k_nn_pass_b_loss<true> : k_nn_pass_b_loss<false>;
+  hipLaunchKernelGGL(pass_b, gb, bd, 0, s, g, nn->lat->g32, nn->paths, fs, target, nn->scal, nn->fg, zb, nn->part);
   hipLaunchKernelGGL(k_sum, dim3(1), bd, 0, s, nn->part, (int)(2 * gb.x), loss_dev, nn->scal);
   hipLaunchKernelGGL(k_nn_dk, dim3(nwg), bd, 0, s, g, nn->lat->g32, nn->fg, src, zb, nn->part);
   hipLaunchKernelGGL(k_nn_dk_sum, dim3(DK_VALUES / WAVE), bd, 0, s, nn->part, nwg, nn->dk);

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(WG, HOP_MIN_WAVES(S, T, NR)) void k_hop_sys(const S
 constexpr int T64 = 4;
 using Lds64 = HopLds<T64, 1, double>;
 
-// The `chunk` consecutive items of an update kernel's work-group: calls
+// The `chunk` consecutive items of a work-group of k_hop_upd: calls
 // each(item) for those whose system has an update pending.  Most iterations have
 // none, and a work-group then only has to find that out: for 12 systems at
 // 24^3x48, 62208 work-groups of one item of k_hop_upd took 42 us to come and go,
@@ -86,23 +86,25 @@ __device__ __forceinline__ void update_items(const SysDesc *sdesc, const uint32_
 
 // T64 = A^-1 H_eo (XH + X): the hop of the current solution for the FP64 residual.
 // Two waves per SIMD: held to three its sums come a colour at a time and it runs
-// 1006 instead of 870 us (12 systems at 24^3x48).
+// 1006 instead of 870 us (12 systems at 24^3x48).  One item a work-group: those of a
+// chunk wait for each other (870 -> 1000 us), as much as the idle launches save.
 template <bool HASLO>
 __global__ __launch_bounds__(WG, 2) void k_hop_sum(const SysDesc *__restrict__ sdesc,
-                                                   const uint32_t *__restrict__ work, int nwork, int chunk) {
+                                                   const uint32_t *__restrict__ work, int nwork) {
+  static_assert(WG / WAVE == T64, "one work item a work-group");
   __shared__ Lds64::V lds[Lds64::VECS];
-  update_items(sdesc, work, nwork, chunk, [&](const Item &it) {
-    const SysDesc &d = sdesc[it.sys];
-    const bool site_ok = it.s < d.g.vh;
-    cpx<double> acc[1][12];
-    SumLd ld{d.f[F_XH], HASLO ? d.f[F_X] : nullptr, d.npad};
-    hop_wave<L_F64R18, false, T64, false>(d.g, d.g64, ld, site_ok ? it.s : 0, 0, it.grp, acc);
-    wave_combine<T64, 1>(acc, it.slot, it.grp, lds);
-    if (site_ok && it.grp == 0) {
-      apply_chi(acc[0], CHI_AINV, d.tmu);
-      SpinorIO<S_F64>::store(d.f[F_T64], it.s, d.npad, acc[0]);
-    }
-  });
+  const Item it = fetch_item<T64>(work, nwork);
+  const SysDesc &d = sdesc[it.sys];
+  if (!it.active || !(d.st->status & ST_UPDATE)) return;   // uniform
+  const bool site_ok = it.s < d.g.vh;
+  cpx<double> acc[1][12];
+  SumLd ld{d.f[F_XH], HASLO ? d.f[F_X] : nullptr, d.npad};
+  hop_wave<L_F64R18, false, T64, false>(d.g, d.g64, ld, site_ok ? it.s : 0, 0, it.grp, acc);
+  wave_combine<T64, 1>(acc, it.slot, it.grp, lds);
+  if (site_ok && it.grp == 0) {
+    apply_chi(acc[0], CHI_AINV, d.tmu);
+    SpinorIO<S_F64>::store(d.f[F_T64], it.s, d.npad, acc[0]);
+  }
 }
 
 // Reliable update on the odd sites (upd_site), with its sums.  Three waves per
@@ -299,15 +301,13 @@ void hop_sys(const Launch &l, int prec, bool dag, int epi, int fi, int fo, int f
 
 // Items per work-group of k_hop_upd: four while there are many times more than
 // the card holds, one where each should have its own (8^4 in FP32 with four: 3%
-// slower).  k_hop_sum takes one: with two waves per SIMD the items of a chunk
-// wait for each other (870 -> 1000 us), as much as the idle launches save.
+// slower).
 static int upd_chunk(const Launch &l) { return l.nwork >= 8192 ? 4 : 1; }
 
 void hop_sum(const Launch &l, bool haslo) {
-  const int c = 1;
-  const dim3 g(l.nwork), b(WG);
-  if (haslo) hipLaunchKernelGGL((k_hop_sum<true>), g, b, 0, l.stream, l.desc, l.work, l.nwork, c);
-  else hipLaunchKernelGGL((k_hop_sum<false>), g, b, 0, l.stream, l.desc, l.work, l.nwork, c);
+  const dim3 g = grid_of(l.nwork, T64), b(WG);
+  if (haslo) hipLaunchKernelGGL((k_hop_sum<true>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
+  else hipLaunchKernelGGL((k_hop_sum<false>), g, b, 0, l.stream, l.desc, l.work, l.nwork);
 }
 
 void hop_upd(const Launch &l, int prec, bool bicg) {
