@@ -206,8 +206,10 @@ qiral_status qiral_apply_M(const qiral_lattice *lat, void *out, const void *in, 
  * right-hand sides per lane 1..4, FP64 1..2, FP32 on 2 waves 1..2, 1 wave 1; and,
  * when that leaves several groups of right-hand sides, the traversal tile of
  * 8, 16, 32 or 64 blocks that each group sweeps before the next one re-reads its
- * links) by timing each candidate on the stream; later hops and solves on this
- * handle use the fastest.  in and out are two distinct packed half-fields of precision prec
+ * links) by timing each candidate on the stream; later hops on this handle use the
+ * fastest, and solves too (F64 and F32 ones, whose hops take one right-hand side per
+ * lane, unless it takes several in more than one group).  in and out are two distinct
+ * packed half-fields of precision prec
  * and nrhs fields (qiral_field_bytes(dims, QIRAL_EVEN, prec, nrhs) bytes each)
  * owned by the caller; in is zeroed, out overwritten.  If the environment
  * variable QIRAL_TUNE_CACHE names a file, the result is looked up there first

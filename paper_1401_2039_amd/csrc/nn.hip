@@ -254,21 +254,22 @@ __device__ __forceinline__ void path_use(const PathIn<SIN> &in, int h, cpx<float
 // the four), so nothing passes through LDS but K's fragments, read there by
 // every wave.  The accumulator rows of lane (g, n) are two complex spin
 // components of one path, colour and site, a float4 unit of the spinor layout,
-// and are stored as they are, as streaming stores (the nine fields are far
-// larger than a cache keeps until pass B reads them once; the same holds for
-// k_nn_pass_a_mfma).  At 24^3x48 with the F32 input: 275 us, 150 of them the
-// products at the full FP32 MFMA rate (the vector-ALU form, two waves per block
-// sweeping the input paths for five and four output paths, took 441).
+// and are stored as they are.  NT: as streaming stores (and streaming loads in pass
+// B), where the nine fields are more than a cache keeps until pass B reads them
+// once; here and in k_nn_pass_a_mfma, see paths_stream.  At 24^3x48 with the F32
+// input, streamed: 293 us, 150 of them the products at the full FP32 MFMA rate (the
+// vector-ALU form, two waves per block sweeping the input paths for five and four
+// output paths, took 441).
 //
 // Work-groups of four waves walk the 64-site blocks of both parities in the
-// hop's XCD-mapped order, `nblk` of them, and keep the fragments.
+// hop's XCD-mapped order and keep the fragments.
 //
 // LO: with the products of what K loses in FP32, on the bf16 matrix cores (lane
 // (g, n)'s eight reals of a path and colour are a 16x16x32 B operand as they stand).
 // K's rounding is the same at every site, so in the loss and the gradient it does
 // not average out: the loss at 24^3x48 is 2.2e-9 off its 64-bit value without and
-// 3.3e-11 with, the largest gradient entry on 8^4 9.3e-8 and 3.9e-8.  Four training
-// steps at 24^3x48: 3.33 / 3.41 ms.
+// 3.3e-11 with, the largest gradient entry on 8^4 9.3e-8 and 3.9e-8.  299 us instead
+// of 293 at 24^3x48.
 template <int SIN, bool NT, bool LO>
 __global__ __launch_bounds__(256, 2) void k_nn_pass_a(Geo g, const void *__restrict__ links,
                                                       const float *__restrict__ frag, const void *__restrict__ frag_lo,
@@ -555,9 +556,10 @@ __global__ __launch_bounds__(256, 3) void k_nn_pass_a_mfma(Geo g, const void *__
 }
 
 // acc = sum_p (T_p m_p)(x) at site x = (px, c.s) of the path fields m.  Each
-// spinor of m is read once in the whole pass: streaming loads, which took pass B
-// over both parities at 24^3x48 from 190 to 131 us (6.8 TB/s) and the lockstep
-// solver's pass over 12 systems from 1100 to 923 us.
+// spinor of m is read once in the whole pass.  NT: by streaming loads, which took
+// pass B over both parities at 24^3x48 from 190 to 131 us (6.8 TB/s) and the lockstep
+// solver's pass over 12 systems from 1100 to 921 us; smaller fields are cached
+// (paths_stream).
 template <bool NT>
 __device__ __forceinline__ void path_sum(const Geo &g, const void *links, const char *m, size_t mstride, size_t hoff,
                                          size_t npad, const SiteC &c, int px, cpx<float> acc[12]) {
@@ -670,8 +672,9 @@ __global__ __launch_bounds__(256) void k_nn_pass_b_loss(Geo g, const void *__res
 // with four waves for each of the two, and two LDS buffers, was 15% slower).
 // FP32 sums run over 32 products (the 32 sites of one colour) and go on in FP64: the
 // gradient's rms error against 64 bits on 8^4 (first layer, 8 channels) is 3.3e-8,
-// 3.6e-8 with runs of 96 and 4.0e-8 in the layers' own gradient kernels.  Four
-// training steps at 24^3x48: 3.51 ms, 3.41 with runs of 96, 3.62 with 16.
+// 3.6e-8 with runs of 96 and 4.0e-8 in the layers' own gradient kernels.  The kernel
+// takes 376 us at 24^3x48; four training steps 3.51 ms, 3.41 with runs of 96, 3.62
+// with 16.
 constexpr int DK_RUN = 2;   // (colour, 16 sites) steps of an FP32 sum
 constexpr int DK_RS = 100, DK_PS = 8 * DK_RS + 16, DK_FS = NPATH * DK_PS;   // strides: real, path, field
 __global__ __launch_bounds__(256, 2) void k_nn_dk(Geo g, const void *__restrict__ links, const void *__restrict__ gf,
@@ -1424,8 +1427,9 @@ void nn_pass_a(const qiral_nn *nn, const void *in0, const void *in1, bool adj, i
 }
 
 // out = N(in) (adj = false) or N^dagger(in), folded, with the fragments of the
-// last nn_fold (nn_frag32 suffices for par < 0).  SIO: storage of in and out (packed F32 or F64 fields), given as
-// half-fields (in0, in1) and (out0, out1).  par >= 0: in is zero off parity par
+// last nn_fold (nn_frag32 suffices for par < 0).  SIO: storage of in and out (packed
+// F32 or F64 fields), given as half-fields (in0, in1) and (out0, out1).  par >= 0: in
+// is zero off parity par
 // (in0 or in1 is then not read) and only that parity of out is written, and
 // pass A runs on bf16 MFMA (about 1e-5 relative; the flexible solvers only).
 // There nsys systems may go through in one pass each: inputs and outputs

@@ -12,12 +12,15 @@ constexpr int SOLO_BLOCKS = 4;
 // The line of a solve: the work-group does two blocks at a time, so its
 // iteration grows by the hops of two blocks (about 20 us for CGNR in FP64) where
 // the grouped solver's stays at its launches' latency, and grows with the number
-// of systems instead.  Grouped / one work-group, us a solve, in FP64 for one
-// source unless said otherwise:
-//   4^4 (2 blocks): CGNR 1650 / 1090, BiCGStab 950 / 523
-//   4^3x6 (3): CGNR 1813 / 1726
-//   4^3x8 (4): CGNR 1820 / 1953, CRNR 1942 / 2141, BiCGStab 1014 / 912, CGNR in
-//     F32 1793 / 1579, F16S 1827 / 1715, 5 sources 2362 / 2003
+// of systems instead.  Grouped / one work-group, us a solve from a Gaussian source on
+// links near 1, kappa 0.12, in FP64 for one source unless said otherwise:
+//   4^4 (2 blocks): CGNR 1950 / 1160, BiCGStab 1010 / 564, CRNR 2000 / 1273
+//   4^3x6 (3): CGNR 2057 / 1908, CRNR 2117 / 2069
+//   4^3x8 (4): BiCGStab 1076 / 998, CGNR in F32 2117 / 1719, F16S 2220 / 1936, 4 sources
+//     2244 / 2235, 5 sources 2307 / 2238, CRNR 4 sources 2386 / 2452
+// and on other links, before the work-group's steps were inlined (which took 2 to 9%
+// off its times):
+//   4^3x8 (4): CGNR 1820 / 1953, CRNR 1942 / 2141
 //   4^2x6x8 (6): CGNR 1919 / 2905, 12 sources 2678 / 2926
 inline int solo_line(int nsys, bool fp64, bool bicgstab) { return fp64 && !bicgstab && nsys < 4 ? 3 : SOLO_BLOCKS; }
 

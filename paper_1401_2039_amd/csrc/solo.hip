@@ -11,8 +11,8 @@
 // bit for bit in FP64 (in the reduced precisions up to the hop's wave split).
 // What bounds it is the chain of one compute unit: loads, about 500 FP64
 // instructions a wave, the combine in LDS and a store's acknowledgement in each
-// of the four hops of an iteration.  FP64 CGNR on 4^4: 1.65 -> 1.09 ms a solve;
-// see solo_line for where it pays.
+// of the four hops of an iteration.  See solo_line for the times of both and where
+// it pays.
 #include "qiral_int.h"
 #include "solver_steps.h"
 #include "solo.h"
