@@ -257,9 +257,9 @@ __device__ __forceinline__ void path_use(const PathIn<SIN> &in, int h, cpx<float
 // and are stored as they are.  NT: as streaming stores (and streaming loads in pass
 // B), where the nine fields are more than a cache keeps until pass B reads them
 // once; here and in k_nn_pass_a_mfma, see paths_stream.  At 24^3x48 with the F32
-// input, streamed: 293 us, 150 of them the products at the full FP32 MFMA rate (the
-// vector-ALU form, two waves per block sweeping the input paths for five and four
-// output paths, took 441).
+// input, streamed: 255 to 325 us, as the clock is, 150 of them the products at the full
+// FP32 MFMA rate (the vector-ALU form, two waves per block sweeping the input paths
+// for five and four output paths, took 441).
 //
 // Work-groups of four waves walk the 64-site blocks of both parities in the
 // hop's XCD-mapped order and keep the fragments.
@@ -268,8 +268,8 @@ __device__ __forceinline__ void path_use(const PathIn<SIN> &in, int h, cpx<float
 // (g, n)'s eight reals of a path and colour are a 16x16x32 B operand as they stand).
 // K's rounding is the same at every site, so in the loss and the gradient it does
 // not average out: the loss at 24^3x48 is 2.2e-9 off its 64-bit value without and
-// 3.3e-11 with, the largest gradient entry on 8^4 9.3e-8 and 3.9e-8.  299 us instead
-// of 293 at 24^3x48.
+// 3.3e-11 with, the largest gradient entry on 8^4 9.3e-8 and 3.9e-8.  The products take
+// a twelfth of the FP32 ones' time: 269 us over many steps at 24^3x48.
 template <int SIN, bool NT, bool LO>
 __global__ __launch_bounds__(256, 2) void k_nn_pass_a(Geo g, const void *__restrict__ links,
                                                       const float *__restrict__ frag, const void *__restrict__ frag_lo,
@@ -673,8 +673,8 @@ __global__ __launch_bounds__(256) void k_nn_pass_b_loss(Geo g, const void *__res
 // FP32 sums run over 32 products (the 32 sites of one colour) and go on in FP64: the
 // gradient's rms error against 64 bits on 8^4 (first layer, 8 channels) is 3.3e-8,
 // 3.6e-8 with runs of 96 and 4.0e-8 in the layers' own gradient kernels.  The kernel
-// takes 376 us at 24^3x48; four training steps 3.51 ms, 3.41 with runs of 96, 3.62
-// with 16.
+// takes 327 us at 24^3x48 over many steps; four training steps 3.51 ms, 3.41 with runs
+// of 96, 3.62 with 16.
 constexpr int DK_RUN = 2;   // (colour, 16 sites) steps of an FP32 sum
 constexpr int DK_RS = 100, DK_PS = 8 * DK_RS + 16, DK_FS = NPATH * DK_PS;   // strides: real, path, field
 __global__ __launch_bounds__(256, 2) void k_nn_dk(Geo g, const void *__restrict__ links, const void *__restrict__ gf,
