@@ -268,8 +268,8 @@ __device__ __forceinline__ void path_use(const PathIn<SIN> &in, int h, cpx<float
 // (g, n)'s eight reals of a path and colour are a 16x16x32 B operand as they stand).
 // K's rounding is the same at every site, so in the loss and the gradient it does
 // not average out: the loss at 24^3x48 is 2.2e-9 off its 64-bit value without and
-// 3.3e-11 with, the largest gradient entry on 8^4 9.3e-8 and 3.9e-8.  The products take
-// a twelfth of the FP32 ones' time: 269 us over many steps at 24^3x48.
+// 3.3e-11 with, and K's rounding alone moves the largest gradient entry on 8^4 by 6.2e-8.
+// The products take a twelfth of the FP32 ones' time: 269 us over many steps at 24^3x48.
 template <int SIN, bool NT, bool LO>
 __global__ __launch_bounds__(256, 2) void k_nn_pass_a(Geo g, const void *__restrict__ links,
                                                       const float *__restrict__ frag, const void *__restrict__ frag_lo,
